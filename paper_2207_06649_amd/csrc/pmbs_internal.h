@@ -39,8 +39,9 @@ struct pmbs_sim {
   float* d_x_rewards;      // [max_envs][max_horizon] extra simulations' rewards (planner, server)
   int32_t* d_x_counts;     // [max_envs]
   uint32_t* d_valid;       // [max_envs][PMBS_VALID_WORDS] start-pose validity words
-  int cus = 0, occ[3][2] = {{0, 0}, {0, 0}, {0, 0}};   // CUs; resident blocks per CU of the
-                                                      // 128/256/512 kernels, 1 or 2 waves per env
+  // CUs; resident blocks per CU of the kernels by shape_index (128 contacts
+  // with the 16-box layout, 256, 512, 128 with the 31-box layout) and waves per env
+  int cus = 0, occ[4][2] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};
   pmbs_launch_plan plan;
   // internal streams and events for the concurrent class launches and graph capture
   hipStream_t side = nullptr, cap = nullptr;
@@ -59,6 +60,8 @@ struct pmbs_sim {
   int stage_k = 0;
   int32_t n_envs, n_bodies;
   std::vector<int32_t> host_offset;
+  int32_t max_nb = 0;         // most bodies of any env of host_offset
+  int graph_small_nb = 0;     // most bodies of the captured 128-contact kernel's envs
   bool pool_layout = false;   // envs live only in pool slots, body constants at d_bc_base rows
   ~pmbs_sim();
 };
@@ -130,8 +133,11 @@ int64_t work_weight(const pmbs_sim_t* sim, const int32_t* act_offset, int e);
 void share_pool(pmbs_sim_t* sim, const pmbs_sim_t* from);
 // waves per environment of a contact class under the launch plan
 int plan_waves(const pmbs_sim_t* sim, int max_contacts);
+// most bodies of the envs that a queued rollout gives the 128-contact kernel
+int small_nb(const pmbs_sim_t* sim);
+int shape_index(int max_contacts, int max_nb);
 // workgroups of a persistent launch of the given contact class and shape
-int class_grid(pmbs_sim_t* sim, int max_contacts, int blocks_per_cu, int waves);
+int class_grid(pmbs_sim_t* sim, int max_contacts, int blocks_per_cu, int waves, int max_nb);
 // the queued rollout launches (all contact classes and fallbacks) on
 // `stream`, then the children's validity words when va is given
 hipError_t enqueue_queued(pmbs_sim_t* sim, const StepArgs& a, hipStream_t stream, bool skip_empty, int n_small,

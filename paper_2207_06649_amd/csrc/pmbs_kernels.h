@@ -111,18 +111,20 @@ struct PoolArgs {
 };
 
 hipError_t launch_pool(const PoolArgs& a, hipStream_t stream);
-// resident workgroups per CU of a contact class with 1 or 2 waves per env
-int step_blocks_per_cu(int max_contacts, int waves);
+// The step kernel is chosen by contact class, waves per env (1 or 2) and
+// max_nb, the most boxes that any env of the launch has.
+// resident workgroups per CU
+int step_blocks_per_cu(int max_contacts, int waves, int max_nb);
 // one workgroup per env (no queue), of 1 or 2 waves
-hipError_t launch_step(const StepArgs& a, int max_contacts, hipStream_t stream, int waves = 1);
+hipError_t launch_step(const StepArgs& a, int max_contacts, hipStream_t stream, int waves, int max_nb);
 // persistent queue launch of one contact class without resetting the queue
 // counter (the caller clears it, e.g. with launch_zero)
-hipError_t launch_step_class(const StepArgs& a, int max_contacts, hipStream_t stream, int grid, int waves = 1);
+hipError_t launch_step_class(const StepArgs& a, int max_contacts, hipStream_t stream, int grid, int waves, int max_nb);
 // cost pass: one block per env writes a.cost_key[e], the env's work
 // estimate (contacts + candidate pairs at the start pose, + 3 for a valid
 // push); order: each XCD's contiguous run of envs by descending estimate
 // into order[0, n), and the eight queue counters queue[0..7] cleared
-hipError_t launch_cost(const StepArgs& a, int max_contacts, hipStream_t stream, int waves = 1);
+hipError_t launch_cost(const StepArgs& a, int max_contacts, hipStream_t stream, int waves, int max_nb);
 hipError_t launch_order(const int* key, int n, int* order, int* queue, hipStream_t stream);
 hipError_t launch_zero(int* p, int n, hipStream_t stream);
 hipError_t launch_reward(const RewardArgs& a, hipStream_t stream);

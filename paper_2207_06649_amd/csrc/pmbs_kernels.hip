@@ -1,18 +1,17 @@
 // pmbs_kernels.hip -- CDNA4 (gfx950) kernels of the batched push transition.
 //
-// One 64-lane wavefront advances one environment (cuboids on a plane plus a
-// kinematic box pusher) through a push: the batch expansion / simulation of
-// PMBS (Sec. IV-C), with the transition of Sec. III-A made explicit.
+// One 64-lane wavefront (or two) advances one environment (cuboids on a plane
+// plus a kinematic box pusher) through a push: the batch expansion /
+// simulation of PMBS (Sec. IV-C), with the transition of Sec. III-A made
+// explicit.
 //
-// Lane roles inside a wave (b = lane & 31):
-//   lane b       owns body b's position and linear velocity
-//   lane b + 32  owns body b's orientation, angular velocity, world inverse
-//                inertia (so two lanes carry every body)
-//   lane l       holds contacts l, l+64, l+128, ... in VGPR slots (K slots)
-// Shared state goes through LDS: body frames, AABBs, the broadphase order
-// and pair list, the contact staging array (reused for the impulse exchange of the
-// solver), per-body incidence lists, warm-start keys and impulses, and the
-// clip polygons of face clipping.
+// Lane roles inside the lead wave: four lanes per body in the 16-box layout,
+// two in the 31-box layout, all holding the body's whole state and together
+// its first four table contacts; every other contact is a row contact, one
+// per lane and slot.  Shared state goes through LDS: body frames, AABBs, the
+// pair list, the row contacts' staging array (reused for the impulse exchange
+// of the solver), per-body incidence lists, warm-start keys and impulses, and
+// the clip polygons of face clipping.
 //
 // Per substep (all in one launch, state stays in registers/LDS; HBM is
 // touched once in and once out per call):
@@ -30,9 +29,6 @@
 namespace pmbs {
 
 constexpr int MAXB = 32;             // boxes (<= 31) + the pusher
-constexpr int PLANE = MAXB;          // LDS index of the table
-constexpr int NOBJ = MAXB + 1;
-constexpr int MAX_PAIRS = MAXB * (MAXB - 1) / 2;
 constexpr int CLIP_GROUPS = 8;       // pairs per narrowphase pass (8-lane groups)
 constexpr int POLY = 8;              // clip polygon capacity
 
@@ -87,6 +83,15 @@ __device__ __forceinline__ int wave_excl_scan(int x, int* total) {
   return v - x;
 }
 
+// An opaque copy of a value: address arithmetic built from it stays where it
+// is used (otherwise one 64-bit row offset per state row is computed at the
+// start, shared by every later load and store of the rows, and held in
+// registers, or scratch, for the whole kernel).
+__device__ __forceinline__ int opaque(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
 // Orders the LDS accesses of the wave's lanes around this point.  A
 // workgroup is one wave and a wave's LDS operations are performed in issue
 // order, so a wavefront-scope fence (no wait instruction) plus a
@@ -102,9 +107,15 @@ __device__ __forceinline__ void wave_sync() {
 __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ __forceinline__ float rsq(float x) { return __builtin_amdgcn_rsqf(x); }
 
-template <int K, int W>
+// NB: box capacity of the layout, 16 or 31 (NB 32 leaves one object for the
+// pusher).
+template <int K, int W, int NB>
 struct Smem {
   static constexpr int C = 64 * K;
+  static constexpr int MB = NB == 16 ? 17 : 32;   // boxes + the pusher
+  static constexpr int PLANE = MB;                // LDS index of the table
+  static constexpr int NOBJ = MB + 1;
+  static constexpr int MAX_PAIRS = MB * (MB - 1) / 2;
   float4 pos[NOBJ];                  // centre
   float4 col[3][NOBJ];               // rotation columns (body axes in world)
   float4 half[NOBJ];                 // hx, hy, hz, inverse mass
@@ -113,49 +124,51 @@ struct Smem {
   float4 vel[NOBJ];                  // solver snapshot: linear
   float4 ang[NOBJ];                  // solver snapshot: angular
   int cnt[NOBJ];                     // contacts touching each body (mass splitting)
-  // Per-body incidence lists, each padded to a multiple of 8 entries, as
-  // ready impulse-row codes: byte offset of the row from the first impulse
-  // row | side (1 = b); list 0 for the linear sums (row P), list 1 for the
-  // angular sums (row ra x P or rb x P).  Padding codes point at the zero row.
-  unsigned short inc[2][2 * C + 8 * MAXB];
-  float4 lo[MAXB], hi[MAXB];         // AABBs: min and max corner (x, y, z, -)
-  int sorted[W > 1 ? MAXB : 1];      // two waves: objects in min-x order (kept while still ordered)
-  int lstart[MAXB];                  // incidence list starts
-  unsigned mask[W > 1 ? MAXB : 1];   // two waves: sweep pair masks
+  // Per-body incidence lists of the row contacts: contact index * 16 | side
+  // (1 = b), in contact-index order.
+  unsigned short inc[2 * C];
+  int lstart[MB];                    // incidence list starts
   unsigned short pairs[MAX_PAIRS];
-  int cab[C];                        // packed a | b << 8 | feature << 16 of each contact
-  int wkey[C];                       // previous substep's contact keys (sorted)
+  int cab[C];                        // packed a | b << 8 | feature << 16 of each row contact
+  int wkey[C];                       // previous substep's row-contact keys (sorted)
   float wl[3][C];                    // and their accumulated impulses (n, t1, t2)
   union {
-    float4 stage[C][2];              // narrowphase output: (p, sep), (n, -)
+    struct {
+      float4 stage[C][2];            // narrowphase output: (p, sep), (n, -)
+      union alignas(16) {
+        struct {
+          float4 lo[MB], hi[MB];     // AABBs: min and max corner (x, y, z, -)
+        } box;
+        // each wave's own narrowphase scratch (no wave writes another's):
+        // first the axis candidates of its eight groups (separation value and
+        // unit axis, x, y, z rows), then their clip polygons
+        union alignas(16) {
+          struct {
+            float v[CLIP_GROUPS][16];
+            float ax[3][CLIP_GROUPS][16];
+          } cand;
+          float clip[2][POLY][3][CLIP_GROUPS];
+        } wave[W];
+        unsigned incm[NOBJ][2 * K];  // incidence build: contact bit masks per body
+        float4 lam[MB * 4];          // table impulses (n, t1, t2) and corner mask of a changed corner set
+      } x;
+    } n;
     float4 imp[3][C];                // solver exchange: P, ra x P, rb x P
   } u;
   float4 zero;                       // a row of zeros after the impulse rows (never written)
-  union alignas(16) {
-    // each wave's own narrowphase scratch (no wave writes another's):
-    // first the axis candidates of its eight groups (separation value and
-    // unit axis, x, y, z rows), then their clip polygons
-    union alignas(16) {
-      struct {
-        float v[CLIP_GROUPS][16];
-        float ax[3][CLIP_GROUPS][16];
-      } cand;
-      float clip[2][POLY][3][CLIP_GROUPS];
-    } wave[W];
-    unsigned incm[NOBJ][2 * K];             // incidence build: contact bit masks per body
-  } x;
   // counts the waves of an environment exchange: candidate pairs, table
-  // contacts, and each wave's kept contacts of a narrowphase round (by the
-  // round's parity)
-  int sh_pairs, sh_plane;
+  // contacts (all, those held by the body lanes, those staged as rows), and
+  // each wave's kept contacts of a narrowphase round (by the round's parity)
+  int sh_pairs, sh_table, sh_held, sh_extra;
   int rcount[2][W];
 };
 
 // Contact key (a+1, b, feature) with the table as a = -1: strictly
 // increasing along the contact list, so the previous list is searchable.
+template <class S>
 __device__ __forceinline__ int contact_key(int ab) {
   const int a = ab & 255, b = (ab >> 8) & 255, f = ab >> 16;
-  return ((a == PLANE ? 0 : a + 1) << 16) | (b << 8) | f;
+  return ((a == S::PLANE ? 0 : a + 1) << 16) | (b << 8) | f;
 }
 
 // ------------------------------------------------------------------ geometry
@@ -285,44 +298,31 @@ __device__ __forceinline__ unsigned long long validity_bits(const S& s, int nb, 
   return __ballot(ok);
 }
 
-// An opaque copy of a value: address arithmetic built from it stays where it
-// is used (otherwise one 64-bit row offset per state row is computed at the
-// start, shared by every later load and store of the rows, and held in
-// registers, or scratch, for the whole kernel).
-__device__ __forceinline__ int opaque(int x) {
-  asm volatile("" : "+v"(x));
-  return x;
-}
 
-// The two halves of the wave, lane by lane (v_permlane32_swap): lane l
-// receives the value of lane l & 31 from lower_half and of lane
-// 32 + (l & 31) from upper_half.
-__device__ __forceinline__ int lower_half(int v) { return __builtin_amdgcn_permlane32_swap(v, v, false, false)[0]; }
-__device__ __forceinline__ int upper_half(int v) { return __builtin_amdgcn_permlane32_swap(v, v, false, false)[1]; }
-
-// Whole-wave shift by one lane (DPP wave_shl:1): lane l receives lane l + 1;
-// lane 63 receives 0 (a float) or the value's own bits (an int).  Callers
-// read only lanes below the object count (at most 33), never lane 63.
-__device__ __forceinline__ float wave_next(float v) {
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x130, 0xf, 0xf, true));
+// A DPP quad permutation of a value: lane i of each four takes lane
+// (CTRL >> 2 i) & 3 of them.
+template <int CTRL>
+__device__ __forceinline__ float quad(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
 }
-// value of lane ^ 1 (DPP quad permutation 1, 0, 3, 2)
-__device__ __forceinline__ float pair_swap(float v) {
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xb1, 0xf, 0xf, true));
+template <int CTRL>
+__device__ __forceinline__ f3 quad(f3 v) {
+  return mk(quad<CTRL>(v.x), quad<CTRL>(v.y), quad<CTRL>(v.z));
 }
-__device__ __forceinline__ int wave_next(int v) { return __builtin_amdgcn_update_dpp(v, v, 0x130, 0xf, 0xf, false); }
+constexpr int Q_XOR1 = 0xb1, Q_XOR2 = 0x4e;   // lane ^ 1, lane ^ 2
+constexpr int Q_LOW = 0x44, Q_HIGH = 0xee;    // lanes 0, 1, 0, 1 and 2, 3, 2, 3
 
 // ------------------------------------------------------------------ clipping
 // the clip buffers of wave wid
 template <class S>
 __device__ __forceinline__ f3 cl_get(const S& s, int wid, int buf, int i, int grp) {
-  return mk(s.x.wave[wid].clip[buf][i][0][grp], s.x.wave[wid].clip[buf][i][1][grp], s.x.wave[wid].clip[buf][i][2][grp]);
+  return mk(s.u.n.x.wave[wid].clip[buf][i][0][grp], s.u.n.x.wave[wid].clip[buf][i][1][grp], s.u.n.x.wave[wid].clip[buf][i][2][grp]);
 }
 template <class S>
 __device__ __forceinline__ void cl_put(S& s, int wid, int buf, int i, int grp, f3 v) {
-  s.x.wave[wid].clip[buf][i][0][grp] = v.x;
-  s.x.wave[wid].clip[buf][i][1][grp] = v.y;
-  s.x.wave[wid].clip[buf][i][2][grp] = v.z;
+  s.u.n.x.wave[wid].clip[buf][i][0][grp] = v.x;
+  s.u.n.x.wave[wid].clip[buf][i][1][grp] = v.y;
+  s.u.n.x.wave[wid].clip[buf][i][2][grp] = v.z;
 }
 
 // Previous lane of each 8-lane group, lane 0 of a group taking lane 7: DPP
@@ -419,6 +419,19 @@ struct Contact {
   float ln, lt1, lt2;
 };
 
+// Index of a key in the previous substep's row contacts, -1 when absent.
+template <class S>
+__device__ __forceinline__ int warm_index(const S& s, int key, int nwarm) {
+  int lo = 0, hi = nwarm - 1;
+  while (lo <= hi) {
+    const int mid = (lo + hi) >> 1, km = s.wkey[mid];
+    if (km == key) return mid;
+    if (km < key) lo = mid + 1;
+    else hi = mid - 1;
+  }
+  return -1;
+}
+
 template <class S>
 __device__ __forceinline__ float eff_mass_side(const S& s, int i, f3 r, f3 d) {
   f3 cr = cross(r, d);
@@ -430,12 +443,11 @@ __device__ __forceinline__ float eff_mass_side(const S& s, int i, f3 r, f3 d) {
   return s.half[i].w + dot(cr, m);
 }
 
-// side_a: some contact of the lane's slot has a body on side a (else every
-// one touches the table there, whose effective-mass terms are exactly zero:
-// ca x 0 + cb x m_b rounds as cb x m_b alone, so skipping them changes no bit)
+// Row contact c of the staging array into registers, with its previous
+// impulse when the key was there (nwarm keys).
 template <class S>
-__device__ __forceinline__ void prep_contact(const S& s, int c, const Params& p, int nwarm, bool side_a, Contact* ct) {
-  float4 s0 = s.u.stage[c][0], s1 = s.u.stage[c][1];
+__device__ __forceinline__ void prep_contact(const S& s, int c, const Params& p, int nwarm, Contact* ct) {
+  const float4 s0 = s.u.n.stage[c][0], s1 = s.u.n.stage[c][1];
   f3 pt = xyz(s0);
   float sep = s0.w;
   int ab = s.cab[c];
@@ -454,36 +466,61 @@ __device__ __forceinline__ void prep_contact(const S& s, int c, const Params& p,
   ct->t2 = t2;
   ct->t1 = t1;
   float ca = (float)s.cnt[a], cb = (float)s.cnt[b];
-  if (side_a) {
-    ct->kn = rcp(ca * eff_mass_side(s, a, ct->ra, n) + cb * eff_mass_side(s, b, ct->rb, n));
-    ct->kt1 = rcp(ca * eff_mass_side(s, a, ct->ra, t1) + cb * eff_mass_side(s, b, ct->rb, t1));
-    ct->kt2 = rcp(ca * eff_mass_side(s, a, ct->ra, t2) + cb * eff_mass_side(s, b, ct->rb, t2));
-  } else {
-    ct->kn = rcp(cb * eff_mass_side(s, b, ct->rb, n));
-    ct->kt1 = rcp(cb * eff_mass_side(s, b, ct->rb, t1));
-    ct->kt2 = rcp(cb * eff_mass_side(s, b, ct->rb, t2));
-  }
+  ct->kn = rcp(ca * eff_mass_side(s, a, ct->ra, n) + cb * eff_mass_side(s, b, ct->rb, n));
+  ct->kt1 = rcp(ca * eff_mass_side(s, a, ct->ra, t1) + cb * eff_mass_side(s, b, ct->rb, t1));
+  ct->kt2 = rcp(ca * eff_mass_side(s, a, ct->ra, t2) + cb * eff_mass_side(s, b, ct->rb, t2));
   ct->mu = 0.5f * (s.iwb[a].z + s.iwb[b].z);
   ct->vstar = sep > 0.0f ? -sep * p.inv_dt : p.beta * fmaxf(-sep - p.slop, 0.0f) * p.inv_dt;
   // warm start from the previous substep's contact with the same key
   ct->ln = ct->lt1 = ct->lt2 = 0.0f;
-  const int key = contact_key(ab);
-  int lo = 0, hi = nwarm - 1;
-  if (c < nwarm && s.wkey[c] == key) {   // unchanged list prefix: same index
-    lo = hi = c;
+  const int key = contact_key<S>(ab);
+  // an unchanged list prefix has it at the same index
+  const int i = c < nwarm && s.wkey[c] == key ? c : warm_index(s, key, nwarm);
+  if (i >= 0) {
+    ct->ln = s.wl[0][i];
+    ct->lt1 = s.wl[1][i];
+    ct->lt2 = s.wl[2][i];
   }
-  while (lo <= hi) {
-    const int mid = (lo + hi) >> 1;
-    const int km = s.wkey[mid];
-    if (km == key) {
-      ct->ln = s.wl[0][mid];
-      ct->lt1 = s.wl[1][mid];
-      ct->lt2 = s.wl[2][mid];
-      break;
-    }
-    if (km < key) lo = mid + 1;
-    else hi = mid - 1;
-  }
+}
+
+// A table contact: normal z, tangents -y and x, nothing on side a.  The
+// impulse of changes (dn, d1, d2) is (d2, -d1, dn) exactly.
+struct TableContact {
+  f3 rb;
+  float kn, kt1, kt2, vstar;
+  float ln, lt1, lt2;
+};
+
+// r x z, r x -y and r x x against a symmetric matrix a (xx, yy, zz), o (xy,
+// xz, yz): the effective-mass products of the general contact with the terms
+// that are exactly zero left out, in the same order.
+__device__ __forceinline__ f3 table_masses(f3 r, f3 a, f3 o) {
+  const float n_x = r.y, n_y = -r.x;
+  const float n_mx = fmaf(a.x, n_x, o.x * n_y), n_my = fmaf(o.x, n_x, a.y * n_y);
+  const float u_x = r.z, u_z = -r.x;
+  const float u_mx = fmaf(o.y, u_z, a.x * u_x), u_mz = fmaf(a.z, u_z, o.y * u_x);
+  const float v_y = r.z, v_z = -r.y;
+  const float v_my = fmaf(o.z, v_z, a.y * v_y), v_mz = fmaf(a.z, v_z, o.z * v_y);
+  return mk(fmaf(n_x, n_mx, n_y * n_my), fmaf(u_z, u_mz, u_x * u_mx), fmaf(v_z, v_mz, v_y * v_my));
+}
+
+// Half extents along x, y, z of the margin-inflated AABB of a box.
+__device__ __forceinline__ f3 aabb_ext(f3 a0, f3 a1, f3 a2, f3 hh, float margin) {
+  return mk(fabsf(a0.x) * hh.x + fabsf(a1.x) * hh.y + fabsf(a2.x) * hh.z + margin,
+            fabsf(a0.y) * hh.x + fabsf(a1.y) * hh.y + fabsf(a2.y) * hh.z + margin,
+            fabsf(a0.z) * hh.x + fabsf(a1.z) * hh.y + fabsf(a2.z) * hh.z + margin);
+}
+
+// Pair number p of the pairs (i, j), i < j < n, in lexicographic order, as
+// i | j << 5; (0, 0) past the last pair.
+__device__ __forceinline__ unsigned pair_of(int p, int n) {
+  if (p >= n * (n - 1) / 2) return 0u;
+  const float m = (float)(2 * n - 1);
+  int i = (int)(0.5f * (m - sqrtf(fmaxf(m * m - 8.0f * (float)p, 0.0f))));
+  i = min(max(i, 0), n - 2);
+  while (i > 0 && i * (2 * n - i - 1) / 2 > p) --i;
+  while ((i + 1) * (2 * n - i - 2) / 2 <= p) ++i;
+  return (unsigned)(i | ((p - i * (2 * n - i - 1) / 2 + i + 1) << 5));
 }
 
 // ------------------------------------------------------------------ footprint distance (reward)
@@ -612,29 +649,52 @@ __device__ __forceinline__ void sync_all() {
 // Runs env e through its pushes: one explicit push (step mode) or a list of
 // contour pushes (rollout mode, with a reward after each push).
 //
-// With W > 1 waves per environment, wave 0 (the lead) runs every phase as a
-// single wave does and owns the bodies; the other waves take the contact
-// slots sl with sl % W == their index (in prep, warm start, the Jacobi
-// contact updates and the warm-start memory) and every W-th narrowphase
-// pass of eight pairs.  Each contact's arithmetic and every per-body sum
-// are those of one wave, in the same order, so the result is bitwise that
-// of W = 1.  Uniform decisions (push validity, rewards, overflow) are taken
-// by every wave from the same LDS data, so all waves run the same loops and
-// meet at the same barriers.
-template <int K, int W, bool COST>
-__device__ __forceinline__ void run_env(Smem<K, W>& s, const StepArgs& g, const int e) {
-  constexpr int C = Smem<K, W>::C;
-  constexpr int KW = K / W;  // contact slots per wave
-  static_assert(K % W == 0, "contact slots split evenly over the waves");
+// Body lanes: L lanes of the lead wave carry each body (lane b L + j), four
+// in the 16-box layout and two in the 31-box one.  All of them hold its whole
+// state, and together its first four table contacts (contact j + L ts in slot
+// ts): a table contact's only body is the lanes' own, so its update needs no
+// memory, and the body's sum over these contacts is a DPP exchange among
+// the L lanes.  The other contacts (pairs, the pusher, a box's fifth and
+// later table corner) are row contacts: one per lane of the lead wave and
+// slot, their velocities gathered from and their impulse rows left in LDS,
+// where the body lanes add them after the table contacts, the even and the
+// odd entries of the body's contact list separately, as ever.
+//
+// Bound: the vector ALU and the LDS pipe, each about half busy before (2076
+// VALU instructions and 2061 LDS cycles per env-substep at 4096 x 15, 3866
+// cycles of a CU), most of them in the ten iterations, whose every contact
+// gathered four velocities from LDS, left three rows there and had them read
+// back.  Nineteen of twenty contacts are table contacts: normal z, tangents
+// -y and x, nothing on side a.  With the terms that are exactly zero left out
+// (the same bits) and the body in the same lanes such a contact costs 28
+// instructions instead of 61 and no LDS, and an environment of which no box
+// touches another iterates without LDS at all.  4096 x 15: 3.15 -> 2.29 ms;
+// 700 x 27: 2.66 -> 1.89; 1024 x 15 on two waves: 1.50 -> 1.31; 64 x 9, one
+// wave per SIMD: 1.19 -> 1.14.
+//
+// With W > 1 waves per environment the second wave tests the broadphase pairs
+// while the lead finds the table contacts, and takes every second narrowphase
+// pass of eight pairs; the results are bitwise those of W = 1.  Uniform
+// decisions (push validity, rewards, overflow) are taken by every wave from
+// the same LDS data, so all waves run the same loops and meet at the same
+// barriers.
+template <int K, int W, int NB, bool COST>
+__device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, const int e) {
+  using S = Smem<K, W, NB>;
+  constexpr int C = S::C, PLANE = S::PLANE, MB = S::MB;
+  constexpr int L = NB == 16 ? 4 : 2;   // lanes per body
+  constexpr int TS = 4 / L;             // table contacts per lane
   const Params& p = g.p;
-  const int lane = threadIdx.x & 63;
+  // opaque: what follows from the lane number is formed anew for each env
+  // and substep; kept over them it fills the registers with addresses
+  const int lane = opaque(threadIdx.x & 63);
   const int wid = W > 1 ? (int)(threadIdx.x >> 6) : 0;
   const bool lead = wid == 0;
-  const int b = lane & 31;
-  const int part = lane >> 5;
+  const int b = lane / L, j = lane % L;
   const int base = g.env_offset[e];
   const int nb = g.env_offset[e + 1] - base;
   const bool active = lead && b < nb;  // a lane of the lead wave that owns a body
+  const bool first = active && j == 0;
   const int N = g.stride;
   const float dt = p.dt;
   const bool rollout = g.actions != nullptr;
@@ -643,10 +703,9 @@ __device__ __forceinline__ void run_env(Smem<K, W>& s, const StepArgs& g, const 
   const int src = (rollout && g.src_slot) ? g.src_slot[e] : -1;
   const int PS = g.pool_stride;
 
-  // ---- load (coalesced SoA): part 0 linear, part 1 angular; from the env
-  // arrays or from the state pool slot of the node being expanded
-  // vl is the lane's own velocity: linear on part 0, angular on part 1
-  f3 x = mk(0, 0, 0), vl = mk(0, 0, 0), h = mk(0, 0, 0), invI = mk(0, 0, 0);
+  // ---- load (SoA rows; the lanes of a body read the same words), from the
+  // env arrays or from the state pool slot of the node being expanded
+  f3 x = mk(0, 0, 0), v = mk(0, 0, 0), w = mk(0, 0, 0), h = mk(0, 0, 0), invI = mk(0, 0, 0);
   float q0 = 1, q1 = 0, q2 = 0, q3 = 0, invm = 0, mu = 0;
   if (active) {
     const int i = base + b;
@@ -656,58 +715,54 @@ __device__ __forceinline__ void run_env(Smem<K, W>& s, const StepArgs& g, const 
     const float* bc = g.bconst;
     const int BN = g.bc_base ? g.bc_stride : N;
     const int bi = g.bc_base ? g.bc_base[e] + b : i;
-    if (part == 0) {
-      x = mk(st[0 * SN + si], st[1 * SN + si], st[2 * SN + si]);
-      vl = mk(st[7 * SN + si], st[8 * SN + si], st[9 * SN + si]);
-      invm = bc[3 * BN + bi];
-    } else {
-      q0 = st[3 * SN + si]; q1 = st[4 * SN + si]; q2 = st[5 * SN + si]; q3 = st[6 * SN + si];
-      vl = mk(st[10 * SN + si], st[11 * SN + si], st[12 * SN + si]);
-      invI = mk(bc[4 * BN + bi], bc[5 * BN + bi], bc[6 * BN + bi]);
-    }
+    x = mk(st[0 * SN + si], st[1 * SN + si], st[2 * SN + si]);
+    q0 = st[3 * SN + si]; q1 = st[4 * SN + si]; q2 = st[5 * SN + si]; q3 = st[6 * SN + si];
+    v = mk(st[7 * SN + si], st[8 * SN + si], st[9 * SN + si]);
+    w = mk(st[10 * SN + si], st[11 * SN + si], st[12 * SN + si]);
     h = mk(bc[0 * BN + bi], bc[1 * BN + bi], bc[2 * BN + bi]);
+    invm = bc[3 * BN + bi];
+    invI = mk(bc[4 * BN + bi], bc[5 * BN + bi], bc[6 * BN + bi]);
     mu = bc[7 * BN + bi];
   }
   const f3 ph = mk(p.phx, p.phy, p.phz);
+  const float mu_table = 0.5f * (p.mu_plane + mu);
+  // what no substep changes: half extents, and the pusher entry (index nb)
+  if (first) s.half[b] = f4(h, invm);
+  if (lead && lane == 0) {
+    s.half[nb] = f4(ph, 0.0f);
+    s.iwa[nb] = make_float4(0, 0, 0, 0);
+    s.iwb[nb] = make_float4(0, 0, p.mu_pusher, 0);
+    s.ang[nb] = make_float4(0, 0, 0, 0);
+    s.cnt[nb] = 1;
+  }
 
-  // frames of the bodies (centre, rotation, inverse mass / inertia)
-  auto write_body_frames = [&]() {
-    if (active) {
-      if (part == 0) {
-        s.pos[b] = f4(x, 0.0f);
-        s.half[b] = f4(h, invm);
-        s.vel[b] = f4(vl, 0.0f);
-      } else {
-        s.ang[b] = f4(vl, 0.0f);
-        f3 c0, c1, c2;
-        quat_cols(q0, q1, q2, q3, &c0, &c1, &c2);
-        const float r00 = c0.x, r01 = c1.x, r02 = c2.x;
-        const float r10 = c0.y, r11 = c1.y, r12 = c2.y;
-        const float r20 = c0.z, r21 = c1.z, r22 = c2.z;
-        s.col[0][b] = f4(c0, 0.0f);
-        s.col[1][b] = f4(c1, 0.0f);
-        s.col[2][b] = f4(c2, 0.0f);
-        // Iw^-1 = R diag(invI) R^T
-        float xx = r00 * invI.x * r00 + r01 * invI.y * r01 + r02 * invI.z * r02;
-        float yy = r10 * invI.x * r10 + r11 * invI.y * r11 + r12 * invI.z * r12;
-        float zz = r20 * invI.x * r20 + r21 * invI.y * r21 + r22 * invI.z * r22;
-        float xy = r00 * invI.x * r10 + r01 * invI.y * r11 + r02 * invI.z * r12;
-        float xz = r00 * invI.x * r20 + r01 * invI.y * r21 + r02 * invI.z * r22;
-        float yz = r10 * invI.x * r20 + r11 * invI.y * r21 + r12 * invI.z * r22;
-        s.iwa[b] = make_float4(xx, yy, zz, xy);
-        s.iwb[b] = make_float4(xz, yz, mu, 0.0f);
-      }
+  // frames of the bodies (centre, rotation)
+  f3 c0, c1, c2;
+  auto write_body_frames = [&](int b, bool first) {
+    quat_cols(q0, q1, q2, q3, &c0, &c1, &c2);
+    if (first) {
+      st3(&s.pos[b], x);
+      st3(&s.col[0][b], c0);
+      st3(&s.col[1][b], c1);
+      st3(&s.col[2][b], c2);
     }
   };
 
-  Contact ct[KW];
   bool deferred = false;
   uint32_t status = 0u;
   float last_r = 0.0f;
   int n_rewards = 0;
   long long stat_nc = 0, stat_pairs = 0, stat_sub = 0;
   const int n_obj = nb + 1;
-  bool order_kept = false;  // s.sorted holds a permutation of this env's objects
+  // the lane's broadphase pairs, pass k's in bits 10 (k mod 3) .. of word k / 3
+  const int n_tri = n_obj * (n_obj - 1) / 2;
+  constexpr int PASSES = (S::MAX_PAIRS + 63) / 64;
+  unsigned tri[(PASSES + 2) / 3];
+#pragma unroll
+  for (int k = 0; k < PASSES; ++k) {
+    const unsigned ij = pair_of(64 * k + lane, n_obj) << (10 * (k % 3));
+    tri[k / 3] = k % 3 ? tri[k / 3] | ij : ij;
+  }
 
   // job 0 is the env's own simulation; job 1 (re-purposing) is one extra
   // simulation of another pair that spends the pushes left when job 0
@@ -716,7 +771,7 @@ __device__ __forceinline__ void run_env(Smem<K, W>& s, const StepArgs& g, const 
   for (int job = 0; job < 2; ++job) {
   for (int t = 0; t < n_push; ++t) {
   // ---- push begin (uniform across the workgroup)
-  write_body_frames();
+  write_body_frames(b, first);
   sync_all<W>();
   bool have_push;
   float4 push = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
@@ -754,36 +809,16 @@ __device__ __forceinline__ void run_env(Smem<K, W>& s, const StepArgs& g, const 
     pc1 = pq.c1;
   }
 
-  // the pusher entry (index nb)
-  auto write_pusher = [&](f3 vp) {
-    if (lead && lane == 32) {
-      s.pos[nb] = f4(xp, 0.0f);
-      s.col[0][nb] = f4(pc0, 0.0f);
-      s.col[1][nb] = f4(pc1, 0.0f);
-      s.col[2][nb] = make_float4(0, 0, 1, 0);
-      s.half[nb] = f4(ph, 0.0f);
-      s.iwa[nb] = make_float4(0, 0, 0, 0);
-      s.iwb[nb] = make_float4(0, 0, p.mu_pusher, 0);
-      s.vel[nb] = f4(vp, 0.0f);
-      s.ang[nb] = make_float4(0, 0, 0, 0);
-      s.cnt[nb] = 1;
-    }
-  };
-  auto write_frames = [&](f3 vp) {
-    write_body_frames();
-    write_pusher(vp);
-  };
-
   // validity of the start pose: SAT separation from every box must be > 0
   bool valid = false;
   if (have_push) {
     bool bad = false;
-    if (b < nb && part == 0) {   // every wave tests the boxes from LDS: the same decision
+    if (lane < nb) {   // every wave tests the boxes from LDS: the same decision
       PusherPose pq;
       pq.x = xp;
       pq.c0 = pc0;
       pq.c1 = pc1;
-      bad = !sat_clear(load_box(s, b), pusher_box(pq, p), p.edge_eps);
+      bad = !sat_clear(load_box(s, lane), pusher_box(pq, p), p.edge_eps);
     }
     valid = __ballot(bad) == 0;
   }
@@ -803,206 +838,159 @@ __device__ __forceinline__ void run_env(Smem<K, W>& s, const StepArgs& g, const 
     else n_rewards_x = t + 1;
     continue;
   }
+  // the pusher's rotation is fixed for the push
+  if (lead && lane == 0) {
+    st3(&s.col[0][nb], pc0);
+    st3(&s.col[1][nb], pc1);
+    st3(&s.col[2][nb], mk(0, 0, 1));
+  }
+  const f3 pext = aabb_ext(pc0, pc1, mk(0, 0, 1), ph, p.margin);
 
   const int n_sub = g.collide_only ? 1 : g.n_substeps;
-  int nwarm = 0;  // impulses are carried within one push only
+  // impulses are carried within one push only: the row contacts' (nwarm of
+  // them, in LDS) and the table contacts', in the lanes, whose corners are
+  // the bits of corners
+  int nwarm = 0;
+  unsigned corners = 0u;
+  TableContact tc[TS];
+  int kk[TS];
+#pragma unroll
+  for (int ts = 0; ts < TS; ++ts) {
+    tc[ts].ln = tc[ts].lt1 = tc[ts].lt2 = 0.0f;
+    kk[ts] = 0;
+  }
+  int n_inc = 0, inc0 = 0;   // the lane's body's list of row contacts: length and start
   for (int k = 0; k < n_sub; ++k) {
+    const int lane = opaque(threadIdx.x & 63), b = lane / L, j = lane % L;
+    const bool active = lead && b < nb, first = active && j == 0;
     // ---- 1. velocity stage
-    if (active && part == 0) vl.z -= p.gravity * dt;
+    v.z -= p.gravity * dt;
     const float vs = (valid && k < n_move) ? p.push_speed : 0.0f;
     f3 vp = pdir * vs;
     if (g.collide_only) vp = mk(0, 0, 0);
 
-    // ---- 2. frames
-    write_frames(vp);
+    // ---- 2. frames and AABBs
+    write_body_frames(b, first);
+    {
+      const f3 ext = aabb_ext(c0, c1, c2, h, p.margin);
+      if (first) {
+        st3(&s.u.n.x.box.lo[b], x - ext);
+        st3(&s.u.n.x.box.hi[b], x + ext);
+      }
+      if (lead && lane == 0) {
+        st3(&s.pos[nb], xp);
+        st3(&s.vel[nb], vp);
+        st3(&s.u.n.x.box.lo[nb], xp - pext);
+        st3(&s.u.n.x.box.hi[nb], xp + pext);
+      }
+    }
+    // world inverse inertia Iw^-1 = R diag(invI) R^T: diagonal, off-diagonal (xy, xz, yz)
+    f3 md, mo;
+    {
+      const float r00 = c0.x, r01 = c1.x, r02 = c2.x;
+      const float r10 = c0.y, r11 = c1.y, r12 = c2.y;
+      const float r20 = c0.z, r21 = c1.z, r22 = c2.z;
+      md.x = r00 * invI.x * r00 + r01 * invI.y * r01 + r02 * invI.z * r02;
+      md.y = r10 * invI.x * r10 + r11 * invI.y * r11 + r12 * invI.z * r12;
+      md.z = r20 * invI.x * r20 + r21 * invI.y * r21 + r22 * invI.z * r22;
+      mo.x = r00 * invI.x * r10 + r01 * invI.y * r11 + r02 * invI.z * r12;
+      mo.y = r00 * invI.x * r20 + r01 * invI.y * r21 + r02 * invI.z * r22;
+      mo.z = r10 * invI.x * r20 + r11 * invI.y * r21 + r12 * invI.z * r22;
+    }
     sync_all<W>();
 
-    // ---- 3.-4a. broadphase (the lead wave) and table contacts (the second
-    // wave when there are two, else the lead after the broadphase)
-    int n_pairs = 0, nc_raw = 0;
-    if (lead) {
-      // ---- 3. broadphase: AABBs, then every pair of objects tested directly
-      // (with two waves per env and more than 16 objects: a rank sort on
-      // min-x and a sweep)
-      if (lane < n_obj) {
-        f3 c = xyz(s.pos[lane]);
-        f3 a0 = xyz(s.col[0][lane]), a1 = xyz(s.col[1][lane]), a2 = xyz(s.col[2][lane]);
-        f3 hh = xyz(s.half[lane]);
-        float ex = fabsf(a0.x) * hh.x + fabsf(a1.x) * hh.y + fabsf(a2.x) * hh.z + p.margin;
-        float ey = fabsf(a0.y) * hh.x + fabsf(a1.y) * hh.y + fabsf(a2.y) * hh.z + p.margin;
-        float ez = fabsf(a0.z) * hh.x + fabsf(a1.z) * hh.y + fabsf(a2.z) * hh.z + p.margin;
-        s.lo[lane] = make_float4(c.x - ex, c.y - ey, c.z - ez, 0.0f);
-        s.hi[lane] = make_float4(c.x + ex, c.y + ey, c.z + ez, 0.0f);
-        if constexpr (W > 1) s.mask[lane] = 0u;
-      }
-      wave_sync();
-      if (W == 1 || n_obj <= 16) {
-        // every pair (i, j), i < j, tested directly: columns j on the lanes
-        // (16 of them up to 16 objects, else 32) and 4 or 2 rows i per pass,
-        // so lane order within a pass and pass order are the pairs'
-        // lexicographic order and a ballot lists the overlapping ones.  With
-        // two waves per env (an env's latency, not throughput, counts) more
-        // than 16 objects take the sort and sweep below, whose DPP steps
-        // have no LDS round trip per pass.
-        const int cs = n_obj <= 16 ? 4 : 5;   // log2 of the columns
-        const int jj = lane & ((1 << cs) - 1);
-        const bool jin = jj < n_obj;
-        const float4 jl = s.lo[jj], jh = s.hi[jj];
-        for (int i0 = 0; i0 < n_obj - 1; i0 += 64 >> cs) {
-          const int ii = i0 + (lane >> cs);
-          const float4 il = s.lo[ii], ih = s.hi[ii];
-          const bool hit = jin && ii < jj && il.x <= jh.x && jl.x <= ih.x && il.y <= jh.y && jl.y <= ih.y &&
-                           il.z <= jh.z && jl.z <= ih.z;
+    // ---- 3. broadphase (the second wave when there are two): every pair
+    // tested directly, 64 per pass in lexicographic order, the overlapping
+    // ones listed by ballot
+    int n_pairs = 0;
+    if (W == 1 || wid == 1) {
+#pragma unroll
+      for (int k2 = 0; k2 < PASSES; ++k2) {
+        if (64 * k2 < n_tri) {
+          const unsigned ij = (unsigned)opaque((int)tri[k2 / 3]) >> (10 * (k2 % 3));
+          const unsigned ii = ij & 31u, jj = (ij >> 5) & 31u;
+          const f3 il = xyz(s.u.n.x.box.lo[ii]), ih = xyz(s.u.n.x.box.hi[ii]);
+          const f3 jl = xyz(s.u.n.x.box.lo[jj]), jh = xyz(s.u.n.x.box.hi[jj]);
+          const bool hit = (ii < jj) & (il.x <= jh.x) & (jl.x <= ih.x) & (il.y <= jh.y) & (jl.y <= ih.y) &
+                           (il.z <= jh.z) & (jl.z <= ih.z);
           const unsigned long long hm = __ballot(hit);
           // rank among the lower lanes' hits (mbcnt)
           const int rk = __builtin_amdgcn_mbcnt_hi((unsigned)(hm >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)hm, 0u));
           if (hit) s.pairs[n_pairs + rk] = (unsigned short)((ii << 8) | jj);
           n_pairs += __popcll(hm);
         }
-      } else {
-        // the previous substep's order is still the order when every object
-        // precedes the next one by (key, index); then the ranks need no update
-        bool order_ok = order_kept;
-        if (order_ok) {
-          const bool in = lane < n_obj;
-          const int o = in ? (s.sorted[lane] & (MAXB - 1)) : 0;
-          float kx = in ? s.lo[o].x : INFINITY;
-          kx = kx == kx ? kx : INFINITY;
-          const float kn = wave_next(kx);
-          const int on = wave_next(o);
-          const bool bad = lane + 1 < n_obj && !(kx < kn || (kx == kn && o < on));
-          order_ok = __ballot(bad) == 0ull;
-        }
-        order_kept = true;
-        if (!order_ok) {
-          // rank of each object's min-x key (ties by index; NaN keys sort last,
-          // so the ranks stay a permutation whatever the state holds)
-          float key = lane < n_obj ? s.lo[lane].x : INFINITY;
-          key = key == key ? key : INFINITY;
-          // lanes past n_obj hold +inf keys and never count, so the loop runs
-          // over fixed lanes (independent readlanes, two counters) with no guard
-          const int ikey = __float_as_int(key);
-          int r0 = 0, r1 = 0;
-    #pragma unroll
-          for (int j = 0; j < 16; ++j) {
-            const float kj = __int_as_float(__builtin_amdgcn_readlane(ikey, j));
-            const int c = (kj < key || (kj == key && j < lane)) ? 1 : 0;
-            if (j & 1) r1 += c;
-            else r0 += c;
-          }
-          if (n_obj > 16) {
-    #pragma unroll
-            for (int j = 16; j < 32; ++j) {
-              const float kj = __int_as_float(__builtin_amdgcn_readlane(ikey, j));
-              const int c = (kj < key || (kj == key && j < lane)) ? 1 : 0;
-              if (j & 1) r1 += c;
-              else r0 += c;
-            }
-          }
-          const int rank = r0 + r1;
-          if (lane < n_obj) s.sorted[rank] = lane;
-        }
-        wave_sync();
-        {
-          // sweep: lane r holds the box at sorted position r and compares it with
-          // the boxes d = 1, 2, ... positions later until every lane has passed
-          // its box's max-x; the later boxes' bounds move down one lane per step
-          // (DPP whole-wave shift, no LDS round trip)
-          const bool in = lane < n_obj;
-          const int oi = in ? (s.sorted[lane] & (MAXB - 1)) : 0;
-          const float4 lb = s.lo[oi], hb4 = s.hi[oi];
-          const float lox = in ? lb.x : INFINITY, hix = in ? hb4.x : -INFINITY;
-          const float loy = in ? lb.y : 0.0f, hiy = in ? hb4.y : 0.0f;
-          const float loz = in ? lb.z : 0.0f, hiz = in ? hb4.z : 0.0f;
-          float lox_q = lox, loy_q = loy, hiy_q = hiy, loz_q = loz, hiz_q = hiz;
-          int oj = oi;
-          // two steps per trip: sorted min-x makes a lane that fails at step d
-          // fail at every later step, so a trip whose second step has no lane
-          // left ends the sweep
-          for (int d = 1; d < n_obj; d += 2) {
-            bool more = false;
-    #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-              lox_q = wave_next(lox_q);
-              loy_q = wave_next(loy_q);
-              hiy_q = wave_next(hiy_q);
-              loz_q = wave_next(loz_q);
-              hiz_q = wave_next(hiz_q);
-              oj = wave_next(oj);
-              const bool go = lane + d + h < n_obj && lox_q <= hix;
-              if (go && loy <= hiy_q && loy_q <= hiy && loz <= hiz_q && loz_q <= hiz) {
-                const int lo_i = oi < oj ? oi : oj, hi_i = oi < oj ? oj : oi;
-                atomicOr(&s.mask[lo_i], 1u << hi_i);
-              }
-              if (h == 1) more = __ballot(go) != 0ull;
-            }
-            if (!more) break;
-          }
-        }
-        wave_sync();
-        {
-          unsigned m = lane < n_obj ? s.mask[lane] : 0u;
-          int off = wave_excl_scan(__popc(m), &n_pairs);
-          int t = 0;
-          while (m) {
-            int j = __builtin_ctz(m);
-            m &= m - 1;
-            if (off + t < MAX_PAIRS) s.pairs[off + t] = (unsigned short)((lane << 8) | j);
-            ++t;
-          }
-        }
       }
-      wave_sync();
     }
 
-    // ---- 4a. box-plane contacts (body order, vertex order).  Corner kk
-    // of body b is tested by lane b when kk has an even number of set bits
-    // and by lane b + 32 otherwise, so every face's four corners split two
-    // and two; the body's two flag bytes give each corner its rank.
-    if (W == 1 || wid == 1) {
-      const bool on = b < nb;
-      const f3 hb = W == 1 ? h : (on ? xyz(s.half[b]) : mk(0, 0, 0));
-      f3 c0 = mk(0, 0, 0), a0 = mk(0, 0, 0), a1 = mk(0, 0, 0), a2 = mk(0, 0, 0);
-      unsigned flags = 0;
-      if (on) {
-        c0 = xyz(s.pos[b]);
-        a0 = xyz(s.col[0][b]); a1 = xyz(s.col[1][b]); a2 = xyz(s.col[2][b]);
+    // ---- 4a. table contacts (body order, corner order): the L lanes of a
+    // body test its eight corners, two or four each, and every lane gets the
+    // corners within the margin as a byte
+    unsigned mask = 0u;
+    int nt = 0;                  // the body's table contacts
+    int n_table = 0, n_held = 0, n_extra = 0;
+    if (lead) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          // the j-th corner of this lane's parity class: 0, 3, 5, 6 or 1, 2, 4, 7
-          const int kk = part == 0 ? (0x6530 >> (4 * j)) & 15 : (0x7421 >> (4 * j)) & 15;
-          const float sx = (kk & 1) ? hb.x : -hb.x, sy = (kk & 2) ? hb.y : -hb.y, sz = (kk & 4) ? hb.z : -hb.z;
-          const float vz = c0.z + (a0.z * sx + a1.z * sy + a2.z * sz);
-          if (vz <= p.margin) flags |= 1u << kk;
+      for (int m = 0; m < 8 / L; ++m) {
+        const int kc = j + L * m;
+        const float sx = (kc & 1) ? h.x : -h.x, sy = (kc & 2) ? h.y : -h.y, sz = (kc & 4) ? h.z : -h.z;
+        const float vz = x.z + (c0.z * sx + c1.z * sy + c2.z * sz);
+        if (vz <= p.margin) mask |= 1u << kc;
+      }
+      mask |= (unsigned)__builtin_amdgcn_mov_dpp((int)mask, Q_XOR1, 0xf, 0xf, true);
+      if (L == 4) mask |= (unsigned)__builtin_amdgcn_mov_dpp((int)mask, Q_XOR2, 0xf, 0xf, true);
+      mask = active ? mask : 0u;
+      nt = __popc(mask);
+#pragma unroll
+      for (int ts = 0; ts < TS; ++ts) n_held += __popcll(__ballot(j + L * ts < nt));
+      n_table = n_held;
+      if (__ballot(nt > 4) != 0ull) {
+        // boxes flatter than the margin: corners past the fourth become row
+        // contacts, the first of the list; the table contacts past the
+        // capacity are dropped in list order
+        const int off = wave_excl_scan(j == 0 ? nt : 0, &n_table) - (j == 0 ? 0 : nt);
+        if (n_table > C) {
+          nt = min(max(C - off, 0), nt);
+          while (__popc(mask) > nt) mask &= ~(1u << (31 - __clz((int)mask)));
+        }
+        n_held = 0;
+#pragma unroll
+        for (int ts = 0; ts < TS; ++ts) n_held += __popcll(__ballot(j + L * ts < nt));
+        const int xo = wave_excl_scan(j == 0 ? max(nt - 4, 0) : 0, &n_extra);
+        if (first && nt > 4) {
+          unsigned m = mask;
+          for (int r = 0; m; ++r) {
+            const int kc = __builtin_ctz(m);
+            m &= m - 1;
+            if (r < 4) continue;
+            const float sx = (kc & 1) ? h.x : -h.x, sy = (kc & 2) ? h.y : -h.y, sz = (kc & 4) ? h.z : -h.z;
+            const f3 vtx = x + mk(c0.x * sx + c1.x * sy + c2.x * sz, c0.y * sx + c1.y * sy + c2.y * sz,
+                                  c0.z * sx + c1.z * sy + c2.z * sz);
+            const int c = xo + r - 4;
+            s.u.n.stage[c][0] = f4(vtx - mk(0, 0, 0.5f * vtx.z), vtx.z);
+            s.u.n.stage[c][1] = make_float4(0, 0, 1, 0);
+            s.cab[c] = PLANE | (b << 8) | (kc << 16);
+          }
         }
       }
-      const unsigned both = (unsigned)(lower_half((int)flags) | upper_half((int)flags));
-      int total;
-      const int off0 = wave_excl_scan(part == 0 ? __popc(both) : 0, &total);
-      const int off = lower_half(off0);
-      while (flags) {
-        const int kk = __builtin_ctz(flags);
-        flags &= flags - 1;
-        float sx = (kk & 1) ? hb.x : -hb.x, sy = (kk & 2) ? hb.y : -hb.y, sz = (kk & 4) ? hb.z : -hb.z;
-        f3 vtx = c0 + mk(a0.x * sx + a1.x * sy + a2.x * sz, a0.y * sx + a1.y * sy + a2.y * sz,
-                         a0.z * sx + a1.z * sy + a2.z * sz);
-        const int c = off + __popc(both & ((1u << kk) - 1u));
-        if (c < C) {
-          s.u.stage[c][0] = f4(vtx - mk(0, 0, 0.5f * vtx.z), vtx.z);
-          s.u.stage[c][1] = make_float4(0, 0, 1, 0);
-          s.cab[c] = PLANE | (b << 8) | (kk << 16);
-        }
-      }
-      nc_raw = total;
     }
     if constexpr (W > 1) {
       // every wave needs the pair list and the table contacts
-      if (lead && lane == 0) s.sh_pairs = n_pairs;
-      if (wid == 1 && lane == 0) s.sh_plane = nc_raw;
+      if (wid == 1 && lane == 0) s.sh_pairs = n_pairs;
+      if (lead && lane == 0) {
+        s.sh_table = n_table;
+        s.sh_held = n_held;
+        s.sh_extra = n_extra;
+      }
       __syncthreads();
-      n_pairs = s.sh_pairs;
-      nc_raw = s.sh_plane;
+      n_pairs = __builtin_amdgcn_readfirstlane(s.sh_pairs);
+      n_table = __builtin_amdgcn_readfirstlane(s.sh_table);
+      n_held = __builtin_amdgcn_readfirstlane(s.sh_held);
+      n_extra = __builtin_amdgcn_readfirstlane(s.sh_extra);
+    } else {
+      wave_sync();
     }
+    const int row_cap = C - n_held;   // row contacts that fit the capacity
+    int n_rows = n_extra;
 
     // ---- 4b. box-box and pusher-box contacts, pairs in lexicographic order.
     // Eight pairs per pass, one 8-lane group each: lane k of a group
@@ -1011,9 +999,12 @@ __device__ __forceinline__ void run_env(Smem<K, W>& s, const StepArgs& g, const 
     // polygon point per lane.  With W waves a round is W passes, wave w
     // taking pairs r0 + 8 w ..; the round's contacts keep the pass order.
     for (int r0 = 0; r0 < n_pairs; r0 += 8 * W) {
-      const int grp = lane >> 3, gl = lane & 7;
+      // opaque: the lane's addresses and selects are formed here, not kept in
+      // registers over the whole push
+      const int ln = opaque(lane);
+      const int grp = ln >> 3, gl = ln & 7;
       const int pi = r0 + 8 * wid + grp;
-      const bool has = pi < n_pairs && pi < MAX_PAIRS;
+      const bool has = pi < n_pairs;
       int ia = 0, ib = 1;
       if (has) {
         const unsigned pr = s.pairs[pi];
@@ -1061,7 +1052,7 @@ __device__ __forceinline__ void run_env(Smem<K, W>& s, const StepArgs& g, const 
         // group scans the fifteen in order: the kept axis starts at candidate
         // 0 (a face of A, valid whenever the pair is) and is replaced only by
         // a later one that exceeds it by tau_face (faces) or tau_edge (edges)
-        auto& cd = s.x.wave[wid].cand;
+        auto& cd = s.u.n.x.wave[wid].cand;
         float* const cv = &cd.v[grp][0];
         cv[gl] = ok0 ? sv0 : -INFINITY;
         cv[gl + 8] = ok1 ? sv1 : -INFINITY;
@@ -1172,21 +1163,22 @@ __device__ __forceinline__ void run_env(Smem<K, W>& s, const StepArgs& g, const 
           round_total += m;
         }
       }
-      const int off = nc_raw + before + __popcll(km & below);
-      if (keep && off < C) {
+      const int off = n_rows + before + __popcll(km & below);
+      if (keep && off < row_cap) {
         const int ab = ia | (ib << 8);
         if (face) {
-          s.u.stage[off][0] = f4(P - nref * (0.5f * psep), psep);
-          s.u.stage[off][1] = f4(n, 0.0f);
+          s.u.n.stage[off][0] = f4(P - nref * (0.5f * psep), psep);
+          s.u.n.stage[off][1] = f4(n, 0.0f);
           s.cab[off] = ab | (__popcll(km & below & gm) << 16);
         } else {
-          s.u.stage[off][0] = f4(edge_point(s, ia, ib, best, n), bs);
-          s.u.stage[off][1] = f4(n, 0.0f);
+          s.u.n.stage[off][0] = f4(edge_point(s, ia, ib, best, n), bs);
+          s.u.n.stage[off][1] = f4(n, 0.0f);
           s.cab[off] = ab;
         }
       }
-      nc_raw += round_total;
+      n_rows += round_total;
     }
+    const int nc_raw = n_table + n_rows - n_extra;
     if (nc_raw > C) {
       status |= PMBS_ENV_CONTACT_OVERFLOW;
       if (g.overflow_list) {
@@ -1196,6 +1188,7 @@ __device__ __forceinline__ void run_env(Smem<K, W>& s, const StepArgs& g, const 
       }
     }
     const int nc = nc_raw < C ? nc_raw : C;
+    n_rows = n_rows < row_cap ? n_rows : row_cap;
     if constexpr (COST) {
       // the work estimate of the env's push from its start pose: contacts
       // and candidate pairs (the per-substep solver and narrowphase work)
@@ -1209,322 +1202,413 @@ __device__ __forceinline__ void run_env(Smem<K, W>& s, const StepArgs& g, const 
     sync_all<W>();   // every wave's contacts are in the staging array
 
     if (g.collide_only) {
-      if (lead && lane == 0) g.dbg_count[e] = nc;
+      // the whole list: table contacts at their rank, then the staged pairs
       float* out = g.dbg_contacts + (size_t)e * C * 9;
-      for (int c = lane; lead && c < nc; c += 64) {
-        float4 s0 = s.u.stage[c][0], s1 = s.u.stage[c][1];
-        int ab = s.cab[c];
-        int a = ab & 255, bb = (ab >> 8) & 255;
+      auto put = [&](int c, int a, int bb, f3 pt, f3 n, float sep) {
         out[c * 9 + 0] = a == PLANE ? -1.0f : (float)a;
         out[c * 9 + 1] = (float)bb;
-        out[c * 9 + 2] = s0.x; out[c * 9 + 3] = s0.y; out[c * 9 + 4] = s0.z;
-        out[c * 9 + 5] = s1.x; out[c * 9 + 6] = s1.y; out[c * 9 + 7] = s1.z;
-        out[c * 9 + 8] = s0.w;
+        out[c * 9 + 2] = pt.x; out[c * 9 + 3] = pt.y; out[c * 9 + 4] = pt.z;
+        out[c * 9 + 5] = n.x; out[c * 9 + 6] = n.y; out[c * 9 + 7] = n.z;
+        out[c * 9 + 8] = sep;
+      };
+      if (lead) {
+        int tot;
+        const int off = wave_excl_scan(j == 0 ? nt : 0, &tot);
+        if (first) {
+          int c = off;
+          for (unsigned m = mask; m; m &= m - 1, ++c) {
+            const int kc = __builtin_ctz(m);
+            const float sx = (kc & 1) ? h.x : -h.x, sy = (kc & 2) ? h.y : -h.y, sz = (kc & 4) ? h.z : -h.z;
+            const f3 vtx = x + mk(c0.x * sx + c1.x * sy + c2.x * sz, c0.y * sx + c1.y * sy + c2.y * sz,
+                                  c0.z * sx + c1.z * sy + c2.z * sz);
+            put(c, PLANE, b, vtx - mk(0, 0, 0.5f * vtx.z), mk(0, 0, 1), vtx.z);
+          }
+        }
+        for (int c = n_extra + lane; c < n_rows; c += 64) {
+          const float4 s0 = s.u.n.stage[c][0], s1 = s.u.n.stage[c][1];
+          const int ab = s.cab[c];
+          put(tot + c - n_extra, ab & 255, (ab >> 8) & 255, xyz(s0), xyz(s1), s0.w);
+        }
+        if (lane == 0) {
+          g.dbg_count[e] = nc;
+          g.env_status[e] = status;
+        }
       }
-      if (lead && lane == 0) g.env_status[e] = status;
       return;
     }
 
-    // ---- 5. per-body incidence lists in contact-index order (CSR) and counts:
-    // every contact sets its bit in the masks of its two bodies; a body's
-    // list length is its bit count; every contact then writes itself into
-    // both lists at its rank among the set bits (contact-index order)
-    const char* imp_base = reinterpret_cast<const char*>(&s.u.imp[0][0]);
-    static_assert(sizeof(s.u) + sizeof(float4) <= 0x10000, "impulse rows and the zero row need 16-bit codes");
-    const unsigned zcode = (unsigned)(reinterpret_cast<const char*>(&s.zero) - imp_base);
-    // A contact list equal to the previous substep's (same count, same keys
-    // in the same order, within one push) has the same incidence lists,
-    // counts and list ranges, which are all still in place: keep them.
-    // the lead wave keeps or rebuilds the lists over every contact slot
+    // the rest of the substep is the lead wave's
     if (lead) {
-      bool same_list = nc > 0 && nc == nwarm;
+    // ---- 5. per-body lists of row contacts in contact-index order (CSR):
+    // every row contact sets its bit in the masks of its two bodies; a
+    // body's list length is its bit count; every contact then writes itself
+    // at its rank among the set bits.  Kept from the previous substep when
+    // neither the row contacts' keys nor any body's corners changed.
+    const int lane = opaque(threadIdx.x & 63);
+    const int nh = nt < 4 ? nt : 4;   // the body's contacts in its lanes: the first of its list
+    const bool moved = __ballot(mask != corners) != 0ull;   // some body's corner set changed
+    if (n_rows > 0) {
+      bool same_list = n_rows == nwarm && !moved;
       if (same_list) {
         bool diff = false;
-  #pragma unroll
+#pragma unroll
         for (int sl = 0; sl < K; ++sl) {
           const int c = 64 * sl + lane;
-          if (c < nc) diff = diff || contact_key(s.cab[c]) != s.wkey[c];
+          if (c < n_rows) diff = diff || contact_key<S>(s.cab[c]) != s.wkey[c];
         }
         same_list = __ballot(diff) == 0ull;
       }
       if (!same_list) {
         constexpr int MW = 2 * K;  // mask words per body: slot sl, lane half
-        for (int t = lane; t < NOBJ * MW; t += 64) (&s.x.incm[0][0])[t] = 0u;
+        unsigned* const im = &s.u.n.x.incm[0][0];
+        for (int i = lane; i < S::NOBJ * MW; i += 64) im[i] = 0u;
         wave_sync();
         int ca[K], cb[K];
         const unsigned bit = 1u << (lane & 31);
-  #pragma unroll
+#pragma unroll
         for (int sl = 0; sl < K; ++sl) {
           const int c = 64 * sl + lane;
-          const int ab = c < nc ? s.cab[c] : -1;
-          ca[sl] = c < nc && (ab & 255) < nb ? (ab & 255) : -1;
-          cb[sl] = c < nc && ((ab >> 8) & 255) < nb ? ((ab >> 8) & 255) : -1;
-          const int w = 2 * sl + (lane >> 5);
-          if (ca[sl] >= 0) atomicOr(&s.x.incm[ca[sl]][w], bit);
-          if (cb[sl] >= 0) atomicOr(&s.x.incm[cb[sl]][w], bit);
+          const int ab = c < n_rows ? s.cab[c] : -1;
+          ca[sl] = c < n_rows && (ab & 255) < nb ? (ab & 255) : -1;
+          cb[sl] = c < n_rows && ((ab >> 8) & 255) < nb ? ((ab >> 8) & 255) : -1;
+          const int wd = 2 * sl + (lane >> 5);
+          if (ca[sl] >= 0) atomicOr(&s.u.n.x.incm[ca[sl]][wd], bit);
+          if (cb[sl] >= 0) atomicOr(&s.u.n.x.incm[cb[sl]][wd], bit);
         }
         wave_sync();
-        int cn = 0;
+        n_inc = 0;
         if (active) {
-  #pragma unroll
-          for (int w = 0; w < MW; ++w) cn += __popc(s.x.incm[b][w]);
+#pragma unroll
+          for (int wd = 0; wd < MW; ++wd) n_inc += __popc(s.u.n.x.incm[b][wd]);
         }
         int tot;
-        const int padded = (cn + 7) & ~7;
-        int st0 = wave_excl_scan(part == 0 ? padded : 0, &tot);
-        const int inc_start = lower_half(st0);
-        if (active && part == 0) {
-          s.cnt[b] = cn;
-          s.lstart[b] = inc_start;
-        }
-        if (active) {
-          for (int t = cn; t < padded; ++t) s.inc[part][inc_start + t] = (unsigned short)zcode;
+        inc0 = wave_excl_scan(j == 0 ? n_inc : 0, &tot) - (j == 0 ? 0 : n_inc);
+        if (first) {
+          s.cnt[b] = nh + n_inc;
+          s.lstart[b] = inc0;
         }
         wave_sync();
-  #pragma unroll
+#pragma unroll
         for (int sl = 0; sl < K; ++sl) {
           const int c = 64 * sl + lane;
-          const int w = 2 * sl + (lane >> 5);
-  #pragma unroll
+          const int wd = 2 * sl + (lane >> 5);
+#pragma unroll
           for (int side = 0; side < 2; ++side) {
-            const int j = side ? cb[sl] : ca[sl];
-            if (j >= 0) {
-              int r = s.lstart[j] + __popc(s.x.incm[j][w] & (bit - 1u));
-  #pragma unroll
+            const int jb = side ? cb[sl] : ca[sl];
+            if (jb >= 0) {
+              int r = s.lstart[jb] + __popc(s.u.n.x.incm[jb][wd] & (bit - 1u));
+#pragma unroll
               for (int w2 = 0; w2 < MW; ++w2)
-                if (w2 < w) r += __popc(s.x.incm[j][w2]);
-              s.inc[0][r] = (unsigned short)(((unsigned)c * 16u) | side);
-              s.inc[1][r] = (unsigned short)((((1u + side) * (unsigned)C + c) * 16u) | side);
+                if (w2 < wd) r += __popc(s.u.n.x.incm[jb][w2]);
+              s.inc[r] = (unsigned short)(((unsigned)c * 16u) | side);
             }
           }
         }
       }
-    }
-    sync_all<W>();   // counts and lists before any wave's prep
-
-    // ---- 6. contact prep into VGPR slots (slot sl on wave sl % W)
-#pragma unroll
-    for (int ls = 0; ls < KW; ++ls) {
-      const int c = 64 * (ls * W + wid) + lane;
-      // one wave per env (throughput) skips the table side's terms; with two
-      // (one env's latency) the extra branch cost more than it saved
-      bool side_a = true;
-      if constexpr (W == 1) side_a = __ballot(c < nc && (s.cab[c < nc ? c : 0] & 255) != PLANE) != 0ull;
-      if (c < nc) prep_contact(s, c, p, nwarm, side_a, &ct[ls]);
-    }
-
-    // ---- 7. projected Jacobi, I iterations
-    // Per-body sums: the lanes of a body's linear velocity (part 0) or
-    // angular velocity (part 1) add the impulse rows of its incidence list
-    // as two partial sums in list order, one over the even entries and one
-    // over the odd entries, then the velocity takes M times their sum (M:
-    // inverse mass times identity, or the world inverse inertia; diagonal
-    // md, off-diagonal mo = (xy, xz, yz)).  Two waves: wave 0 sums the
-    // linear and wave 1 the angular velocities, a lane pair per body (one
-    // partial sum each, exchanged within the pair).  One wave: the same lane
-    // pairs when the env has at most 16 boxes, else one lane per body and
-    // part holding both partial sums.  Every layout gives the same bits.
-    const bool two = W > 1 || nb <= 16;
-    const int sp = W > 1 ? wid : (lane >> 5);
-    const int sb = W > 1 ? (lane >> 1) : (two ? ((lane & 31) >> 1) : (lane & 31));
-    const int sh = two ? (lane & 1) : 0;
-    const bool sum_on = sb < nb;
-    const bool sum_store = sum_on && sh == 0;
-    float4* const vw_slot = sp == 0 ? &s.vel[sb] : &s.ang[sb];
-    f3 vw = mk(0, 0, 0), md = mk(0, 0, 0), mo = mk(0, 0, 0);
-    // four entries of the list stay in registers for the whole solve as row
-    // byte offsets and signs (a pair lane: its entries sh, sh + 2, sh + 4,
-    // sh + 6; a single lane: entries 0-3), so their loads need no index
-    // arithmetic and no guard; slots past the end of a list point at the
-    // zero row, whose term (-1 times +0) leaves every sum unchanged, an
-    // empty list's sum included (+0)
-    unsigned radr[4];
-    float rsg[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      radr[u] = zcode;
-      rsg[u] = -1.0f;
-    }
-    int ccount = 0, cstart = 0;
-    if (sum_on) {
-      vw = xyz(*vw_slot);
-      if (sp == 0) {
-        const float im = s.half[sb].w;
-        md = mk(im, im, im);
-      } else {
-        const float4 ia = s.iwa[sb], ib = s.iwb[sb];
-        md = mk(ia.x, ia.y, ia.z);
-        mo = mk(ia.w, ib.x, ib.y);
+      // the bodies' data that the row contacts read
+      if (first && n_inc > 0) {
+        s.iwa[b] = make_float4(md.x, md.y, md.z, mo.x);
+        s.iwb[b] = make_float4(mo.y, mo.z, mu, 0.0f);
       }
-      ccount = s.cnt[sb];
-      cstart = s.lstart[sb];
-      if (ccount > 0) {   // the list holds at least 8 entries (padding included)
+    } else {
+      n_inc = 0;
+    }
+    // a corner set that changed, or table contacts among the rows: last
+    // substep's table impulses go through LDS (once per change; a resting or
+    // sliding box keeps its corners for many substeps)
+    const bool relist = moved || n_extra > 0;
+    if (relist) {
+      wave_sync();
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const unsigned code = s.inc[sp][cstart + (two ? sh + 2 * u : u)];
-          radr[u] = code & 0xfffeu;
-          rsg[u] = (code & 1u) ? 1.0f : -1.0f;
+      for (int ts = 0; ts < TS; ++ts)
+        if (active)
+          s.u.n.x.lam[4 * b + j + L * ts] = make_float4(tc[ts].ln, tc[ts].lt1, tc[ts].lt2, __int_as_float((int)corners));
+      wave_sync();
+#pragma unroll
+      for (int ts = 0; ts < TS; ++ts) {
+        const int i = j + L * ts;   // the lane's contact: corner number i of the set
+        unsigned m = mask;
+#pragma unroll
+        for (int r = 0; r < 3; ++r) m = r < i ? m & (m - 1u) : m;
+        kk[ts] = m ? __builtin_ctz(m) : 0;
+        tc[ts].ln = tc[ts].lt1 = tc[ts].lt2 = 0.0f;
+        if (i < nt && (corners >> kk[ts] & 1u)) {
+          const int o = __popc(corners & ((1u << kk[ts]) - 1u));
+          if (o < 4) {
+            const float4 l = s.u.n.x.lam[4 * b + o];
+            tc[ts].ln = l.x;
+            tc[ts].lt1 = l.y;
+            tc[ts].lt2 = l.z;
+          } else {
+            const int wi = warm_index(s, (b << 8) | kk[ts], nwarm);
+            if (wi >= 0) {
+              tc[ts].ln = s.wl[0][wi];
+              tc[ts].lt1 = s.wl[1][wi];
+              tc[ts].lt2 = s.wl[2][wi];
+            }
+          }
+        }
+      }
+      corners = mask;
+    }
+
+    // ---- 6. contact prep: the lanes' table contacts (an absent one has zero
+    // masses, so its impulses stay zero), then the row contacts
+    const float cbn = (float)(nh + n_inc);
+#pragma unroll
+    for (int ts = 0; ts < TS; ++ts) {
+      TableContact& q = tc[ts];
+      const bool on = j + L * ts < nt;
+      const int kc = kk[ts];
+      const float sx = (kc & 1) ? h.x : -h.x, sy = (kc & 2) ? h.y : -h.y, sz = (kc & 4) ? h.z : -h.z;
+      const f3 vtx = x + mk(c0.x * sx + c1.x * sy + c2.x * sz, c0.y * sx + c1.y * sy + c2.y * sz,
+                            c0.z * sx + c1.z * sy + c2.z * sz);
+      const f3 pt = vtx - mk(0, 0, 0.5f * vtx.z);
+      const float sep = vtx.z;
+      q.rb = pt - x;
+      const f3 em = table_masses(q.rb, md, mo);
+      q.kn = on ? rcp(cbn * (invm + em.x)) : 0.0f;
+      q.kt1 = on ? rcp(cbn * (invm + em.y)) : 0.0f;
+      q.kt2 = on ? rcp(cbn * (invm + em.z)) : 0.0f;
+      q.vstar = sep > 0.0f ? -sep * p.inv_dt : p.beta * fmaxf(-sep - p.slop, 0.0f) * p.inv_dt;
+    }
+    Contact ct[K];
+    if (n_rows > 0) {
+      wave_sync();
+#pragma unroll
+      for (int sl = 0; sl < K; ++sl) {
+        const int c = 64 * sl + lane;
+        if (64 * sl < n_rows) {
+          if (c < n_rows) {
+            prep_contact(s, c, p, nwarm, &ct[sl]);
+            if (n_extra > 0 && c < n_extra) {
+              // a table corner among the rows: its impulse may have been a lane's
+              const int bb = (ct[sl].ab >> 8) & 255, kc = ct[sl].ab >> 16;
+              const unsigned old = (unsigned)__float_as_int(s.u.n.x.lam[4 * bb].w);
+              const int o = __popc(old & ((1u << kc) - 1u));
+              if ((old >> kc & 1u) && o < 4) {
+                const float4 l = s.u.n.x.lam[4 * bb + o];
+                ct[sl].ln = l.x;
+                ct[sl].lt1 = l.y;
+                ct[sl].lt2 = l.z;
+              }
+            }
+          } else {
+            // an absent contact of the table with itself: zero impulses
+            const f3 z = mk(0, 0, 0);
+            ct[sl] = Contact{PLANE | (PLANE << 8), z, z, z, z, z, 0, 0, 0, 0, 0, 0, 0, 0};
+          }
         }
       }
     }
-    const int cpad = (ccount + 7) & ~7;
-    // one wave per env: lane pairs whose lists all hold at most four entries
-    // (bodies touched by at most four contacts, e.g. boxes resting on the
-    // table alone) skip entries sh + 4 and sh + 6, zero rows whose terms
-    // change no sum (a partial sum is never -0)
-    const bool short_lists = W == 1 && two && __ballot(sum_on && ccount > 4) == 0ull;
-    auto row_of = [&](unsigned code) { return *reinterpret_cast<const float4*>(imp_base + (code & 0xfffeu)); };
-    auto reg_row = [&](unsigned off) { return *reinterpret_cast<const float4*>(imp_base + off); };
-    auto add_signed = [](f3 a, float sg, float4 val) {
+
+    // ---- 7. projected Jacobi, I iterations.  A body's velocity changes by M
+    // times the sum of its contacts' impulses (M: inverse mass, world inverse
+    // inertia), added as two partial sums over the even and the odd entries of its
+    // contact list, each in list order: lanes j of even and odd parity hold
+    // them, the table contacts' terms first (entries 0-3), then the rows.
+    f3 P[TS];
+    auto row_at = [&](unsigned off) {
+      return xyz(*reinterpret_cast<const float4*>(reinterpret_cast<const char*>(&s.u.imp[0][0]) + off));
+    };
+    auto add_signed = [](f3 a, float sg, f3 val) {
       return mk(fmaf(sg, val.x, a.x), fmaf(sg, val.y, a.y), fmaf(sg, val.z, a.z));
     };
-    auto add_row = [&](f3 a, unsigned code, float4 val) { return add_signed(a, (code & 1u) ? 1.0f : -1.0f, val); };
-    // four entries per step so their LDS loads are in flight together
-    auto apply_sums = [&]() {
-      if (!sum_on) return;
-      f3 a0 = mk(0, 0, 0), a1 = mk(0, 0, 0);
-      if (two && short_lists) {
-        const float4 v0 = reg_row(radr[0]), v1 = reg_row(radr[1]);
-        a0 = add_signed(a0, rsg[0], v0);
-        a0 = add_signed(a0, rsg[1], v1);
-        a1 = mk(pair_swap(a0.x), pair_swap(a0.y), pair_swap(a0.z));
-      } else if (two) {
-        {
-          float4 val[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) val[u] = reg_row(radr[u]);
-#pragma unroll
-          for (int u = 0; u < 4; ++u) a0 = add_signed(a0, rsg[u], val[u]);
-        }
-        for (int k = 8; k < cpad; k += 8) {
-          unsigned code[4];
-          float4 val[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) code[u] = s.inc[sp][cstart + k + sh + 2 * u];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) val[u] = row_of(code[u]);
-#pragma unroll
-          for (int u = 0; u < 4; ++u) a0 = add_row(a0, code[u], val[u]);
-        }
-        // the partner lane's partial sum (lane ^ 1)
-        a1 = mk(pair_swap(a0.x), pair_swap(a0.y), pair_swap(a0.z));
+    auto apply = [&](f3 lin, f3 ang) {
+      v = mk(fmaf(invm, lin.x, v.x), fmaf(invm, lin.y, v.y), fmaf(invm, lin.z, v.z));
+      w = mk(fmaf(md.x, ang.x, fmaf(mo.x, ang.y, fmaf(mo.y, ang.z, w.x))),
+             fmaf(mo.x, ang.x, fmaf(md.y, ang.y, fmaf(mo.z, ang.z, w.y))),
+             fmaf(mo.y, ang.x, fmaf(mo.z, ang.y, fmaf(md.z, ang.z, w.z))));
+    };
+    // the table contacts' terms of the lane's parity
+    auto table_sums = [&](f3* lin, f3* ang) {
+      if constexpr (L == 4) {
+        const f3 T = cross(tc[0].rb, P[0]);
+        *lin = P[0] + quad<Q_XOR2>(P[0]);
+        *ang = T + quad<Q_XOR2>(T);
       } else {
-        {
-          float4 val[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) val[u] = reg_row(radr[u]);
-          a0 = add_signed(a0, rsg[0], val[0]);
-          a1 = add_signed(a1, rsg[1], val[1]);
-          a0 = add_signed(a0, rsg[2], val[2]);
-          a1 = add_signed(a1, rsg[3], val[3]);
-        }
-        // entries 4.. from the list in LDS (entries 4-7 add nothing to a
-        // list of at most four)
-        for (int k = 4; k < (ccount > 4 ? cpad : 0); k += 4) {
-          unsigned code[4];
-          float4 val[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) code[u] = s.inc[sp][cstart + k + u];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) val[u] = row_of(code[u]);
-          a0 = add_row(a0, code[0], val[0]);
-          a1 = add_row(a1, code[1], val[1]);
-          a0 = add_row(a0, code[2], val[2]);
-          a1 = add_row(a1, code[3], val[3]);
-        }
+        *lin = P[0] + P[TS - 1];
+        *ang = cross(tc[0].rb, P[0]) + cross(tc[TS - 1].rb, P[TS - 1]);
       }
-      const f3 acc = mk(a0.x + a1.x, a0.y + a1.y, a0.z + a1.z);
-      vw = mk(fmaf(md.x, acc.x, fmaf(mo.x, acc.y, fmaf(mo.y, acc.z, vw.x))),
-              fmaf(mo.x, acc.x, fmaf(md.y, acc.y, fmaf(mo.z, acc.z, vw.y))),
-              fmaf(mo.y, acc.x, fmaf(mo.z, acc.y, fmaf(md.z, acc.z, vw.z))));
     };
-    // warm start: the impulses carried over from the previous substep (the
-    // impulse rows share LDS with the staging array every prep has read)
-    sync_all<W>();
+    auto table_update = [&]() {
 #pragma unroll
-    for (int ls = 0; ls < KW; ++ls) {
-      const int c = 64 * (ls * W + wid) + lane;
-      if (c < nc) {
-        const Contact& q = ct[ls];
-        const f3 P = fma3(q.n, q.ln, fma3(q.t1, q.lt1, q.t2 * q.lt2));
-        st3(&s.u.imp[0][c], P);
-        st3(&s.u.imp[1][c], cross(q.ra, P));
-        st3(&s.u.imp[2][c], cross(q.rb, P));
+      for (int ts = 0; ts < TS; ++ts) {
+        TableContact& q = tc[ts];
+        const f3 u = cross_add(w, q.rb, v);
+        const float ln = fmaxf(q.ln + q.kn * (q.vstar - u.z), 0.0f);
+        float lt1 = q.lt1 + q.kt1 * u.y;
+        float lt2 = q.lt2 - q.kt2 * u.x;
+        // onto the friction disc: scale by min(1, lim / |lt|) (a zero
+        // tangential impulse gives inf or nan, and the min keeps 1)
+        const float lim = mu_table * ln, mag2 = lt1 * lt1 + lt2 * lt2;
+        const float sc = fminf(lim * rsq(mag2), 1.0f);
+        lt1 *= sc;
+        lt2 *= sc;
+        P[ts] = mk(lt2 - q.lt2, q.lt1 - lt1, ln - q.ln);
+        q.ln = ln;
+        q.lt1 = lt1;
+        q.lt2 = lt2;
       }
-    }
-    sync_all<W>();
-    apply_sums();
-    auto jacobi_pass = [&]() {
-      if (sum_store) st3(vw_slot, vw);
-      sync_all<W>();   // the iteration-start velocities, and every wave done with the rows
+    };
 #pragma unroll
-      for (int ls = 0; ls < KW; ++ls) {
-        const int c = 64 * (ls * W + wid) + lane;
-        if (c < nc) {
-          Contact& q = ct[ls];
-          const f3 t2 = q.t2;
-          const int a = q.ab & 255, bb = (q.ab >> 8) & 255;
-          f3 va = xyz(s.vel[a]), wa = xyz(s.ang[a]), vb = xyz(s.vel[bb]), wb = xyz(s.ang[bb]);
-          f3 u = cross_add(wb, q.rb, vb) - cross_add(wa, q.ra, va);
-          float ln = fmaxf(q.ln + q.kn * (q.vstar - dot(u, q.n)), 0.0f);
-          float dln = ln - q.ln;
-          q.ln = ln;
-          float lt1 = q.lt1 - q.kt1 * dot(u, q.t1);
-          float lt2 = q.lt2 - q.kt2 * dot(u, t2);
-          // onto the friction disc: scale by min(1, lim / |lt|) (a zero
-          // tangential impulse gives inf or nan, and the min keeps 1)
-          const float lim = q.mu * ln, mag2 = lt1 * lt1 + lt2 * lt2;
-          const float sc = fminf(lim * rsq(mag2), 1.0f);
-          lt1 *= sc;
-          lt2 *= sc;
-          float dl1 = lt1 - q.lt1, dl2 = lt2 - q.lt2;
-          q.lt1 = lt1;
-          q.lt2 = lt2;
-          const f3 P = fma3(q.n, dln, fma3(q.t1, dl1, t2 * dl2));
-          st3(&s.u.imp[0][c], P);
-          st3(&s.u.imp[1][c], cross(q.ra, P));
-          st3(&s.u.imp[2][c], cross(q.rb, P));
+    for (int ts = 0; ts < TS; ++ts) P[ts] = mk(tc[ts].lt2, -tc[ts].lt1, tc[ts].ln);
+    if (n_rows == 0) {
+      // table contacts alone: every body by itself, nothing through LDS
+      auto sums = [&]() {
+        f3 lin, ang;
+        table_sums(&lin, &ang);
+        apply(lin + quad<Q_XOR1>(lin), ang + quad<Q_XOR1>(ang));
+      };
+      sums();
+      for (int it = 0; it < p.iters; ++it) {
+        table_update();
+        sums();
+      }
+    } else {
+      // the lane's entries of its body's list: parity j & 1; with four lanes
+      // per body lanes 0 and 1 add the linear rows and lanes 2 and 3 the
+      // angular ones, with two lanes both.  The first four entries stay in
+      // registers as row offsets and signs; one past the end of the list
+      // points at the zero row, whose term (-1 times +0) changes no sum.
+      constexpr int RG = 4;
+      const unsigned zrow = (unsigned)(reinterpret_cast<const char*>(&s.zero) - reinterpret_cast<const char*>(&s.u.imp[0][0]));
+      static_assert(sizeof(s.u) + sizeof(float4) <= 0x10000, "impulse rows and the zero row need 16-bit codes");
+      const bool ang_lane = L == 4 && j >= 2;
+      const int k0 = (j ^ nh) & 1;
+      unsigned radr[RG], rada[L == 2 ? RG : 1];
+      float rsg[RG];
+      auto row_lin = [&](unsigned code) { return code & 0xfffeu; };
+      auto row_ang = [&](unsigned code) { return (code & 0xfffeu) + (1u + (code & 1u)) * (unsigned)(C * 16); };
+#pragma unroll
+      for (int u = 0; u < RG; ++u) {
+        const int i = k0 + 2 * u;
+        const bool in = i < n_inc;
+        const unsigned code = in ? s.inc[inc0 + i] : 0u;
+        rsg[u] = in && (code & 1u) ? 1.0f : -1.0f;
+        radr[u] = in ? (ang_lane ? row_ang(code) : row_lin(code)) : zrow;
+        if constexpr (L == 2) rada[u] = in ? row_ang(code) : zrow;
+      }
+      const bool rows2 = __ballot(n_inc > k0 + 4) != 0ull;   // some lane has a third entry
+      const bool rows4 = __ballot(n_inc > k0 + 2 * RG) != 0ull;
+      auto sums = [&]() {
+        f3 lin, ang;
+        table_sums(&lin, &ang);
+        if constexpr (L == 4) {
+          f3 a = sel(ang_lane, ang, lin);
+          const f3 r0 = row_at(radr[0]), r1 = row_at(radr[1]);
+          a = add_signed(a, rsg[0], r0);
+          a = add_signed(a, rsg[1], r1);
+          if (rows2) {
+            const f3 r2 = row_at(radr[2]), r3 = row_at(radr[3]);
+            a = add_signed(a, rsg[2], r2);
+            a = add_signed(a, rsg[3], r3);
+            if (rows4)
+              for (int i = k0 + 2 * RG; i < n_inc; i += 2) {
+                const unsigned code = s.inc[inc0 + i];
+                a = add_signed(a, (code & 1u) ? 1.0f : -1.0f, row_at(ang_lane ? row_ang(code) : row_lin(code)));
+              }
+          }
+          a = a + quad<Q_XOR1>(a);
+          apply(quad<Q_LOW>(a), quad<Q_HIGH>(a));
+        } else {
+          const f3 r0 = row_at(radr[0]), r1 = row_at(radr[1]), t0 = row_at(rada[0]), t1 = row_at(rada[1]);
+          lin = add_signed(lin, rsg[0], r0);
+          lin = add_signed(lin, rsg[1], r1);
+          ang = add_signed(ang, rsg[0], t0);
+          ang = add_signed(ang, rsg[1], t1);
+          if (rows2) {
+            const f3 r2 = row_at(radr[2]), r3 = row_at(radr[3]), t2 = row_at(rada[2]), t3 = row_at(rada[3]);
+            lin = add_signed(lin, rsg[2], r2);
+            lin = add_signed(lin, rsg[3], r3);
+            ang = add_signed(ang, rsg[2], t2);
+            ang = add_signed(ang, rsg[3], t3);
+            if (rows4)
+              for (int i = k0 + 2 * RG; i < n_inc; i += 2) {
+                const unsigned code = s.inc[inc0 + i];
+                const float sg = (code & 1u) ? 1.0f : -1.0f;
+                lin = add_signed(lin, sg, row_at(row_lin(code)));
+                ang = add_signed(ang, sg, row_at(row_ang(code)));
+              }
+          }
+          apply(lin + quad<Q_XOR1>(lin), ang + quad<Q_XOR1>(ang));
+        }
+      };
+      auto put_rows = [&](int c, const Contact& q, f3 R) {
+        st3(&s.u.imp[0][c], R);
+        st3(&s.u.imp[1][c], cross(q.ra, R));
+        st3(&s.u.imp[2][c], cross(q.rb, R));
+      };
+      // warm start: the impulses carried over from the previous substep (the
+      // impulse rows share LDS with the staging array every prep has read)
+      wave_sync();
+#pragma unroll
+      for (int sl = 0; sl < K; ++sl)
+        if (64 * sl < n_rows) {
+          const Contact& q = ct[sl];
+          put_rows(64 * sl + lane, q, fma3(q.n, q.ln, fma3(q.t1, q.lt1, q.t2 * q.lt2)));
+        }
+      wave_sync();
+      sums();
+      // lane 0 of a body with row contacts publishes its linear, lane 1 its
+      // angular velocity
+      float4* const vslot = j == 0 ? &s.vel[b < MB ? b : 0] : &s.ang[b < MB ? b : 0];
+      const bool publish = active && j < 2 && n_inc > 0;
+      for (int it = 0; it < p.iters; ++it) {
+        if (publish) st3(vslot, sel(j == 0, v, w));
+        wave_sync();   // the iteration-start velocities
+#pragma unroll
+        for (int sl = 0; sl < K; ++sl)
+          if (64 * sl < n_rows) {
+            Contact& q = ct[sl];
+            const int a = q.ab & 255, bb = (q.ab >> 8) & 255;
+            const f3 va = xyz(s.vel[a]), wa = xyz(s.ang[a]), vb = xyz(s.vel[bb]), wb = xyz(s.ang[bb]);
+            if (sl == 0) table_update();   // while the loads are in flight
+            const f3 u = cross_add(wb, q.rb, vb) - cross_add(wa, q.ra, va);
+            const float ln = fmaxf(q.ln + q.kn * (q.vstar - dot(u, q.n)), 0.0f);
+            const float dln = ln - q.ln;
+            q.ln = ln;
+            float lt1 = q.lt1 - q.kt1 * dot(u, q.t1);
+            float lt2 = q.lt2 - q.kt2 * dot(u, q.t2);
+            const float lim = q.mu * ln, mag2 = lt1 * lt1 + lt2 * lt2;
+            const float sc = fminf(lim * rsq(mag2), 1.0f);
+            lt1 *= sc;
+            lt2 *= sc;
+            const float dl1 = lt1 - q.lt1, dl2 = lt2 - q.lt2;
+            q.lt1 = lt1;
+            q.lt2 = lt2;
+            put_rows(64 * sl + lane, q, fma3(q.n, dln, fma3(q.t1, dl1, q.t2 * dl2)));
+          }
+        wave_sync();   // the impulse rows
+        sums();
+      }
+      // remember this substep's accumulated impulses by key
+#pragma unroll
+      for (int sl = 0; sl < K; ++sl) {
+        const int c = 64 * sl + lane;
+        if (64 * sl < n_rows && c < n_rows) {
+          s.wkey[c] = contact_key<S>(ct[sl].ab);
+          s.wl[0][c] = ct[sl].ln;
+          s.wl[1][c] = ct[sl].lt1;
+          s.wl[2][c] = ct[sl].lt2;
         }
       }
-      sync_all<W>();   // every wave's impulse rows
-      apply_sums();
-    };
-    for (int it = 0; it < p.iters; ++it) jacobi_pass();
-    // the body lanes take the solved velocities back
-    if (sum_store) st3(vw_slot, vw);
-    sync_all<W>();
-    if (active) {
-      vl = xyz(part == 0 ? s.vel[b] : s.ang[b]);
     }
-    // remember this substep's accumulated impulses by key
-#pragma unroll
-    for (int ls = 0; ls < KW; ++ls) {
-      const int c = 64 * (ls * W + wid) + lane;
-      if (c < nc) {
-        s.wkey[c] = contact_key(ct[ls].ab);
-        s.wl[0][c] = ct[ls].ln;
-        s.wl[1][c] = ct[ls].lt1;
-        s.wl[2][c] = ct[ls].lt2;
-      }
-    }
-    nwarm = nc;
+    nwarm = n_rows;
 
     // ---- 8. position stage
-    if (active) {
-      if (part == 0) {
-        x = fma3(vl, dt, x);
-      } else {
-        const f3 w = vl;
-        float dw = -(w.x * q1 + w.y * q2 + w.z * q3);
-        float dx = q0 * w.x + (w.y * q3 - w.z * q2);
-        float dy = q0 * w.y + (w.z * q1 - w.x * q3);
-        float dz = q0 * w.z + (w.x * q2 - w.y * q1);
-        float hd = 0.5f * dt;
-        q0 += hd * dw; q1 += hd * dx; q2 += hd * dy; q3 += hd * dz;
-        const float il = rsq(q0 * q0 + q1 * q1 + q2 * q2 + q3 * q3);
-        q0 *= il; q1 *= il; q2 *= il; q3 *= il;
-      }
+    x = fma3(v, dt, x);
+    {
+      float dw = -(w.x * q1 + w.y * q2 + w.z * q3);
+      float dx = q0 * w.x + (w.y * q3 - w.z * q2);
+      float dy = q0 * w.y + (w.z * q1 - w.x * q3);
+      float dz = q0 * w.z + (w.x * q2 - w.y * q1);
+      float hd = 0.5f * dt;
+      q0 += hd * dw; q1 += hd * dx; q2 += hd * dy; q3 += hd * dz;
+      const float il = rsq(q0 * q0 + q1 * q1 + q2 * q2 + q3 * q3);
+      q0 *= il; q1 *= il; q2 *= il; q3 *= il;
     }
+    }  // lead
     xp = fma3(vp, dt, xp);
     wave_sync();
   }
@@ -1532,15 +1616,18 @@ __device__ __forceinline__ void run_env(Smem<K, W>& s, const StepArgs& g, const 
 
   if (rollout) {
     // ---- reward after the push: clearance of the target's footprint, by
-    // every wave from the frames in LDS (the same stopping decision)
-    write_body_frames();
+    // every wave from the frames in LDS (the same stopping decision); the L
+    // lanes of a body share its vertices
+    write_body_frames(b, first);
     sync_all<W>();
     const int tg = g.target[e];
+    const int lane = opaque(threadIdx.x & 63), b = lane / L, j = lane % L;
+    const bool active = lead && b < nb;
     float d2 = INFINITY;
-    if (b < nb && b != tg && tg >= 0 && tg < nb) {   // the two lanes of a body share its vertices
+    if (b < nb && b != tg && tg >= 0 && tg < nb) {
       const Foot T = foot_of(xyz(s.pos[tg]), xyz(s.col[0][tg]), xyz(s.col[1][tg]), xyz(s.col[2][tg]), xyz(s.half[tg]));
       const Foot J = foot_of(xyz(s.pos[b]), xyz(s.col[0][b]), xyz(s.col[1][b]), xyz(s.col[2][b]), xyz(s.half[b]));
-      d2 = foot_distance2<2>(T, J, part);
+      d2 = foot_distance2<L>(T, J, j);
     }
     for (int o = 32; o > 0; o >>= 1) d2 = fminf(d2, __shfl_xor(d2, o, 64));
     const float d = sqrtf(d2);
@@ -1551,14 +1638,14 @@ __device__ __forceinline__ void run_env(Smem<K, W>& s, const StepArgs& g, const 
     if (lead && lane == 0) (job ? g.x_rewards : g.rewards)[(size_t)e * g.max_h + t] = r;
     // the expanded child's state goes to its pool slot
     const int cs = (t == 0 && job == 0 && g.child_slot) ? g.child_slot[e] : -1;
-    if (cs >= 0 && active) {
+    if (cs >= 0 && active && j < 2) {
       float* dst = g.pool + (size_t)cs * 13 * PS + opaque(b);
-      if (part == 0) {
+      if (j == 0) {
         dst[0 * PS] = x.x; dst[1 * PS] = x.y; dst[2 * PS] = x.z;
-        dst[7 * PS] = vl.x; dst[8 * PS] = vl.y; dst[9 * PS] = vl.z;
+        dst[7 * PS] = v.x; dst[8 * PS] = v.y; dst[9 * PS] = v.z;
       } else {
         dst[3 * PS] = q0; dst[4 * PS] = q1; dst[5 * PS] = q2; dst[6 * PS] = q3;
-        dst[10 * PS] = vl.x; dst[11 * PS] = vl.y; dst[12 * PS] = vl.z;
+        dst[10 * PS] = w.x; dst[11 * PS] = w.y; dst[12 * PS] = w.z;
       }
     }
     sync_all<W>();   // every wave has read the frames before they change
@@ -1576,13 +1663,10 @@ __device__ __forceinline__ void run_env(Smem<K, W>& s, const StepArgs& g, const 
   last_r = 0.0f;
   if (active) {
     const float* st = g.pool + (size_t)g.x_desc[e].x * 13 * PS + opaque(b);
-    if (part == 0) {
-      x = mk(st[0 * PS], st[1 * PS], st[2 * PS]);
-      vl = mk(st[7 * PS], st[8 * PS], st[9 * PS]);
-    } else {
-      q0 = st[3 * PS]; q1 = st[4 * PS]; q2 = st[5 * PS]; q3 = st[6 * PS];
-      vl = mk(st[10 * PS], st[11 * PS], st[12 * PS]);
-    }
+    x = mk(st[0 * PS], st[1 * PS], st[2 * PS]);
+    q0 = st[3 * PS]; q1 = st[4 * PS]; q2 = st[5 * PS]; q3 = st[6 * PS];
+    v = mk(st[7 * PS], st[8 * PS], st[9 * PS]);
+    w = mk(st[10 * PS], st[11 * PS], st[12 * PS]);
   }
   }  // jobs
 
@@ -1608,18 +1692,18 @@ __device__ __forceinline__ void run_env(Smem<K, W>& s, const StepArgs& g, const 
 
   // ---- write back
   bool bad = false;
-  if (active) {
+  if (active && j < 2) {
     const int i = opaque(base + b);
     float* st = g.state;
-    if (part == 0) {
+    if (j == 0) {
       st[0 * N + i] = x.x; st[1 * N + i] = x.y; st[2 * N + i] = x.z;
-      st[7 * N + i] = vl.x; st[8 * N + i] = vl.y; st[9 * N + i] = vl.z;
-      bad = !(isfinite(x.x) && isfinite(x.y) && isfinite(x.z) && isfinite(vl.x) && isfinite(vl.y) && isfinite(vl.z));
+      st[7 * N + i] = v.x; st[8 * N + i] = v.y; st[9 * N + i] = v.z;
+      bad = !(isfinite(x.x) && isfinite(x.y) && isfinite(x.z) && isfinite(v.x) && isfinite(v.y) && isfinite(v.z));
     } else {
       st[3 * N + i] = q0; st[4 * N + i] = q1; st[5 * N + i] = q2; st[6 * N + i] = q3;
-      st[10 * N + i] = vl.x; st[11 * N + i] = vl.y; st[12 * N + i] = vl.z;
-      bad = !(isfinite(q0) && isfinite(q1) && isfinite(q2) && isfinite(q3) && isfinite(vl.x) && isfinite(vl.y) &&
-              isfinite(vl.z));
+      st[10 * N + i] = w.x; st[11 * N + i] = w.y; st[12 * N + i] = w.z;
+      bad = !(isfinite(q0) && isfinite(q1) && isfinite(q2) && isfinite(q3) && isfinite(w.x) && isfinite(w.y) &&
+              isfinite(w.z));
     }
   }
   if (__ballot(bad) != 0) status |= PMBS_ENV_NONFINITE;
@@ -1645,7 +1729,7 @@ __device__ __forceinline__ int xcd_start(int x, int n) {
 __device__ __forceinline__ int xcd_item(int bid, int n) { return xcd_start(bid % 8, n) + bid / 8; }
 
 // ------------------------------------------------------------------ the step kernel
-// One wave per environment.  Without a work queue block i runs work item
+// One workgroup per environment.  Without a work queue block i runs work item
 // env_base + xcd_item(i); with one, blocks pull work items from the device counter
 // until it passes n_envs (every block reaches that exit).  order[] maps
 // work items to environments (longest horizon first for uneven rollouts).
@@ -1657,6 +1741,7 @@ __device__ __forceinline__ int xcd_item(int bid, int n) { return xcd_start(bid %
 // them, so a workgroup sets them once.
 template <class S>
 __device__ __forceinline__ void init_plane(S& s, const Params& p) {
+  constexpr int PLANE = S::PLANE;
   if (threadIdx.x == 0) {
     s.pos[PLANE] = make_float4(0, 0, 0, 0);
     s.col[0][PLANE] = make_float4(1, 0, 0, 0);
@@ -1672,9 +1757,9 @@ __device__ __forceinline__ void init_plane(S& s, const Params& p) {
   }
 }
 
-template <int K, int W>
-__global__ __launch_bounds__(64 * W, 2) void step_kernel(StepArgs g) {
-  __shared__ Smem<K, W> s;
+template <int K, int W, int NB>
+__global__ __launch_bounds__(64 * W, NB == 16 && W == 1 ? 3 : 2) void step_kernel(StepArgs g) {
+  __shared__ Smem<K, W, NB> s;
   __shared__ int next;
   init_plane(s, g.p);
   int n_work = g.work_count ? *g.work_count : g.n_envs;
@@ -1691,11 +1776,11 @@ __global__ __launch_bounds__(64 * W, 2) void step_kernel(StepArgs g) {
     if (g.queue) {
       if (threadIdx.x == 0) next = atomicAdd(queue, 1);
       __syncthreads();
-      wi = next;
+      wi = __builtin_amdgcn_readfirstlane(next);
       __syncthreads();
     }
     if (wi >= n_work) break;
-    run_env<K, W, false>(s, g, g.order ? g.order[seg + wi] : wi);
+    run_env<K, W, NB, false>(s, g, __builtin_amdgcn_readfirstlane(g.order ? g.order[seg + wi] : wi));
     if (!g.queue) break;
     __syncthreads();
   }
@@ -1704,12 +1789,12 @@ __global__ __launch_bounds__(64 * W, 2) void step_kernel(StepArgs g) {
 // The cost pass of a queued step: one block per env runs the push begin
 // and the first substep's collision detection and writes the env's work
 // estimate to cost_key (the rest of run_env is not compiled in).
-template <int K, int W>
+template <int K, int W, int NB>
 __global__ __launch_bounds__(64 * W, 2) void cost_kernel(StepArgs g) {
-  __shared__ Smem<K, W> s;
+  __shared__ Smem<K, W, NB> s;
   init_plane(s, g.p);
   const int e = g.env_base + xcd_item(blockIdx.x, gridDim.x);
-  if (e < g.n_envs) run_env<K, W, true>(s, g, e);
+  if (e < g.n_envs) run_env<K, W, NB, true>(s, g, e);
 }
 
 // Schedule of a queued step: each XCD's contiguous run of envs (xcd_start)
@@ -1879,47 +1964,50 @@ hipError_t launch_valid(const ValidArgs& a, hipStream_t stream, int grid) {
   return hipGetLastError();
 }
 
-// The kernel of a contact class (128, 256 or 512 contacts: 2, 4 or 8 VGPR
-// slots per lane) and workgroup shape (1 or 2 waves per environment).
-template <int W>
-static hipError_t launch_class(const StepArgs& a, int max_contacts, hipStream_t stream, int grid) {
-  if (max_contacts <= 128) {
-    hipLaunchKernelGGL((step_kernel<2, W>), dim3(grid), dim3(64 * W), 0, stream, a);
-  } else if (max_contacts <= 256) {
-    hipLaunchKernelGGL((step_kernel<4, W>), dim3(grid), dim3(64 * W), 0, stream, a);
-  } else {
-    hipLaunchKernelGGL((step_kernel<8, W>), dim3(grid), dim3(64 * W), 0, stream, a);
-  }
-  return hipGetLastError();
+// Calls f(kernel tag) for the kernel of a contact class (128, 256 or 512
+// contacts: 2, 4 or 8 slots of row contacts per lane), a workgroup shape (1
+// or 2 waves per environment; the 512-contact class has one) and the largest
+// body count: 128 contacts and at most 16 boxes take the 16-box layout.
+template <int K_, int W_, int NB_>
+struct Shape {
+  static constexpr int K = K_, W = W_, NB = NB_;
+};
+template <class F>
+static auto with_shape(int max_contacts, int waves, int max_nb, F f) {
+  if (max_contacts > 256) return f(Shape<8, 1, 32>{});
+  if (max_contacts > 128) return waves == 2 ? f(Shape<4, 2, 32>{}) : f(Shape<4, 1, 32>{});
+  if (max_nb > 16) return waves == 2 ? f(Shape<2, 2, 32>{}) : f(Shape<2, 1, 32>{});
+  return waves == 2 ? f(Shape<2, 2, 16>{}) : f(Shape<2, 1, 16>{});
 }
 
-hipError_t launch_step(const StepArgs& a, int max_contacts, hipStream_t stream, int waves) {
+static hipError_t launch_shape(const StepArgs& a, int max_contacts, hipStream_t stream, int grid, int waves, int max_nb) {
+  return with_shape(max_contacts, waves, max_nb, [&](auto t) {
+    using T = decltype(t);
+    hipLaunchKernelGGL((step_kernel<T::K, T::W, T::NB>), dim3(grid), dim3(64 * T::W), 0, stream, a);
+    return hipGetLastError();
+  });
+}
+
+hipError_t launch_step(const StepArgs& a, int max_contacts, hipStream_t stream, int waves, int max_nb) {
   const int n = a.n_envs - a.env_base;
-  if (n <= 0) return hipSuccess;
-  return waves == 2 ? launch_class<2>(a, max_contacts, stream, n) : launch_class<1>(a, max_contacts, stream, n);
+  return n <= 0 ? hipSuccess : launch_shape(a, max_contacts, stream, n, waves, max_nb);
 }
 
-hipError_t launch_step_class(const StepArgs& a, int max_contacts, hipStream_t stream, int grid, int waves) {
+hipError_t launch_step_class(const StepArgs& a, int max_contacts, hipStream_t stream, int grid, int waves, int max_nb) {
   if (grid <= 0 || !a.queue) return hipErrorInvalidValue;
-  return waves == 2 ? launch_class<2>(a, max_contacts, stream, grid) : launch_class<1>(a, max_contacts, stream, grid);
+  return launch_shape(a, max_contacts, stream, grid, waves, max_nb);
 }
 
-hipError_t launch_cost(const StepArgs& a, int max_contacts, hipStream_t stream, int waves) {
+hipError_t launch_cost(const StepArgs& a, int max_contacts, hipStream_t stream, int waves, int max_nb) {
   const int n = a.n_envs - a.env_base;
   if (n <= 0 || !a.cost_key) return n <= 0 ? hipSuccess : hipErrorInvalidValue;
   StepArgs c = a;
   if (c.n_substeps < 1) c.n_substeps = 1;   // the estimate comes from the first substep
-  const dim3 block(64 * (waves == 2 ? 2 : 1));
-  if (waves == 2) {
-    if (max_contacts <= 128) hipLaunchKernelGGL((cost_kernel<2, 2>), dim3(n), block, 0, stream, c);
-    else if (max_contacts <= 256) hipLaunchKernelGGL((cost_kernel<4, 2>), dim3(n), block, 0, stream, c);
-    else hipLaunchKernelGGL((cost_kernel<8, 2>), dim3(n), block, 0, stream, c);
-  } else {
-    if (max_contacts <= 128) hipLaunchKernelGGL((cost_kernel<2, 1>), dim3(n), block, 0, stream, c);
-    else if (max_contacts <= 256) hipLaunchKernelGGL((cost_kernel<4, 1>), dim3(n), block, 0, stream, c);
-    else hipLaunchKernelGGL((cost_kernel<8, 1>), dim3(n), block, 0, stream, c);
-  }
-  return hipGetLastError();
+  return with_shape(max_contacts, waves, max_nb, [&](auto t) {
+    using T = decltype(t);
+    hipLaunchKernelGGL((cost_kernel<T::K, T::W, T::NB>), dim3(n), dim3(64 * T::W), 0, stream, c);
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_order(const int* key, int n, int* order, int* queue, hipStream_t stream) {
@@ -1934,18 +2022,14 @@ hipError_t launch_zero(int* p, int n, hipStream_t stream) {
   return hipGetLastError();
 }
 
-template <int W>
-static int blocks_per_cu(int max_contacts) {
-  int n = 0;
-  hipError_t e;
-  if (max_contacts <= 128) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, step_kernel<2, W>, 64 * W, 0);
-  else if (max_contacts <= 256) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, step_kernel<4, W>, 64 * W, 0);
-  else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, step_kernel<8, W>, 64 * W, 0);
-  return e == hipSuccess ? n : 0;
-}
-
-int step_blocks_per_cu(int max_contacts, int waves) {
-  return waves == 2 ? blocks_per_cu<2>(max_contacts) : blocks_per_cu<1>(max_contacts);
+int step_blocks_per_cu(int max_contacts, int waves, int max_nb) {
+  return with_shape(max_contacts, waves, max_nb, [&](auto t) {
+    using T = decltype(t);
+    int n = 0;
+    const hipError_t e =
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, step_kernel<T::K, T::W, T::NB>, 64 * T::W, 0);
+    return e == hipSuccess ? n : 0;
+  });
 }
 
 hipError_t launch_pool(const PoolArgs& a, hipStream_t stream) {

@@ -214,6 +214,12 @@ pmbs_status upload_pool_slot(pmbs_sim_t* sim, int slot, int n, const float* stat
   return PMBS_OK;
 }
 
+static int32_t most_bodies(const std::vector<int32_t>& off) {
+  int32_t m = 0;
+  for (size_t e = 0; e + 1 < off.size(); ++e) m = std::max(m, off[e + 1] - off[e]);
+  return m;
+}
+
 pmbs_status set_layout(pmbs_sim_t* sim, int n_envs, const int32_t* env_offset, const int32_t* bc_base) {
   if (n_envs < 0 || n_envs > sim->cfg.max_envs) return fail(PMBS_ERR_CAPACITY, "n_envs %d > max_envs", n_envs);
   if (env_offset[0] != 0) return fail(PMBS_ERR_INVALID_ARG, "env_offset[0] must be 0");
@@ -230,6 +236,7 @@ pmbs_status set_layout(pmbs_sim_t* sim, int n_envs, const int32_t* env_offset, c
   if (e == hipSuccess) e = hipStreamSynchronize(sim->stream);
   if (e != hipSuccess) return hip_fail(e, "layout upload");
   sim->host_offset.assign(env_offset, env_offset + n_envs + 1);
+  sim->max_nb = most_bodies(sim->host_offset);
   sim->n_envs = n_envs;
   sim->n_bodies = 0;
   sim->pool_layout = true;
@@ -265,14 +272,16 @@ pmbs_status rewards_from_pool(pmbs_sim_t* sim, const int32_t* slots, const int32
   return PMBS_OK;
 }
 
-static int class_index(int max_contacts) { return max_contacts <= 128 ? 0 : max_contacts <= 256 ? 1 : 2; }
+int shape_index(int max_contacts, int max_nb) {
+  return max_contacts <= 128 ? (max_nb <= 16 ? 0 : 3) : max_contacts <= 256 ? 1 : 2;
+}
 
 int plan_waves(const pmbs_sim_t* sim, int max_contacts) {
   const int w = max_contacts <= 128 ? sim->plan.small_waves : max_contacts <= 256 ? sim->plan.large_waves : 1;
   return w == 2 ? 2 : 1;
 }
 
-int class_grid(pmbs_sim_t* sim, int max_contacts, int blocks_per_cu, int waves) {
+int class_grid(pmbs_sim_t* sim, int max_contacts, int blocks_per_cu, int waves, int max_nb) {
   if (sim->cus <= 0) {
     int dev = 0;
     sim->cus = 256;
@@ -280,9 +289,9 @@ int class_grid(pmbs_sim_t* sim, int max_contacts, int blocks_per_cu, int waves) 
     if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
       sim->cus = prop.multiProcessorCount;
   }
-  const int k = class_index(max_contacts), w = waves == 2 ? 1 : 0;
+  const int k = shape_index(max_contacts, max_nb), w = waves == 2 ? 1 : 0;
   if (sim->occ[k][w] <= 0) {
-    const int o = step_blocks_per_cu(max_contacts, waves == 2 ? 2 : 1);
+    const int o = step_blocks_per_cu(max_contacts, waves == 2 ? 2 : 1, max_nb);
     sim->occ[k][w] = o > 0 ? o : 1;
   }
   const int per_cu = blocks_per_cu > 0 && blocks_per_cu < sim->occ[k][w] ? blocks_per_cu : sim->occ[k][w];
@@ -323,7 +332,9 @@ hipError_t enqueue_queued(pmbs_sim_t* sim, const StepArgs& a, hipStream_t stream
   // persistent workgroups of the two classes; with the counts known (no
   // capture) never more than the class has envs, so a batch of at most one
   // env per CU gets one workgroup per CU (none sharing a CU with another)
-  int grid_s = class_grid(sim, 128, pl.small_blocks_per_cu, ws), grid_l = class_grid(sim, 256, pl.large_blocks_per_cu, wl);
+  const int nb_s = small_nb(sim), nb_l = sim->max_nb;
+  int grid_s = class_grid(sim, 128, pl.small_blocks_per_cu, ws, nb_s);
+  int grid_l = class_grid(sim, 256, pl.large_blocks_per_cu, wl, nb_l);
   if (skip_empty) {
     grid_s = std::max(1, std::min(grid_s, n_small));
     grid_l = std::max(1, std::min(grid_l, n_large));
@@ -335,7 +346,7 @@ hipError_t enqueue_queued(pmbs_sim_t* sim, const StepArgs& a, hipStream_t stream
   sm.work_count = ctl + 8;
   sm.queue = ctl + 0;
   if (mc == 128) {
-    if (!skip_empty || n_small > 0) e = launch_step_class(sm, 128, stream, grid_s, ws);
+    if (!skip_empty || n_small > 0) e = launch_step_class(sm, 128, stream, grid_s, ws, nb_s);
     if (e == hipSuccess && va) e = launch_valid_counted(sim, *va, stream);
     return e;
   }
@@ -358,16 +369,17 @@ hipError_t enqueue_queued(pmbs_sim_t* sim, const StepArgs& a, hipStream_t stream
   if (run_large) {
     if ((e = hipEventRecord(sim->ev_fork, stream)) != hipSuccess) return e;
     if ((e = hipStreamWaitEvent(sim->side, sim->ev_fork, 0)) != hipSuccess) return e;
-    if ((e = launch_step_class(lg, 256, sim->side, grid_l, wl)) != hipSuccess) return e;
+    if ((e = launch_step_class(lg, 256, sim->side, grid_l, wl, nb_l)) != hipSuccess) return e;
     if ((e = hipEventRecord(sim->ev_join, sim->side)) != hipSuccess) return e;
   }
   if (run_small) {
-    if ((e = launch_step_class(sm, 128, stream, grid_s, ws)) != hipSuccess) return e;
-    if ((e = launch_step_class(f4, 256, stream, class_grid(sim, 256, pl.large_blocks_per_cu, wl), wl)) != hipSuccess)
+    if ((e = launch_step_class(sm, 128, stream, grid_s, ws, nb_s)) != hipSuccess) return e;
+    if ((e = launch_step_class(f4, 256, stream, class_grid(sim, 256, pl.large_blocks_per_cu, wl, nb_s), wl, nb_s)) !=
+        hipSuccess)
       return e;
   }
   if (run_large && (e = hipStreamWaitEvent(stream, sim->ev_join, 0)) != hipSuccess) return e;
-  if (mc > 256) e = launch_step_class(f8, 512, stream, class_grid(sim, 512, 0, 1), 1);
+  if (mc > 256) e = launch_step_class(f8, 512, stream, class_grid(sim, 512, 0, 1, nb_l), 1, nb_l);
   if (e == hipSuccess && va) e = launch_valid_counted(sim, *va, stream);
   return e;
 }
@@ -398,6 +410,8 @@ pmbs_status check_rollout_inputs(const pmbs_sim_t* sim, const int32_t* actions, 
 int class_split(const pmbs_sim_t* sim) {
   return sim->cfg.max_contacts == 128 ? PMBS_MAX_BODIES_PER_ENV : sim->plan.small_max_bodies;
 }
+
+int small_nb(const pmbs_sim_t* sim) { return std::min(class_split(sim), (int)sim->max_nb); }
 
 int64_t work_weight(const pmbs_sim_t* sim, const int32_t* act_offset, int e) {
   const int h = act_offset[e + 1] - act_offset[e], nb = sim->host_offset[e + 1] - sim->host_offset[e];
@@ -640,6 +654,7 @@ pmbs_status pmbs_sim_set_state(pmbs_sim_t* sim, int32_t n_envs, const int32_t* e
   e = hipStreamSynchronize(sim->stream);
   if (e != hipSuccess) return hip_fail(e, "set_state sync");
   sim->host_offset.assign(env_offset, env_offset + n_envs + 1);
+  sim->max_nb = most_bodies(sim->host_offset);
   sim->n_envs = n_envs;
   sim->n_bodies = n;
   sim->pool_layout = false;
@@ -674,7 +689,7 @@ pmbs_status pmbs_sim_step(pmbs_sim_t* sim, const float* push, int32_t push_is_de
   a.n_substeps = n_substeps;
   const int mc = sim->cfg.max_contacts, waves = plan_waves(sim, mc);
   hipError_t e = hipSuccess;
-  const int grid = class_grid(sim, mc, 0, waves);
+  const int grid = class_grid(sim, mc, 0, waves, sim->max_nb);
   if (sim->plan.order != 0 && n_substeps > 0 && sim->n_envs > grid && grid >= 8) {
     // more envs than resident workgroups: a cost pass estimates each env's
     // work at its start pose, and persistent workgroups take the envs from
@@ -684,14 +699,14 @@ pmbs_status pmbs_sim_step(pmbs_sim_t* sim, const float* push, int32_t push_is_de
     // are d_ctl[16..23], which rollouts leave alone)
     StepArgs c = a;
     c.cost_key = sim->d_order + sim->cfg.max_envs;
-    e = launch_cost(c, mc, sim->stream, waves);
+    e = launch_cost(c, mc, sim->stream, waves, sim->max_nb);
     if (e == hipSuccess) e = launch_order(c.cost_key, sim->n_envs, sim->d_order, sim->d_ctl + 16, sim->stream);
     a.order = sim->d_order;
     a.queue = sim->d_ctl + 16;
     a.xcd_queues = 1;
-    if (e == hipSuccess) e = launch_step_class(a, mc, sim->stream, grid, waves);
+    if (e == hipSuccess) e = launch_step_class(a, mc, sim->stream, grid, waves, sim->max_nb);
   } else {
-    e = launch_step(a, mc, sim->stream, waves);
+    e = launch_step(a, mc, sim->stream, waves, sim->max_nb);
   }
   if (e != hipSuccess) return hip_fail(e, "step launch");
   return PMBS_OK;
@@ -900,7 +915,7 @@ pmbs_status pmbs_sim_rollout_ex(pmbs_sim_t* sim, const int32_t* actions, const i
   ValidArgs va = valid_args(sim, a.child_slot);
   const ValidArgs* vap = (flags & PMBS_ROLLOUT_CHILD_VALID) && a.child_slot ? &va : nullptr;
   if (!use_queue) {
-    hipError_t e = launch_step(a, sim->cfg.max_contacts, sim->stream, plan_waves(sim, sim->cfg.max_contacts));
+    hipError_t e = launch_step(a, sim->cfg.max_contacts, sim->stream, plan_waves(sim, sim->cfg.max_contacts), sim->max_nb);
     if (e == hipSuccess && vap) e = launch_valid(va, sim->stream);
     if (e != hipSuccess) return hip_fail(e, "rollout launch");
     return PMBS_OK;
@@ -910,7 +925,8 @@ pmbs_status pmbs_sim_rollout_ex(pmbs_sim_t* sim, const int32_t* actions, const i
   if (e != hipSuccess) return hip_fail(e, "stream creation");
   for (int mc : {128, 256, 512})
     if (mc <= sim->cfg.max_contacts)
-      for (int w : {1, 2}) (void)class_grid(sim, mc, 0, w);  // occupancy queries outside any capture
+      for (int w : {1, 2})   // occupancy queries outside any capture
+        for (int nb : {small_nb(sim), (int)sim->max_nb}) (void)class_grid(sim, mc, 0, w, nb);
   if (!(flags & PMBS_ROLLOUT_GRAPH)) {
     e = enqueue_queued(sim, a, sim->stream, true, counts[0], counts[1], vap);
     if (e != hipSuccess) return hip_fail(e, "rollout launch");
@@ -918,7 +934,8 @@ pmbs_status pmbs_sim_rollout_ex(pmbs_sim_t* sim, const int32_t* actions, const i
   }
   const int with_valid = vap ? 1 : 0;
   if (!sim->graph_exec || std::memcmp(&sim->graph_args, &a, sizeof a) != 0 ||
-      std::memcmp(&sim->graph_plan, &sim->plan, sizeof sim->plan) != 0 || sim->graph_valid != with_valid) {
+      std::memcmp(&sim->graph_plan, &sim->plan, sizeof sim->plan) != 0 || sim->graph_valid != with_valid ||
+      (sim->graph_small_nb > 16) != (small_nb(sim) > 16)) {
     if (sim->graph_exec) (void)hipGraphExecDestroy(sim->graph_exec);
     if (sim->graph) (void)hipGraphDestroy(sim->graph);
     sim->graph_exec = nullptr;
@@ -941,6 +958,7 @@ pmbs_status pmbs_sim_rollout_ex(pmbs_sim_t* sim, const int32_t* actions, const i
     sim->graph_args = a;
     sim->graph_plan = sim->plan;
     sim->graph_valid = with_valid;
+    sim->graph_small_nb = small_nb(sim);
   }
   e = hipGraphLaunch(sim->graph_exec, sim->stream);
   if (e != hipSuccess) return hip_fail(e, "graph launch");
@@ -1008,7 +1026,7 @@ pmbs_status pmbs_sim_collide(pmbs_sim_t* sim, const float* push, int32_t push_is
   a.collide_only = 1;
   a.dbg_count = d_counts;
   a.dbg_contacts = d_contacts;
-  hipError_t e = launch_step(a, sim->cfg.max_contacts, sim->stream);
+  hipError_t e = launch_step(a, sim->cfg.max_contacts, sim->stream, 1, sim->max_nb);
   if (e != hipSuccess) return hip_fail(e, "collide launch");
   return PMBS_OK;
 }

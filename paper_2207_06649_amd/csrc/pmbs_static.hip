@@ -147,7 +147,7 @@ pmbs_status pmbs_sim_rollout_static(pmbs_sim_t* sim, const int32_t* actions, con
   // stream): 128-contact list, 256-contact list, then the fallbacks
   const int mc = sim->cfg.max_contacts;
   const pmbs_launch_plan& pl = sim->plan;
-  const int ws = plan_waves(sim, 128), wl = plan_waves(sim, 256);
+  const int ws = plan_waves(sim, 128), wl = plan_waves(sim, 256), nb_s = small_nb(sim), nb_l = sim->max_nb;
   int32_t* ctl = sc + O_CTL;
   // the children's validity words, after every class
   const bool child_valid = (flags & PMBS_ROLLOUT_CHILD_VALID) && child_slot;
@@ -157,7 +157,7 @@ pmbs_status pmbs_sim_rollout_static(pmbs_sim_t* sim, const int32_t* actions, con
   sm.work_count = ctl + 8;
   sm.queue = ctl + 0;
   if (mc == 128) {
-    if (ns > 0) e = launch_step_class(sm, 128, s, class_grid(sim, 128, pl.small_blocks_per_cu, ws), ws);
+    if (ns > 0) e = launch_step_class(sm, 128, s, class_grid(sim, 128, pl.small_blocks_per_cu, ws, nb_s), ws, nb_s);
     if (e == hipSuccess && child_valid) e = launch_valid(va, s);
     return e == hipSuccess ? PMBS_OK : hip_fail(e, "static rollout launch");
   }
@@ -176,12 +176,12 @@ pmbs_status pmbs_sim_rollout_static(pmbs_sim_t* sim, const int32_t* actions, con
   f8.order = sc + O_OVF8;
   f8.work_count = ctl + 5;
   f8.queue = ctl + 3;
-  if (ns > 0) e = launch_step_class(sm, 128, s, class_grid(sim, 128, pl.small_blocks_per_cu, ws), ws);
+  if (ns > 0) e = launch_step_class(sm, 128, s, class_grid(sim, 128, pl.small_blocks_per_cu, ws, nb_s), ws, nb_s);
   if (e == hipSuccess && nl > 0)
-    e = launch_step_class(lg, 256, s, class_grid(sim, 256, pl.large_blocks_per_cu, wl), wl);
+    e = launch_step_class(lg, 256, s, class_grid(sim, 256, pl.large_blocks_per_cu, wl, nb_l), wl, nb_l);
   if (e == hipSuccess && ns > 0)
-    e = launch_step_class(f4, 256, s, class_grid(sim, 256, pl.large_blocks_per_cu, wl), wl);
-  if (e == hipSuccess && mc > 256) e = launch_step_class(f8, 512, s, class_grid(sim, 512, 0, 1), 1);
+    e = launch_step_class(f4, 256, s, class_grid(sim, 256, pl.large_blocks_per_cu, wl, nb_l), wl, nb_l);
+  if (e == hipSuccess && mc > 256) e = launch_step_class(f8, 512, s, class_grid(sim, 512, 0, 1, nb_l), 1, nb_l);
   if (e == hipSuccess && child_valid) e = launch_valid(va, s);
   return e == hipSuccess ? PMBS_OK : hip_fail(e, "static rollout launch");
 }

@@ -43,3 +43,68 @@ def test_reward_shared_vertices(pm, n):
         else:
             assert abs(clr[0] - want) <= 1e-6 + 1e-5 * want
             assert abs(rew[0] - O.reward(st, bd, target, 0.08)) <= 2e-5
+
+
+def flat_scene(n, seed):
+    """n boxes in a grid, two of three thinner than the contact margin, so that
+    all eight corners touch the table (four of them past the lanes' own)."""
+    rng = np.random.default_rng(seed)
+    st, bd = np.zeros((n, 13)), np.zeros((n, 5))
+    for i in range(n):
+        hz = 0.02 if i % 3 == 0 else 0.0008
+        yaw = rng.uniform(0, 3)
+        st[i] = [0.07 * (i % 6) - 0.2, 0.07 * (i // 6) - 0.2, hz, np.cos(yaw / 2), 0, 0, np.sin(yaw / 2),
+                 *rng.normal(scale=0.02, size=3), 0, 0, rng.normal(scale=0.1)]
+        bd[i] = [rng.uniform(0.01, 0.02), rng.uniform(0.01, 0.02), hz, rng.uniform(0.05, 0.2), 0.5]
+    return f32(st), f32(bd)
+
+
+def stepped(pm, off, st, bd, push, n_sub, waves=1, contacts=128):
+    sim = pm.Sim(max_envs=len(off) - 1, max_bodies=int(off[-1]), max_contacts=contacts)
+    sim.set_launch_plan(small_waves=waves, large_waves=waves)
+    sim.set_state(off, st, bd)
+    sim.step(np.asarray(push, np.float32).reshape(-1, 4), n_sub)
+    return sim.get_state(), sim.env_status(), sim.stats()
+
+
+FAR = [5.0, 5.0, 5.1, 5.0]
+
+
+@pytest.mark.parametrize("waves", [1, 2])
+@pytest.mark.parametrize("n", [1, 4, 13, 16, 17, 20])
+def test_flat_boxes_match_oracle(pm, n, waves):
+    """Corners past a box's fourth are row contacts: one substep against the
+    oracle under the bars of the other one-substep tests (1e-5 m and
+    quaternion, 1e-4 velocity)."""
+    st, bd = flat_scene(n, n)
+    contacts = 128 if n <= 16 else 256
+    g, status, stats = stepped(pm, [0, n], st, bd, FAR, 1, waves, contacts)
+    o, _, _ = O.step(O.make_config(max_contacts=contacts), np.array([0, n], np.int32), st, bd, f32([FAR]), 1)
+    assert status[0] == 0 and stats[0, 0] == 4 * ((n + 2) // 3) + 8 * (n - (n + 2) // 3)
+    assert np.abs(g[:, :7] - o[:, :7]).max() <= 1e-5
+    assert np.abs(g[:, 7:] - o[:, 7:]).max() <= 1e-4
+
+
+@pytest.mark.parametrize("n", [1, 5, 15, 16])
+def test_body_lane_layouts_agree(pm, n):
+    """Four lanes per body (up to 16 boxes in the launch) and two (an env of
+    17 boxes with it) give the same bits, as do one and two waves and the
+    larger contact classes, over a push with pair contacts and over flat
+    boxes whose corner sets change."""
+    c = scenes.clutter_batch(70 + n, 2, n)
+    fst, fbd = flat_scene(n, 3)
+    fst[:, 2] += 0.001      # they fall onto the table
+    envs = [(c.env(0).state, c.env(0).body), (c.env(1).state, c.env(1).body), (fst, fbd)]
+    x0 = c.state[0]         # a pusher that starts 4 mm beside the first box
+    push = np.array([[x0[0] - 0.05, x0[1], x0[0], x0[1]], c.push[1], FAR])
+    off = np.arange(4) * n
+    st, bd = np.concatenate([e[0] for e in envs]), np.concatenate([e[1] for e in envs])
+    want = stepped(pm, off, st, bd, push, 90)
+    big = scenes.clutter_batch(5, 1, 17)
+    off2, push2 = np.append(off, 3 * n + 17), np.vstack([push, big.push])
+    for waves in (1, 2):
+        for contacts in (128, 256, 512):
+            got = stepped(pm, off, st, bd, push, 90, waves, contacts)
+            assert all(np.array_equal(a, b) for a, b in zip(got, want)), (waves, contacts)
+        two = stepped(pm, off2, np.vstack([st, big.state]), np.vstack([bd, big.body]), push2, 90, waves)
+        assert np.array_equal(two[0][:3 * n], want[0]) and np.array_equal(two[2][:3], want[2]), waves
