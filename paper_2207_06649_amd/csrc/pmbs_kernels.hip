@@ -92,6 +92,12 @@ __device__ __forceinline__ int opaque(int x) {
   return x;
 }
 
+// A value that is the same in every lane, in scalar registers.
+__device__ __forceinline__ float uniform(float v) {
+  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+}
+__device__ __forceinline__ f3 uniform(f3 v) { return mk(uniform(v.x), uniform(v.y), uniform(v.z)); }
+
 // Orders the LDS accesses of the wave's lanes around this point.  A
 // workgroup is one wave and a wave's LDS operations are performed in issue
 // order, so a wavefront-scope fence (no wait instruction) plus a
@@ -844,7 +850,9 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
     st3(&s.col[1][nb], pc1);
     st3(&s.col[2][nb], mk(0, 0, 1));
   }
-  const f3 pext = aabb_ext(pc0, pc1, mk(0, 0, 1), ph, p.margin);
+  const f3 pext = uniform(aabb_ext(pc0, pc1, mk(0, 0, 1), ph, p.margin));
+  pdir = uniform(pdir);
+  n_move = __builtin_amdgcn_readfirstlane(n_move);
 
   const int n_sub = g.collide_only ? 1 : g.n_substeps;
   // impulses are carried within one push only: the row contacts' (nwarm of
@@ -883,19 +891,6 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
         st3(&s.u.n.x.box.lo[nb], xp - pext);
         st3(&s.u.n.x.box.hi[nb], xp + pext);
       }
-    }
-    // world inverse inertia Iw^-1 = R diag(invI) R^T: diagonal, off-diagonal (xy, xz, yz)
-    f3 md, mo;
-    {
-      const float r00 = c0.x, r01 = c1.x, r02 = c2.x;
-      const float r10 = c0.y, r11 = c1.y, r12 = c2.y;
-      const float r20 = c0.z, r21 = c1.z, r22 = c2.z;
-      md.x = r00 * invI.x * r00 + r01 * invI.y * r01 + r02 * invI.z * r02;
-      md.y = r10 * invI.x * r10 + r11 * invI.y * r11 + r12 * invI.z * r12;
-      md.z = r20 * invI.x * r20 + r21 * invI.y * r21 + r22 * invI.z * r22;
-      mo.x = r00 * invI.x * r10 + r01 * invI.y * r11 + r02 * invI.z * r12;
-      mo.y = r00 * invI.x * r20 + r01 * invI.y * r21 + r02 * invI.z * r22;
-      mo.z = r10 * invI.x * r20 + r11 * invI.y * r21 + r12 * invI.z * r22;
     }
     sync_all<W>();
 
@@ -1239,6 +1234,23 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
 
     // the rest of the substep is the lead wave's
     if (lead) {
+    // the body's rotation from LDS again (not held over the narrowphase)
+    c0 = xyz(s.col[0][active ? b : 0]);
+    c1 = xyz(s.col[1][active ? b : 0]);
+    c2 = xyz(s.col[2][active ? b : 0]);
+    // world inverse inertia Iw^-1 = R diag(invI) R^T: diagonal, off-diagonal (xy, xz, yz)
+    f3 md, mo;
+    {
+      const float r00 = c0.x, r01 = c1.x, r02 = c2.x;
+      const float r10 = c0.y, r11 = c1.y, r12 = c2.y;
+      const float r20 = c0.z, r21 = c1.z, r22 = c2.z;
+      md.x = r00 * invI.x * r00 + r01 * invI.y * r01 + r02 * invI.z * r02;
+      md.y = r10 * invI.x * r10 + r11 * invI.y * r11 + r12 * invI.z * r12;
+      md.z = r20 * invI.x * r20 + r21 * invI.y * r21 + r22 * invI.z * r22;
+      mo.x = r00 * invI.x * r10 + r01 * invI.y * r11 + r02 * invI.z * r12;
+      mo.y = r00 * invI.x * r20 + r01 * invI.y * r21 + r02 * invI.z * r22;
+      mo.z = r10 * invI.x * r20 + r11 * invI.y * r21 + r12 * invI.z * r22;
+    }
     // ---- 5. per-body lists of row contacts in contact-index order (CSR):
     // every row contact sets its bit in the masks of its two bodies; a
     // body's list length is its bit count; every contact then writes itself
