@@ -449,10 +449,19 @@ __device__ __forceinline__ float eff_mass_side(const S& s, int i, f3 r, f3 d) {
   return s.half[i].w + dot(cr, m);
 }
 
-// Row contact c of the staging array into registers, with its previous
-// impulse when the key was there (nwarm keys).
+// Tangent basis from the world axis least aligned with the normal.
+__device__ __forceinline__ void tangents(f3 n, f3* t1, f3* t2) {
+  float ax = fabsf(n.x), ay = fabsf(n.y), az = fabsf(n.z);
+  const int ei = (ax <= ay && ax <= az) ? 0 : (ay <= az ? 1 : 2);
+  f3 e = mk(ei == 0 ? 1.0f : 0.0f, ei == 1 ? 1.0f : 0.0f, ei == 2 ? 1.0f : 0.0f);
+  *t1 = cross(e, n);
+  *t1 = *t1 * rsq(dot(*t1, *t1));
+  *t2 = cross(n, *t1);
+}
+
+// Row contact c of the staging array into registers.
 template <class S>
-__device__ __forceinline__ void prep_contact(const S& s, int c, const Params& p, int nwarm, Contact* ct) {
+__device__ __forceinline__ void prep_contact(const S& s, int c, const Params& p, Contact* ct) {
   const float4 s0 = s.u.n.stage[c][0], s1 = s.u.n.stage[c][1];
   f3 pt = xyz(s0);
   float sep = s0.w;
@@ -463,30 +472,81 @@ __device__ __forceinline__ void prep_contact(const S& s, int c, const Params& p,
   ct->n = n;
   ct->ra = pt - xyz(s.pos[a]);
   ct->rb = pt - xyz(s.pos[b]);
-  float ax = fabsf(n.x), ay = fabsf(n.y), az = fabsf(n.z);
-  const int ei = (ax <= ay && ax <= az) ? 0 : (ay <= az ? 1 : 2);
-  f3 e = mk(ei == 0 ? 1.0f : 0.0f, ei == 1 ? 1.0f : 0.0f, ei == 2 ? 1.0f : 0.0f);
-  f3 t1 = cross(e, n);
-  t1 = t1 * rsq(dot(t1, t1));
-  f3 t2 = cross(n, t1);
-  ct->t2 = t2;
+  f3 t1, t2;
+  tangents(n, &t1, &t2);
   ct->t1 = t1;
+  ct->t2 = t2;
   float ca = (float)s.cnt[a], cb = (float)s.cnt[b];
   ct->kn = rcp(ca * eff_mass_side(s, a, ct->ra, n) + cb * eff_mass_side(s, b, ct->rb, n));
   ct->kt1 = rcp(ca * eff_mass_side(s, a, ct->ra, t1) + cb * eff_mass_side(s, b, ct->rb, t1));
   ct->kt2 = rcp(ca * eff_mass_side(s, a, ct->ra, t2) + cb * eff_mass_side(s, b, ct->rb, t2));
   ct->mu = 0.5f * (s.iwb[a].z + s.iwb[b].z);
   ct->vstar = sep > 0.0f ? -sep * p.inv_dt : p.beta * fmaxf(-sep - p.slop, 0.0f) * p.inv_dt;
-  // warm start from the previous substep's contact with the same key
-  ct->ln = ct->lt1 = ct->lt2 = 0.0f;
-  const int key = contact_key<S>(ab);
+}
+
+// The impulse (n, t1, t2) that row contact c starts from: the previous
+// substep's of the same key, among its nwarm rows or, for one of the n_extra
+// table corners among the rows, in the impulses that the lanes left in LDS.
+template <class S>
+__device__ __forceinline__ f3 warm_impulse(const S& s, int c, int nwarm, int n_extra) {
+  const int ab = s.cab[c], key = contact_key<S>(ab);
   // an unchanged list prefix has it at the same index
   const int i = c < nwarm && s.wkey[c] == key ? c : warm_index(s, key, nwarm);
-  if (i >= 0) {
-    ct->ln = s.wl[0][i];
-    ct->lt1 = s.wl[1][i];
-    ct->lt2 = s.wl[2][i];
+  f3 l = i >= 0 ? mk(s.wl[0][i], s.wl[1][i], s.wl[2][i]) : mk(0, 0, 0);
+  if (c < n_extra) {
+    const int b = (ab >> 8) & 255, kc = ab >> 16;
+    const unsigned old = (unsigned)__float_as_int(s.u.n.x.lam[4 * b].w);
+    const int o = __popc(old & ((1u << kc) - 1u));
+    if ((old >> kc & 1u) && o < 4) l = xyz(s.u.n.x.lam[4 * b + o]);
   }
+  return l;
+}
+
+// A row contact spread over four lanes: lane q of the quad has row q of its
+// frame (q = 0 normal, 1 and 2 tangents; impulse lam, effective mass k) and
+// component q of its vectors (lane 3 repeats lane 0 and is not read).
+struct QuadContact {
+  int at_a, at_b;             // bodies a and b: offset of their velocity's component q
+  f3 dir, comp;               // frame row q; component q of the three rows
+  float ra1, ra2, rb1, rb2;   // components q + 1 and q + 2 of the lever arms
+  float k, vs, mu, lam, lo, hi;
+};
+
+// Components q, q + 1 and q + 2 (cyclic) of a vector.
+__device__ __forceinline__ f3 turn(f3 v, int q) {
+  return sel(q == 1, mk(v.y, v.z, v.x), sel(q == 2, mk(v.z, v.x, v.y), v));
+}
+
+// Row contact c of the staging array into the lanes of a quad: the terms of
+// prep_contact, each lane with its own row's effective mass.
+template <class S>
+__device__ __forceinline__ void prep_quad(const S& s, int c, int q, const Params& p, QuadContact* ct) {
+  const float4 s0 = s.u.n.stage[c][0];
+  const f3 pt = xyz(s0), n = xyz(s.u.n.stage[c][1]);
+  const float sep = s0.w;
+  const int ab = s.cab[c], a = ab & 255, b = (ab >> 8) & 255;
+  const f3 ra = pt - xyz(s.pos[a]), rb = pt - xyz(s.pos[b]);
+  f3 t1, t2;
+  tangents(n, &t1, &t2);
+  const f3 d = sel(q == 1, t1, sel(q == 2, t2, n));
+  const float ca = (float)s.cnt[a], cb = (float)s.cnt[b];
+  ct->k = rcp(ca * eff_mass_side(s, a, ra, d) + cb * eff_mass_side(s, b, rb, d));
+  ct->mu = 0.5f * (s.iwb[a].z + s.iwb[b].z);
+  const float vstar = sep > 0.0f ? -sep * p.inv_dt : p.beta * fmaxf(-sep - p.slop, 0.0f) * p.inv_dt;
+  const bool normal = q != 1 && q != 2;
+  ct->vs = normal ? vstar : 0.0f;
+  ct->lo = normal ? 0.0f : -INFINITY;   // the normal impulse is clamped from below,
+  ct->hi = normal ? 1.0f : -INFINITY;   // and not scaled by the friction disc
+  ct->dir = d;
+  ct->comp = mk(turn(n, q).x, turn(t1, q).x, turn(t2, q).x);
+  const f3 ta = turn(ra, q), tb = turn(rb, q);
+  ct->ra1 = ta.y;
+  ct->ra2 = ta.z;
+  ct->rb1 = tb.y;
+  ct->rb2 = tb.z;
+  const int qc = q < 3 ? q : 0;
+  ct->at_a = 4 * a + qc;
+  ct->at_b = 4 * b + qc;
 }
 
 // A table contact: normal z, tangents -y and x, nothing on side a.  The
@@ -674,9 +734,10 @@ __device__ __forceinline__ void sync_all() {
 // -y and x, nothing on side a.  With the terms that are exactly zero left out
 // (the same bits) and the body in the same lanes such a contact costs 28
 // instructions instead of 61 and no LDS, and an environment of which no box
-// touches another iterates without LDS at all.  4096 x 15: 3.15 -> 2.29 ms;
-// 700 x 27: 2.66 -> 1.89; 1024 x 15 on two waves: 1.50 -> 1.31; 64 x 9, one
-// wave per SIMD: 1.19 -> 1.14.
+// touches another iterates without LDS at all.  4096 x 15: 3.15 -> 2.19 ms;
+// 700 x 27: 2.66 -> 1.85; 1024 x 15 on two waves: 1.50 -> 1.32; 64 x 9, one
+// wave per SIMD: 1.19 -> 1.10.  With row contacts in quads of lanes (below):
+// 2.09, 1.73, 1.18 and 0.97 ms.
 //
 // With W > 1 waves per environment the second wave tests the broadphase pairs
 // while the lead finds the table contacts, and takes every second narrowphase
@@ -1364,8 +1425,8 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
       corners = mask;
     }
 
-    // ---- 6. contact prep: the lanes' table contacts (an absent one has zero
-    // masses, so its impulses stay zero), then the row contacts
+    // ---- 6. prep of the lanes' table contacts (an absent one has zero
+    // masses, so its impulses stay zero)
     const float cbn = (float)(nh + n_inc);
 #pragma unroll
     for (int ts = 0; ts < TS; ++ts) {
@@ -1384,36 +1445,6 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
       q.kt2 = on ? rcp(cbn * (invm + em.z)) : 0.0f;
       q.vstar = sep > 0.0f ? -sep * p.inv_dt : p.beta * fmaxf(-sep - p.slop, 0.0f) * p.inv_dt;
     }
-    Contact ct[K];
-    if (n_rows > 0) {
-      wave_sync();
-#pragma unroll
-      for (int sl = 0; sl < K; ++sl) {
-        const int c = 64 * sl + lane;
-        if (64 * sl < n_rows) {
-          if (c < n_rows) {
-            prep_contact(s, c, p, nwarm, &ct[sl]);
-            if (n_extra > 0 && c < n_extra) {
-              // a table corner among the rows: its impulse may have been a lane's
-              const int bb = (ct[sl].ab >> 8) & 255, kc = ct[sl].ab >> 16;
-              const unsigned old = (unsigned)__float_as_int(s.u.n.x.lam[4 * bb].w);
-              const int o = __popc(old & ((1u << kc) - 1u));
-              if ((old >> kc & 1u) && o < 4) {
-                const float4 l = s.u.n.x.lam[4 * bb + o];
-                ct[sl].ln = l.x;
-                ct[sl].lt1 = l.y;
-                ct[sl].lt2 = l.z;
-              }
-            }
-          } else {
-            // an absent contact of the table with itself: zero impulses
-            const f3 z = mk(0, 0, 0);
-            ct[sl] = Contact{PLANE | (PLANE << 8), z, z, z, z, z, 0, 0, 0, 0, 0, 0, 0, 0};
-          }
-        }
-      }
-    }
-
     // ---- 7. projected Jacobi, I iterations.  A body's velocity changes by M
     // times the sum of its contacts' impulses (M: inverse mass, world inverse
     // inertia), added as two partial sums over the even and the odd entries of its
@@ -1505,10 +1536,11 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
       const bool rows4 = __ballot(n_inc > k0 + 2 * RG) != 0ull;
       auto sums = [&]() {
         f3 lin, ang;
-        table_sums(&lin, &ang);
         if constexpr (L == 4) {
-          f3 a = sel(ang_lane, ang, lin);
           const f3 r0 = row_at(radr[0]), r1 = row_at(radr[1]);
+          __builtin_amdgcn_sched_barrier(0);
+          table_sums(&lin, &ang);   // while the loads are in flight
+          f3 a = sel(ang_lane, ang, lin);
           a = add_signed(a, rsg[0], r0);
           a = add_signed(a, rsg[1], r1);
           if (rows2) {
@@ -1525,6 +1557,8 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
           apply(quad<Q_LOW>(a), quad<Q_HIGH>(a));
         } else {
           const f3 r0 = row_at(radr[0]), r1 = row_at(radr[1]), t0 = row_at(rada[0]), t1 = row_at(rada[1]);
+          __builtin_amdgcn_sched_barrier(0);
+          table_sums(&lin, &ang);
           lin = add_signed(lin, rsg[0], r0);
           lin = add_signed(lin, rsg[1], r1);
           ang = add_signed(ang, rsg[0], t0);
@@ -1546,63 +1580,140 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
           apply(lin + quad<Q_XOR1>(lin), ang + quad<Q_XOR1>(ang));
         }
       };
-      auto put_rows = [&](int c, const Contact& q, f3 R) {
-        st3(&s.u.imp[0][c], R);
-        st3(&s.u.imp[1][c], cross(q.ra, R));
-        st3(&s.u.imp[2][c], cross(q.rb, R));
-      };
-      // warm start: the impulses carried over from the previous substep (the
-      // impulse rows share LDS with the staging array every prep has read)
-      wave_sync();
-#pragma unroll
-      for (int sl = 0; sl < K; ++sl)
-        if (64 * sl < n_rows) {
-          const Contact& q = ct[sl];
-          put_rows(64 * sl + lane, q, fma3(q.n, q.ln, fma3(q.t1, q.lt1, q.t2 * q.lt2)));
-        }
-      wave_sync();
-      sums();
       // lane 0 of a body with row contacts publishes its linear, lane 1 its
-      // angular velocity
+      // angular velocity (as y, z, x, y: components q + 1 and q + 2 adjacent)
       float4* const vslot = j == 0 ? &s.vel[b < MB ? b : 0] : &s.ang[b < MB ? b : 0];
-      const bool publish = active && j < 2 && n_inc > 0;
-      for (int it = 0; it < p.iters; ++it) {
-        if (publish) st3(vslot, sel(j == 0, v, w));
+      const bool publisher = active && j < 2 && n_inc > 0;
+      auto publish = [&]() {
+        if (publisher) *vslot = j == 0 ? make_float4(v.x, v.y, v.z, 0.0f) : make_float4(w.y, w.z, w.x, w.y);
         wave_sync();   // the iteration-start velocities
+      };
+      // The row contacts' prep, then their warm start: the impulses carried
+      // over from the previous substep (the impulse rows share LDS with the
+      // staging array that the prep reads).  Up to 16 take a quad of lanes
+      // each, more a lane each: most environments have none or a few, and a
+      // quad's lanes share the three rows of an update (38 instructions
+      // instead of 61, and a third of the prep's masses).
+      wave_sync();
+      if (n_rows <= 16) {
+        QuadContact qc;
+        {
+          const int c = lane >> 2, q = lane & 3;
+          if (c < n_rows) {
+            prep_quad(s, c, q, p, &qc);
+            qc.lam = turn(warm_impulse(s, c, nwarm, n_extra), q).x;
+          } else {
+            // an absent contact of the table with itself: zero impulses
+            const f3 z = mk(0, 0, 0);
+            qc = QuadContact{4 * PLANE, 4 * PLANE, z, z, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+          }
+        }
+        wave_sync();
+        float* const rows = reinterpret_cast<float*>(&s.u.imp[0][0]) + lane;
+        auto put_rows = [&](float dl) {
+          const float R = fmaf(qc.comp.x, quad<0x00>(dl), fmaf(qc.comp.y, quad<0x55>(dl), qc.comp.z * quad<0xaa>(dl)));
+          const float R1 = quad<0xc9>(R), R2 = quad<0xd2>(R);   // components q + 1, q + 2
+          rows[0] = R;
+          rows[4 * C] = qc.ra1 * R2 - qc.ra2 * R1;
+          rows[8 * C] = qc.rb1 * R2 - qc.rb2 * R1;
+          wave_sync();   // the impulse rows
+        };
+        put_rows(qc.lam);
+        sums();
+        const float* const vel = reinterpret_cast<const float*>(&s.vel[0]);
+        const float* const ang = reinterpret_cast<const float*>(&s.ang[0]);
+        for (int it = 0; it < p.iters; ++it) {
+          publish();
+          const float va = vel[qc.at_a], wa1 = ang[qc.at_a], wa2 = ang[qc.at_a + 1];
+          const float vb = vel[qc.at_b], wb1 = ang[qc.at_b], wb2 = ang[qc.at_b + 1];
+          __builtin_amdgcn_sched_barrier(0);
+          table_update();   // while the loads are in flight
+          const float u = fmaf(wb1, qc.rb2, fmaf(-wb2, qc.rb1, vb)) - fmaf(wa1, qc.ra2, fmaf(-wa2, qc.ra1, va));
+          const f3 U = mk(quad<0x00>(u), quad<0x55>(u), quad<0xaa>(u));
+          float l = fmaxf(qc.lam + qc.k * (qc.vs - dot(U, qc.dir)), qc.lo);
+          const float ln = quad<0x00>(l), lt1 = quad<0x55>(l), lt2 = quad<0xaa>(l);
+          const float lim = qc.mu * ln, mag2 = lt1 * lt1 + lt2 * lt2;
+          l *= fmaxf(fminf(lim * rsq(mag2), 1.0f), qc.hi);
+          const float dl = l - qc.lam;
+          qc.lam = l;
+          put_rows(dl);
+          sums();
+        }
+        // remember this substep's accumulated impulses by key
+        const int c = lane >> 2, q = lane & 3;
+        if (c < n_rows && q < 3) {
+          if (q == 0) s.wkey[c] = contact_key<S>(s.cab[c]);
+          s.wl[q][c] = qc.lam;
+        }
+      } else {
+        Contact ct[K];
+#pragma unroll
+        for (int sl = 0; sl < K; ++sl) {
+          const int c = 64 * sl + lane;
+          if (64 * sl < n_rows) {
+            if (c < n_rows) {
+              prep_contact(s, c, p, &ct[sl]);
+              const f3 l = warm_impulse(s, c, nwarm, n_extra);
+              ct[sl].ln = l.x;
+              ct[sl].lt1 = l.y;
+              ct[sl].lt2 = l.z;
+            } else {
+              const f3 z = mk(0, 0, 0);
+              ct[sl] = Contact{PLANE | (PLANE << 8), z, z, z, z, z, 0, 0, 0, 0, 0, 0, 0, 0};
+            }
+          }
+        }
+        wave_sync();
+        auto put_rows = [&](int c, const Contact& q, f3 R) {
+          st3(&s.u.imp[0][c], R);
+          st3(&s.u.imp[1][c], cross(q.ra, R));
+          st3(&s.u.imp[2][c], cross(q.rb, R));
+        };
 #pragma unroll
         for (int sl = 0; sl < K; ++sl)
           if (64 * sl < n_rows) {
-            Contact& q = ct[sl];
-            const int a = q.ab & 255, bb = (q.ab >> 8) & 255;
-            const f3 va = xyz(s.vel[a]), wa = xyz(s.ang[a]), vb = xyz(s.vel[bb]), wb = xyz(s.ang[bb]);
-            if (sl == 0) table_update();   // while the loads are in flight
-            const f3 u = cross_add(wb, q.rb, vb) - cross_add(wa, q.ra, va);
-            const float ln = fmaxf(q.ln + q.kn * (q.vstar - dot(u, q.n)), 0.0f);
-            const float dln = ln - q.ln;
-            q.ln = ln;
-            float lt1 = q.lt1 - q.kt1 * dot(u, q.t1);
-            float lt2 = q.lt2 - q.kt2 * dot(u, q.t2);
-            const float lim = q.mu * ln, mag2 = lt1 * lt1 + lt2 * lt2;
-            const float sc = fminf(lim * rsq(mag2), 1.0f);
-            lt1 *= sc;
-            lt2 *= sc;
-            const float dl1 = lt1 - q.lt1, dl2 = lt2 - q.lt2;
-            q.lt1 = lt1;
-            q.lt2 = lt2;
-            put_rows(64 * sl + lane, q, fma3(q.n, dln, fma3(q.t1, dl1, q.t2 * dl2)));
+            const Contact& q = ct[sl];
+            put_rows(64 * sl + lane, q, fma3(q.n, q.ln, fma3(q.t1, q.lt1, q.t2 * q.lt2)));
           }
-        wave_sync();   // the impulse rows
+        wave_sync();
         sums();
-      }
-      // remember this substep's accumulated impulses by key
+        for (int it = 0; it < p.iters; ++it) {
+          publish();
 #pragma unroll
-      for (int sl = 0; sl < K; ++sl) {
-        const int c = 64 * sl + lane;
-        if (64 * sl < n_rows && c < n_rows) {
-          s.wkey[c] = contact_key<S>(ct[sl].ab);
-          s.wl[0][c] = ct[sl].ln;
-          s.wl[1][c] = ct[sl].lt1;
-          s.wl[2][c] = ct[sl].lt2;
+          for (int sl = 0; sl < K; ++sl)
+            if (sl == 0 || 64 * sl < n_rows) {
+              Contact& q = ct[sl];
+              const int a = q.ab & 255, bb = (q.ab >> 8) & 255;
+              const f3 va = xyz(s.vel[a]), ta = xyz(s.ang[a]), vb = xyz(s.vel[bb]), tb = xyz(s.ang[bb]);
+              const f3 wa = mk(ta.z, ta.x, ta.y), wb = mk(tb.z, tb.x, tb.y);
+              if (sl == 0) table_update();
+              const f3 u = cross_add(wb, q.rb, vb) - cross_add(wa, q.ra, va);
+              const float ln = fmaxf(q.ln + q.kn * (q.vstar - dot(u, q.n)), 0.0f);
+              const float dln = ln - q.ln;
+              q.ln = ln;
+              float lt1 = q.lt1 - q.kt1 * dot(u, q.t1);
+              float lt2 = q.lt2 - q.kt2 * dot(u, q.t2);
+              const float lim = q.mu * ln, mag2 = lt1 * lt1 + lt2 * lt2;
+              const float sc = fminf(lim * rsq(mag2), 1.0f);
+              lt1 *= sc;
+              lt2 *= sc;
+              const float dl1 = lt1 - q.lt1, dl2 = lt2 - q.lt2;
+              q.lt1 = lt1;
+              q.lt2 = lt2;
+              put_rows(64 * sl + lane, q, fma3(q.n, dln, fma3(q.t1, dl1, q.t2 * dl2)));
+            }
+          wave_sync();   // the impulse rows
+          sums();
+        }
+#pragma unroll
+        for (int sl = 0; sl < K; ++sl) {
+          const int c = 64 * sl + lane;
+          if (64 * sl < n_rows && c < n_rows) {
+            s.wkey[c] = contact_key<S>(ct[sl].ab);
+            s.wl[0][c] = ct[sl].ln;
+            s.wl[1][c] = ct[sl].lt1;
+            s.wl[2][c] = ct[sl].lt2;
+          }
         }
       }
     }

@@ -108,3 +108,21 @@ def test_body_lane_layouts_agree(pm, n):
             assert all(np.array_equal(a, b) for a, b in zip(got, want)), (waves, contacts)
         two = stepped(pm, off2, np.vstack([st, big.state]), np.vstack([bd, big.body]), push2, 90, waves)
         assert np.array_equal(two[0][:3 * n], want[0]) and np.array_equal(two[2][:3], want[2]), waves
+
+
+@pytest.mark.parametrize("n", [2, 5, 6, 17, 18])
+def test_row_contact_forms_match_oracle(pm, n):
+    """A tower of n cubes has four contacts between neighbours: 16 rows at
+    five cubes are the last in quads of lanes, 17 and more are one per lane,
+    65 and more (18 cubes) two.  One substep against the oracle under the bars
+    of the other one-substep tests."""
+    st, bd = np.zeros((n, 13)), np.zeros((n, 5))
+    for i in range(n):
+        st[i] = [0.0005 * (i % 3), -0.0004 * (i % 2), 0.02 + 0.0399 * i, 1, 0, 0, 0, 0.01 * (i % 2), 0, 0, 0, 0, 0]
+        bd[i] = [0.02, 0.02, 0.02, 0.1, 0.5]
+    st, bd = f32(st), f32(bd)
+    g, status, stats = stepped(pm, [0, n], st, bd, FAR, 1)
+    o, _, _ = O.step(O.make_config(), np.array([0, n], np.int32), st, bd, f32([FAR]), 1)
+    assert status[0] == 0 and stats[0, 0] == 4 * n
+    assert np.abs(g[:, :7] - o[:, :7]).max() <= 1e-5
+    assert np.abs(g[:, 7:] - o[:, 7:]).max() <= 1e-4
