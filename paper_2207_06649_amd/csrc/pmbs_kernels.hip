@@ -125,6 +125,7 @@ struct Smem {
   float4 pos[NOBJ];                  // centre
   float4 col[3][NOBJ];               // rotation columns (body axes in world)
   float4 half[NOBJ];                 // hx, hy, hz, inverse mass
+  float4 quat[MB];                   // orientation (the lanes' copy between the stages that use it)
   float4 iwa[NOBJ];                  // world inverse inertia xx, yy, zz, xy
   float4 iwb[NOBJ];                  // xz, yz, mu, -
   float4 vel[NOBJ];                  // solver snapshot: linear
@@ -509,7 +510,7 @@ struct QuadContact {
   int at_a, at_b;             // bodies a and b: offset of their velocity's component q
   f3 dir, comp;               // frame row q; component q of the three rows
   float ra1, ra2, rb1, rb2;   // components q + 1 and q + 2 of the lever arms
-  float k, vs, mu, lam, lo, hi;
+  float k, vs, mu, lam, lo;
 };
 
 // Components q, q + 1 and q + 2 (cyclic) of a vector.
@@ -531,12 +532,13 @@ __device__ __forceinline__ void prep_quad(const S& s, int c, int q, const Params
   const f3 d = sel(q == 1, t1, sel(q == 2, t2, n));
   const float ca = (float)s.cnt[a], cb = (float)s.cnt[b];
   ct->k = rcp(ca * eff_mass_side(s, a, ra, d) + cb * eff_mass_side(s, b, rb, d));
-  ct->mu = 0.5f * (s.iwb[a].z + s.iwb[b].z);
-  const float vstar = sep > 0.0f ? -sep * p.inv_dt : p.beta * fmaxf(-sep - p.slop, 0.0f) * p.inv_dt;
   const bool normal = q != 1 && q != 2;
+  const float vstar = sep > 0.0f ? -sep * p.inv_dt : p.beta * fmaxf(-sep - p.slop, 0.0f) * p.inv_dt;
+  ct->mu = normal ? INFINITY : 0.5f * (s.iwb[a].z + s.iwb[b].z);
   ct->vs = normal ? vstar : 0.0f;
-  ct->lo = normal ? 0.0f : -INFINITY;   // the normal impulse is clamped from below,
-  ct->hi = normal ? 1.0f : -INFINITY;   // and not scaled by the friction disc
+  // the normal impulse is clamped from below and not scaled by the friction
+  // disc: an infinite limit scales by 1, also where it gives a nan
+  ct->lo = normal ? 0.0f : -INFINITY;
   ct->dir = d;
   ct->comp = mk(turn(n, q).x, turn(t1, q).x, turn(t2, q).x);
   const f3 ta = turn(ra, q), tb = turn(rb, q);
@@ -812,6 +814,7 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
       st3(&s.col[0][b], c0);
       st3(&s.col[1][b], c1);
       st3(&s.col[2][b], c2);
+      s.quat[b] = make_float4(q0, q1, q2, q3);
     }
   };
 
@@ -938,7 +941,11 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
     f3 vp = pdir * vs;
     if (g.collide_only) vp = mk(0, 0, 0);
 
-    // ---- 2. frames and AABBs
+    // ---- 2. frames and AABBs.  Half extents, and after the narrowphase
+    // centre, rotation and orientation, are read back from LDS: held in
+    // registers over the substep they spill.
+    const int bl = active ? b : 0;
+    h = xyz(s.half[bl]);
     write_body_frames(b, first);
     {
       const f3 ext = aabb_ext(c0, c1, c2, h, p.margin);
@@ -1256,6 +1263,11 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
     stat_pairs += n_pairs;
     stat_sub += 1;
     sync_all<W>();   // every wave's contacts are in the staging array
+    x = xyz(s.pos[bl]);
+    h = xyz(s.half[bl]);
+    c0 = xyz(s.col[0][bl]);
+    c1 = xyz(s.col[1][bl]);
+    c2 = xyz(s.col[2][bl]);
 
     if (g.collide_only) {
       // the whole list: table contacts at their rank, then the staged pairs
@@ -1295,10 +1307,6 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
 
     // the rest of the substep is the lead wave's
     if (lead) {
-    // the body's rotation from LDS again (not held over the narrowphase)
-    c0 = xyz(s.col[0][active ? b : 0]);
-    c1 = xyz(s.col[1][active ? b : 0]);
-    c2 = xyz(s.col[2][active ? b : 0]);
     // world inverse inertia Iw^-1 = R diag(invI) R^T: diagonal, off-diagonal (xy, xz, yz)
     f3 md, mo;
     {
@@ -1504,7 +1512,16 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
         apply(lin + quad<Q_XOR1>(lin), ang + quad<Q_XOR1>(ang));
       };
       sums();
-      for (int it = 0; it < p.iters; ++it) {
+      // two per trip: the new impulses of one are the next one's old ones
+      // without copies
+      int it = 0;
+      for (; it + 1 < p.iters; it += 2) {
+        table_update();
+        sums();
+        table_update();
+        sums();
+      }
+      if (it < p.iters) {
         table_update();
         sums();
       }
@@ -1605,8 +1622,9 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
           } else {
             // an absent contact of the table with itself: zero impulses
             const f3 z = mk(0, 0, 0);
-            qc = QuadContact{4 * PLANE, 4 * PLANE, z, z, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+            qc = QuadContact{4 * PLANE, 4 * PLANE, z, z, 0, 0, 0, 0, 0, 0, 0, 0, 0};
           }
+          qc.lo = __builtin_canonicalizef(qc.lo);   // here once, not in every iteration's maximum
         }
         wave_sync();
         float* const rows = reinterpret_cast<float*>(&s.u.imp[0][0]) + lane;
@@ -1633,7 +1651,7 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
           float l = fmaxf(qc.lam + qc.k * (qc.vs - dot(U, qc.dir)), qc.lo);
           const float ln = quad<0x00>(l), lt1 = quad<0x55>(l), lt2 = quad<0xaa>(l);
           const float lim = qc.mu * ln, mag2 = lt1 * lt1 + lt2 * lt2;
-          l *= fmaxf(fminf(lim * rsq(mag2), 1.0f), qc.hi);
+          l *= fminf(lim * rsq(mag2), 1.0f);
           const float dl = l - qc.lam;
           qc.lam = l;
           put_rows(dl);
@@ -1646,82 +1664,86 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
           s.wl[q][c] = qc.lam;
         }
       } else {
-        Contact ct[K];
+        // the first RS slots' contacts in registers; the others, which only
+        // towers and piles reach, in a lane's private memory, so that they
+        // cost no environment registers
+        constexpr int RS = NB == 16 ? 1 : 2;
+        Contact ct[RS], more[K > RS ? K - RS : 1];
+        auto each_slot = [&](auto f) {
 #pragma unroll
-        for (int sl = 0; sl < K; ++sl) {
-          const int c = 64 * sl + lane;
-          if (64 * sl < n_rows) {
-            if (c < n_rows) {
-              prep_contact(s, c, p, &ct[sl]);
-              const f3 l = warm_impulse(s, c, nwarm, n_extra);
-              ct[sl].ln = l.x;
-              ct[sl].lt1 = l.y;
-              ct[sl].lt2 = l.z;
-            } else {
-              const f3 z = mk(0, 0, 0);
-              ct[sl] = Contact{PLANE | (PLANE << 8), z, z, z, z, z, 0, 0, 0, 0, 0, 0, 0, 0};
-            }
+          for (int sl = 0; sl < RS; ++sl)
+            if (sl == 0 || 64 * sl < n_rows) f(64 * sl + lane, ct[sl]);
+          if constexpr (K > RS) {
+#pragma unroll 1
+            for (int sl = RS; 64 * sl < n_rows; ++sl) f(64 * sl + lane, more[sl - RS]);
           }
-        }
+        };
+        each_slot([&](int c, Contact& q) {
+          if (c < n_rows) {
+            prep_contact(s, c, p, &q);
+            const f3 l = warm_impulse(s, c, nwarm, n_extra);
+            q.ln = l.x;
+            q.lt1 = l.y;
+            q.lt2 = l.z;
+          } else {
+            const f3 z = mk(0, 0, 0);
+            q = Contact{PLANE | (PLANE << 8), z, z, z, z, z, 0, 0, 0, 0, 0, 0, 0, 0};
+          }
+        });
         wave_sync();
         auto put_rows = [&](int c, const Contact& q, f3 R) {
           st3(&s.u.imp[0][c], R);
           st3(&s.u.imp[1][c], cross(q.ra, R));
           st3(&s.u.imp[2][c], cross(q.rb, R));
         };
-#pragma unroll
-        for (int sl = 0; sl < K; ++sl)
-          if (64 * sl < n_rows) {
-            const Contact& q = ct[sl];
-            put_rows(64 * sl + lane, q, fma3(q.n, q.ln, fma3(q.t1, q.lt1, q.t2 * q.lt2)));
-          }
+        each_slot([&](int c, Contact& q) { put_rows(c, q, fma3(q.n, q.ln, fma3(q.t1, q.lt1, q.t2 * q.lt2))); });
         wave_sync();
         sums();
         for (int it = 0; it < p.iters; ++it) {
           publish();
-#pragma unroll
-          for (int sl = 0; sl < K; ++sl)
-            if (sl == 0 || 64 * sl < n_rows) {
-              Contact& q = ct[sl];
-              const int a = q.ab & 255, bb = (q.ab >> 8) & 255;
-              const f3 va = xyz(s.vel[a]), ta = xyz(s.ang[a]), vb = xyz(s.vel[bb]), tb = xyz(s.ang[bb]);
-              const f3 wa = mk(ta.z, ta.x, ta.y), wb = mk(tb.z, tb.x, tb.y);
-              if (sl == 0) table_update();
-              const f3 u = cross_add(wb, q.rb, vb) - cross_add(wa, q.ra, va);
-              const float ln = fmaxf(q.ln + q.kn * (q.vstar - dot(u, q.n)), 0.0f);
-              const float dln = ln - q.ln;
-              q.ln = ln;
-              float lt1 = q.lt1 - q.kt1 * dot(u, q.t1);
-              float lt2 = q.lt2 - q.kt2 * dot(u, q.t2);
-              const float lim = q.mu * ln, mag2 = lt1 * lt1 + lt2 * lt2;
-              const float sc = fminf(lim * rsq(mag2), 1.0f);
-              lt1 *= sc;
-              lt2 *= sc;
-              const float dl1 = lt1 - q.lt1, dl2 = lt2 - q.lt2;
-              q.lt1 = lt1;
-              q.lt2 = lt2;
-              put_rows(64 * sl + lane, q, fma3(q.n, dln, fma3(q.t1, dl1, q.t2 * dl2)));
-            }
+          table_update();
+          each_slot([&](int c, Contact& q) {
+            const int a = q.ab & 255, bb = (q.ab >> 8) & 255;
+            const f3 va = xyz(s.vel[a]), ta = xyz(s.ang[a]), vb = xyz(s.vel[bb]), tb = xyz(s.ang[bb]);
+            const f3 wa = mk(ta.z, ta.x, ta.y), wb = mk(tb.z, tb.x, tb.y);
+            const f3 u = cross_add(wb, q.rb, vb) - cross_add(wa, q.ra, va);
+            const float ln = fmaxf(q.ln + q.kn * (q.vstar - dot(u, q.n)), 0.0f);
+            const float dln = ln - q.ln;
+            q.ln = ln;
+            float lt1 = q.lt1 - q.kt1 * dot(u, q.t1);
+            float lt2 = q.lt2 - q.kt2 * dot(u, q.t2);
+            const float lim = q.mu * ln, mag2 = lt1 * lt1 + lt2 * lt2;
+            const float sc = fminf(lim * rsq(mag2), 1.0f);
+            lt1 *= sc;
+            lt2 *= sc;
+            const float dl1 = lt1 - q.lt1, dl2 = lt2 - q.lt2;
+            q.lt1 = lt1;
+            q.lt2 = lt2;
+            put_rows(c, q, fma3(q.n, dln, fma3(q.t1, dl1, q.t2 * dl2)));
+          });
           wave_sync();   // the impulse rows
           sums();
         }
-#pragma unroll
-        for (int sl = 0; sl < K; ++sl) {
-          const int c = 64 * sl + lane;
-          if (64 * sl < n_rows && c < n_rows) {
-            s.wkey[c] = contact_key<S>(ct[sl].ab);
-            s.wl[0][c] = ct[sl].ln;
-            s.wl[1][c] = ct[sl].lt1;
-            s.wl[2][c] = ct[sl].lt2;
+        each_slot([&](int c, Contact& q) {
+          if (c < n_rows) {
+            s.wkey[c] = contact_key<S>(q.ab);
+            s.wl[0][c] = q.ln;
+            s.wl[1][c] = q.lt1;
+            s.wl[2][c] = q.lt2;
           }
-        }
+        });
       }
     }
     nwarm = n_rows;
 
     // ---- 8. position stage
-    x = fma3(v, dt, x);
+    x = fma3(v, dt, xyz(s.pos[bl]));
     {
+      const float4 q = s.quat[bl];
+      q0 = q.x;
+      q1 = q.y;
+      q2 = q.z;
+      q3 = q.w;
       float dw = -(w.x * q1 + w.y * q2 + w.z * q3);
       float dx = q0 * w.x + (w.y * q3 - w.z * q2);
       float dy = q0 * w.y + (w.z * q1 - w.x * q3);

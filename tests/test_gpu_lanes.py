@@ -110,12 +110,12 @@ def test_body_lane_layouts_agree(pm, n):
         assert np.array_equal(two[0][:3 * n], want[0]) and np.array_equal(two[2][:3], want[2]), waves
 
 
-@pytest.mark.parametrize("n", [2, 5, 6, 17, 18])
+@pytest.mark.parametrize("n", [2, 5, 6, 17, 18, 31])
 def test_row_contact_forms_match_oracle(pm, n):
     """A tower of n cubes has four contacts between neighbours: 16 rows at
-    five cubes are the last in quads of lanes, 17 and more are one per lane,
-    65 and more (18 cubes) two.  One substep against the oracle under the bars
-    of the other one-substep tests."""
+    five cubes are the last in quads of lanes, more are one per lane, 65 and
+    more (18 cubes) two.  One substep against the oracle under the bars of
+    the other one-substep tests."""
     st, bd = np.zeros((n, 13)), np.zeros((n, 5))
     for i in range(n):
         st[i] = [0.0005 * (i % 3), -0.0004 * (i % 2), 0.02 + 0.0399 * i, 1, 0, 0, 0, 0.01 * (i % 2), 0, 0, 0, 0, 0]
@@ -126,3 +126,28 @@ def test_row_contact_forms_match_oracle(pm, n):
     assert status[0] == 0 and stats[0, 0] == 4 * n
     assert np.abs(g[:, :7] - o[:, :7]).max() <= 1e-5
     assert np.abs(g[:, 7:] - o[:, 7:]).max() <= 1e-4
+
+
+@pytest.mark.parametrize("waves", [1, 2])
+@pytest.mark.parametrize("n", [10, 18])
+def test_more_than_64_rows(pm, n, waves):
+    """Two towers 1.5 mm apart: 84 rows with 10 cubes (in the 16-box layout the
+    second slot is in private memory), 164 with 18 (256- and 512-contact
+    classes: a third slot).  Against the oracle over one substep, and the
+    classes against each other."""
+    st, bd = np.zeros((n, 13)), np.zeros((n, 5))
+    for i in range(n):
+        st[i] = [0.0415 * (i % 2), 0, 0.02 + 0.0399 * (i // 2), 1, 0, 0, 0, 0.01 * (i % 3), 0, 0, 0, 0, 0]
+        bd[i] = [0.02, 0.02, 0.02, 0.1, 0.5]
+    st, bd = f32(st), f32(bd)
+    contacts = 128 if n == 10 else 256
+    got = stepped(pm, [0, n], st, bd, FAR, 1, waves, contacts)
+    cfg = O.make_config(max_contacts=contacts)
+    o, _, _ = O.step(cfg, np.array([0, n], np.int32), st, bd, f32([FAR]), 1)
+    rows = len(O.collide(cfg, st, bd, f32(FAR))[0]) - 8
+    assert rows > (64 if n == 10 else 128)
+    assert got[1][0] == 0 and got[2][0, 0] == 8 + rows
+    assert np.abs(got[0][:, :7] - o[:, :7]).max() <= 1e-5
+    assert np.abs(got[0][:, 7:] - o[:, 7:]).max() <= 1e-4
+    other = stepped(pm, [0, n], st, bd, FAR, 1, waves, 512)
+    assert all(np.array_equal(a, b) for a, b in zip(got, other))
