@@ -121,8 +121,7 @@ hipError_t launch_step(const StepArgs& a, int max_contacts, hipStream_t stream, 
 // counter (the caller clears it, e.g. with launch_zero)
 hipError_t launch_step_class(const StepArgs& a, int max_contacts, hipStream_t stream, int grid, int waves, int max_nb);
 // cost pass: one block per env writes a.cost_key[e], the env's work
-// estimate (contacts + candidate pairs at the start pose, + 3 for a valid
-// push); order: each XCD's contiguous run of envs by descending estimate
+// estimate from its start pose; order: each XCD's contiguous run of envs by descending estimate
 // into order[0, n), and the eight queue counters queue[0..7] cleared
 hipError_t launch_cost(const StepArgs& a, int max_contacts, hipStream_t stream, int waves, int max_nb);
 hipError_t launch_order(const int* key, int n, int* order, int* queue, hipStream_t stream);
