@@ -510,7 +510,8 @@ struct QuadContact {
   int at_a, at_b;             // bodies a and b: offset of their velocity's component q
   f3 dir, comp;               // frame row q; component q of the three rows
   float ra1, ra2, rb1, rb2;   // components q + 1 and q + 2 of the lever arms
-  float k, vs, mu, lam, lo;
+  float k, vs, mu, lam;
+  int lo;                     // least impulse as an integer (negative floats are negative integers)
 };
 
 // Components q, q + 1 and q + 2 (cyclic) of a vector.
@@ -538,7 +539,7 @@ __device__ __forceinline__ void prep_quad(const S& s, int c, int q, const Params
   ct->vs = normal ? vstar : 0.0f;
   // the normal impulse is clamped from below and not scaled by the friction
   // disc: an infinite limit scales by 1, also where it gives a nan
-  ct->lo = normal ? 0.0f : -INFINITY;
+  ct->lo = normal ? 0 : INT32_MIN;
   ct->dir = d;
   ct->comp = mk(turn(n, q).x, turn(t1, q).x, turn(t2, q).x);
   const f3 ta = turn(ra, q), tb = turn(rb, q);
@@ -1502,25 +1503,38 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
         *ang = cross(tc[0].rb, P[0]) + cross(tc[TS - 1].rb, P[TS - 1]);
       }
     };
-    auto table_update = [&]() {
+    // an update in two halves: the new impulses up to the friction disc's
+    // root, and the rest
+    float t_ln[TS], t_lt1[TS], t_lt2[TS], t_root[TS];
+    auto table_begin = [&]() {
+#pragma unroll
+      for (int ts = 0; ts < TS; ++ts) {
+        const TableContact& q = tc[ts];
+        const f3 u = cross_add(w, q.rb, v);
+        t_ln[ts] = fmaxf(q.ln + q.kn * (q.vstar - u.z), 0.0f);
+        t_lt1[ts] = q.lt1 + q.kt1 * u.y;
+        t_lt2[ts] = q.lt2 - q.kt2 * u.x;
+        t_root[ts] = rsq(t_lt1[ts] * t_lt1[ts] + t_lt2[ts] * t_lt2[ts]);
+      }
+    };
+    auto table_end = [&]() {
 #pragma unroll
       for (int ts = 0; ts < TS; ++ts) {
         TableContact& q = tc[ts];
-        const f3 u = cross_add(w, q.rb, v);
-        const float ln = fmaxf(q.ln + q.kn * (q.vstar - u.z), 0.0f);
-        float lt1 = q.lt1 + q.kt1 * u.y;
-        float lt2 = q.lt2 - q.kt2 * u.x;
         // onto the friction disc: scale by min(1, lim / |lt|) (a zero
         // tangential impulse gives inf or nan, and the min keeps 1)
-        const float lim = mu_table * ln, mag2 = lt1 * lt1 + lt2 * lt2;
-        const float sc = fminf(lim * rsq(mag2), 1.0f);
-        lt1 *= sc;
-        lt2 *= sc;
-        P[ts] = mk(lt2 - q.lt2, q.lt1 - lt1, ln - q.ln);
-        q.ln = ln;
+        const float lim = mu_table * t_ln[ts];
+        const float sc = fminf(lim * t_root[ts], 1.0f);
+        const float lt1 = t_lt1[ts] * sc, lt2 = t_lt2[ts] * sc;
+        P[ts] = mk(lt2 - q.lt2, q.lt1 - lt1, t_ln[ts] - q.ln);
+        q.ln = t_ln[ts];
         q.lt1 = lt1;
         q.lt2 = lt2;
       }
+    };
+    auto table_update = [&]() {
+      table_begin();
+      table_end();
     };
 #pragma unroll
     for (int ts = 0; ts < TS; ++ts) P[ts] = mk(tc[ts].lt2, -tc[ts].lt1, tc[ts].ln);
@@ -1644,7 +1658,6 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
             const f3 z = mk(0, 0, 0);
             qc = QuadContact{4 * PLANE, 4 * PLANE, z, z, 0, 0, 0, 0, 0, 0, 0, 0, 0};
           }
-          qc.lo = __builtin_canonicalizef(qc.lo);   // here once, not in every iteration's maximum
         }
         wave_sync();
         float* const rows = reinterpret_cast<float*>(&s.u.imp[0][0]) + lane;
@@ -1665,10 +1678,12 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
           const float va = vel[qc.at_a], wa1 = ang[qc.at_a], wa2 = ang[qc.at_a + 1];
           const float vb = vel[qc.at_b], wb1 = ang[qc.at_b], wb2 = ang[qc.at_b + 1];
           __builtin_amdgcn_sched_barrier(0);
-          table_update();   // while the loads are in flight
+          table_begin();   // while the loads are in flight
+          __builtin_amdgcn_sched_barrier(0);
+          table_end();     // between the steps of the rows' chain
           const float u = fmaf(wb1, qc.rb2, fmaf(-wb2, qc.rb1, vb)) - fmaf(wa1, qc.ra2, fmaf(-wa2, qc.ra1, va));
           const f3 U = mk(quad<0x00>(u), quad<0x55>(u), quad<0xaa>(u));
-          float l = fmaxf(qc.lam + qc.k * (qc.vs - dot(U, qc.dir)), qc.lo);
+          float l = __int_as_float(max(__float_as_int(qc.lam + qc.k * (qc.vs - dot(U, qc.dir))), qc.lo));
           const float ln = quad<0x00>(l), lt1 = quad<0x55>(l), lt2 = quad<0xaa>(l);
           const float lim = qc.mu * ln, mag2 = lt1 * lt1 + lt2 * lt2;
           l *= fminf(lim * rsq(mag2), 1.0f);
