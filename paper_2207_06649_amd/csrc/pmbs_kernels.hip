@@ -29,7 +29,7 @@
 namespace pmbs {
 
 constexpr int MAXB = 32;             // boxes (<= 31) + the pusher
-constexpr int CLIP_GROUPS = 8;       // pairs per narrowphase pass (8-lane groups)
+constexpr int GROUPS = 4;            // pairs per narrowphase pass (16-lane groups)
 constexpr int POLY = 8;              // clip polygon capacity
 
 // ------------------------------------------------------------------ vectors
@@ -135,7 +135,8 @@ struct Smem {
   // (1 = b), in contact-index order.
   unsigned short inc[2 * C];
   int lstart[MB];                    // incidence list starts
-  unsigned short pairs[MAX_PAIRS];
+  unsigned short pairs[MAX_PAIRS];   // candidate pairs (one wave: then the live ones)
+  unsigned short list[W > 1 ? W : 1][W > 1 ? MAX_PAIRS : 1];   // two waves: each its copy of the live pairs
   int cab[C];                        // packed a | b << 8 | feature << 16 of each row contact
   int wkey[C];                       // previous substep's row-contact keys (sorted)
   float wl[3][C];                    // and their accumulated impulses (n, t1, t2)
@@ -146,16 +147,10 @@ struct Smem {
         struct {
           float4 lo[MB], hi[MB];     // AABBs: min and max corner (x, y, z, -)
         } box;
-        // each wave's own narrowphase scratch (no wave writes another's):
-        // first the axis candidates of its eight groups (separation value and
-        // unit axis, x, y, z rows), then their clip polygons
-        union alignas(16) {
-          struct {
-            float v[CLIP_GROUPS][16];
-            float ax[3][CLIP_GROUPS][16];
-          } cand;
-          float clip[2][POLY][3][CLIP_GROUPS];
-        } wave[W];
+        struct {
+          unsigned char live[MAX_PAIRS];     // candidate pairs that no face axis separates
+          float clip[W][2][POLY][3][GROUPS]; // each wave's clip polygons
+        } np;
         unsigned incm[NOBJ][2 * K];  // incidence build: contact bit masks per body
         float4 lam[MB * 4];          // table impulses (n, t1, t2) and corner mask of a changed corner set
       } x;
@@ -323,17 +318,25 @@ constexpr int Q_LOW = 0x44, Q_HIGH = 0xee;    // lanes 0, 1, 0, 1 and 2, 3, 2, 3
 // the clip buffers of wave wid
 template <class S>
 __device__ __forceinline__ f3 cl_get(const S& s, int wid, int buf, int i, int grp) {
-  return mk(s.u.n.x.wave[wid].clip[buf][i][0][grp], s.u.n.x.wave[wid].clip[buf][i][1][grp], s.u.n.x.wave[wid].clip[buf][i][2][grp]);
+  const auto& c = s.u.n.x.np.clip[wid][buf][i];
+  return mk(c[0][grp], c[1][grp], c[2][grp]);
 }
 template <class S>
 __device__ __forceinline__ void cl_put(S& s, int wid, int buf, int i, int grp, f3 v) {
-  s.u.n.x.wave[wid].clip[buf][i][0][grp] = v.x;
-  s.u.n.x.wave[wid].clip[buf][i][1][grp] = v.y;
-  s.u.n.x.wave[wid].clip[buf][i][2][grp] = v.z;
+  auto& c = s.u.n.x.np.clip[wid][buf][i];
+  c[0][grp] = v.x;
+  c[1][grp] = v.y;
+  c[2][grp] = v.z;
 }
 
-// Previous lane of each 8-lane group, lane 0 of a group taking lane 7: DPP
-// row_shr:1 and row_ror:9 within the 16-lane rows.
+// Value of lane K of each 16-lane row (DPP row broadcast).
+template <int K>
+__device__ __forceinline__ float row_value(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x150 + K, 0xf, 0xf, true));
+}
+
+// Previous of the first eight lanes of each 16-lane row, lane 0 taking lane 7:
+// DPP row_shr:1 and row_ror:9.
 __device__ __forceinline__ float group_prev(float v, bool first) {
   const int iv = __float_as_int(v);
   const int down = __builtin_amdgcn_mov_dpp(iv, 0x111, 0xf, 0xf, false);
@@ -342,8 +345,9 @@ __device__ __forceinline__ float group_prev(float v, bool first) {
 }
 
 // One Sutherland-Hodgman stage against sign * ((x - f).dir) - h <= 0 for
-// the polygons of all eight groups at once, point i of a group's polygon
-// in lane i of the group (lanes past the last point hold copies of it).
+// the polygons of all four groups at once, point i of a group's polygon
+// in lane i of the group (lanes past the last point hold copies of it, lanes
+// 8-15 no point).
 // Lane i handles the edge from point i-1 (the last point for i = 0) to
 // point i: it emits the crossing point if the edge crosses the plane, then
 // point i if inside, at its rank among the group's emissions; at most POLY
@@ -364,7 +368,7 @@ __device__ __forceinline__ int clip_group(S& s, f3* P, int n, f3 f, f3 dir, floa
   const bool in_c = dc <= 0.0f, in_p = dp <= 0.0f;
   const bool emit_x = live && (in_c != in_p), emit_c = live && in_c;
   const unsigned long long mx = __ballot(emit_x), mc = __ballot(emit_c);
-  const unsigned long long gm = 0xffull << (8 * grp), below = ((1ull << lane) - 1ull) & gm;
+  const unsigned long long gm = 0xffffull << (16 * grp), below = ((1ull << lane) - 1ull) & gm;
   const int q = __popcll(mx & below) + __popcll(mc & below);
   const int m = __popcll(mx & gm) + __popcll(mc & gm);
   if (emit_x && q < POLY) cl_put(s, wid, buf, q, grp, fma3(*P - Pp, dp * rcp(dp - dc), Pp));
@@ -760,7 +764,7 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
   const int lane = opaque(threadIdx.x & 63);
   const int wid = W > 1 ? (int)(threadIdx.x >> 6) : 0;
   const bool lead = wid == 0;
-  const int b = lane / L, j = lane % L;
+  const int b = (unsigned)lane / L, j = (unsigned)lane % L;
   const int base = g.env_offset[e];
   const int nb = g.env_offset[e + 1] - base;
   const bool active = lead && b < nb;  // a lane of the lead wave that owns a body
@@ -934,13 +938,12 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
   }
   int n_inc = 0, inc0 = 0;   // the lane's body's list of row contacts: length and start
   for (int k = 0; k < n_sub; ++k) {
-    const int lane = opaque(threadIdx.x & 63), b = lane / L, j = lane % L;
+    const int lane = opaque(threadIdx.x & 63), b = (unsigned)lane / L, j = (unsigned)lane % L;
     const bool active = lead && b < nb, first = active && j == 0;
     // ---- 1. velocity stage
     v.z -= p.gravity * dt;
     const float vs = (valid && k < n_move) ? p.push_speed : 0.0f;
-    f3 vp = pdir * vs;
-    if (g.collide_only) vp = mk(0, 0, 0);
+    const f3 vp = pdir * vs;
 
     // ---- 2. frames and AABBs.  Half extents, and after the narrowphase
     // centre, rotation and orientation, are read back from LDS: held in
@@ -968,20 +971,45 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
     // ones listed by ballot
     int n_pairs = 0;
     if (W == 1 || wid == 1) {
+      struct Two {
+        unsigned ii, jj;
+        f3 il, ih, jl, jh;
+      };
+      auto load = [&](int k2) {
+        const unsigned ij = (unsigned)opaque((int)tri[k2 / 3]) >> (10 * (k2 % 3));
+        Two t;
+        t.ii = ij & 31u;
+        t.jj = (ij >> 5) & 31u;
+        t.il = xyz(s.u.n.x.box.lo[t.ii]);
+        t.ih = xyz(s.u.n.x.box.hi[t.ii]);
+        t.jl = xyz(s.u.n.x.box.lo[t.jj]);
+        t.jh = xyz(s.u.n.x.box.hi[t.jj]);
+        return t;
+      };
+      auto test = [&](const Two& t) {
+        // one compare per ballot, joined in scalar registers
+        const unsigned long long hm = __ballot(t.ii < t.jj) & __ballot(t.il.x <= t.jh.x) & __ballot(t.jl.x <= t.ih.x) &
+                                      __ballot(t.il.y <= t.jh.y) & __ballot(t.jl.y <= t.ih.y) &
+                                      __ballot(t.il.z <= t.jh.z) & __ballot(t.jl.z <= t.ih.z);
+        // rank among the lower lanes' hits (mbcnt)
+        const int rk = __builtin_amdgcn_mbcnt_hi((unsigned)(hm >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)hm, 0u));
+        if (__builtin_amdgcn_inverse_ballot_w64(hm)) s.pairs[n_pairs + rk] = (unsigned short)((t.ii << 8) | t.jj);
+        n_pairs += __popcll(hm);
+      };
+      // two passes' corners in flight together (past the last pair a lane has
+      // the pair (0, 0), which is none)
 #pragma unroll
-      for (int k2 = 0; k2 < PASSES; ++k2) {
+      for (int k2 = 0; k2 < PASSES; k2 += 2) {
         if (64 * k2 < n_tri) {
-          const unsigned ij = (unsigned)opaque((int)tri[k2 / 3]) >> (10 * (k2 % 3));
-          const unsigned ii = ij & 31u, jj = (ij >> 5) & 31u;
-          const f3 il = xyz(s.u.n.x.box.lo[ii]), ih = xyz(s.u.n.x.box.hi[ii]);
-          const f3 jl = xyz(s.u.n.x.box.lo[jj]), jh = xyz(s.u.n.x.box.hi[jj]);
-          const bool hit = (ii < jj) & (il.x <= jh.x) & (jl.x <= ih.x) & (il.y <= jh.y) & (jl.y <= ih.y) &
-                           (il.z <= jh.z) & (jl.z <= ih.z);
-          const unsigned long long hm = __ballot(hit);
-          // rank among the lower lanes' hits (mbcnt)
-          const int rk = __builtin_amdgcn_mbcnt_hi((unsigned)(hm >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)hm, 0u));
-          if (hit) s.pairs[n_pairs + rk] = (unsigned short)((ii << 8) | jj);
-          n_pairs += __popcll(hm);
+          const Two t0 = load(k2);
+          if (k2 + 1 < PASSES && 64 * (k2 + 1) < n_tri) {
+            const Two t1 = load(k2 + 1 < PASSES ? k2 + 1 : k2);
+            __builtin_amdgcn_sched_barrier(0);
+            test(t0);
+            test(t1);
+          } else {
+            test(t0);
+          }
         }
       }
     }
@@ -1057,79 +1085,81 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
     int n_rows = n_extra;
 
     // ---- 4b. box-box and pusher-box contacts, pairs in lexicographic order.
-    // Eight pairs per pass, one 8-lane group each: lane k of a group
-    // evaluates candidate axes k and k + 8, the group scans the candidates in
-    // order (row broadcasts), and the incident face is clipped with one
-    // polygon point per lane.  With W waves a round is W passes, wave w
-    // taking pairs r0 + 8 w ..; the round's contacts keep the pass order.
-    for (int r0 = 0; r0 < n_pairs; r0 += 8 * W) {
+    // More than four candidate pairs are sieved first, eight per pass on eight
+    // lanes each: a pair separated along a face axis by more than the margin
+    // has no contact whatever the other axes give (at the headline 92 % of
+    // them; face gl of A, gl - 3 of B).  The live ones are listed in order.
+    int n_live = n_pairs;
+    const unsigned short* live_list = s.pairs;
+    if (n_pairs > GROUPS) {
       // opaque: the lane's addresses and selects are formed here, not kept in
       // registers over the whole push
-      const int ln = opaque(lane);
-      const int grp = ln >> 3, gl = ln & 7;
-      const int pi = r0 + 8 * wid + grp;
-      const bool has = pi < n_pairs;
-      int ia = 0, ib = 1;
-      if (has) {
-        const unsigned pr = s.pairs[pi];
-        ia = pr >> 8;
-        ib = pr & 255;
+      const int ln = opaque(lane), grp = ln >> 3, gl = ln & 7;
+      for (int r0 = 8 * wid; r0 < n_pairs; r0 += 8 * W) {
+        const int pi = r0 + grp;
+        const bool has = pi < n_pairs;
+        const unsigned pr = has ? s.pairs[pi] : 0u;
+        const int ia = pr >> 8, ib = pr & 255;
+        const Box A = load_box(s, ia), B = load_box(s, ib);
+        const f3 d = B.c - A.c;
+        const f3 L = lds_axis(s, gl < 3 ? ia : ib, gl < 3 ? gl : (gl < 6 ? gl - 3 : gl - 6));
+        const float sv = fabsf(dot(d, L)) - radius_along(A, L) - radius_along(B, L);
+        const unsigned long long apart = __ballot(sv > p.margin) & (0xffull << (8 * grp));
+        if (has && gl == 0) s.u.n.x.np.live[pi] = apart == 0ull ? 1 : 0;
       }
-      const Box A = load_box(s, ia), B = load_box(s, ib);
-      const f3 d = B.c - A.c;
-      const unsigned long long gm = 0xffull << (8 * grp);
-      // the six face axes first (candidate gl < 6: face gl of A, gl - 3 of
-      // B; lanes 6-7 repeat two of B's here and take edge crosses below).
-      // A pair separated along a face axis by more than the margin has no
-      // contact whatever the other axes give, and a pass whose pairs are all
-      // such skips the edge axes, the axis scan and clipping.
-      const f3 Lf = lds_axis(s, gl < 3 ? ia : ib, gl < 3 ? gl : (gl < 6 ? gl - 3 : gl - 6));
-      const float svf = fabsf(dot(d, Lf)) - radius_along(A, Lf) - radius_along(B, Lf);
-      const bool live = has && (__ballot(gl < 6 && svf > p.margin) & gm) == 0ull;
+      sync_all<W>();
+      // one wave lists them in place (a place is read before it is written),
+      // two each in a list of its own
+      unsigned short* const out = W > 1 ? s.list[wid] : s.pairs;
+      n_live = 0;
+      for (int p0 = 0; p0 < n_pairs; p0 += 64) {
+        const int pi = p0 + ln;
+        const bool hit = pi < n_pairs && s.u.n.x.np.live[pi] != 0;
+        const unsigned short pr = pi < n_pairs ? s.pairs[pi] : 0;
+        const unsigned long long hm = __ballot(hit);
+        const int rk = __builtin_amdgcn_mbcnt_hi((unsigned)(hm >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)hm, 0u));
+        if (hit) out[n_live + rk] = pr;
+        n_live += __popcll(hm);
+      }
+      live_list = out;
+      wave_sync();
+    }
+    // Four pairs per pass, 16 lanes each: lane k evaluates candidate axis k
+    // (0-2 faces of A, 3-5 faces of B, 6-14 edge crosses A_i x B_j), one
+    // evaluation for all fifteen.  Bound by the pass's chain of LDS round
+    // trips and dependent instructions.  With W waves a round is W passes,
+    // wave w taking pairs r0 + 4 w ..; the round's contacts keep the order.
+    for (int r0 = 0; r0 < n_live; r0 += GROUPS * W) {
+      const int ln = opaque(lane);
+      const int grp = ln >> 4, gl = ln & 15;
+      const int pi = r0 + GROUPS * wid + grp;
+      const bool has = pi < n_live;
+      const unsigned pr = has ? live_list[pi] : 0u;
+      const int ia = pr >> 8, ib = pr & 255;
+      const unsigned long long gm = 0xffffull << (16 * grp);
       bool keep = false, face = false;
       f3 P = mk(0, 0, 0), nref = mk(0, 0, 1), n = mk(0, 0, 0);
       float psep = 0.0f, bs = 0.0f;
       int best = -1;
-      if (__ballot(live) != 0ull) {
-        // candidate gl: 0-2 faces of A, 3-5 faces of B, 6-7 edge crosses A0 x B0, A0 x B1
-        f3 L0 = Lf;
-        float sv0 = svf;
-        bool ok0 = has;
-        if (gl >= 6) {
-          const f3 v = cross(A.a0, axis(B, gl - 6));
-          const float l2 = dot(v, v);
-          ok0 = ok0 && l2 >= p.edge_eps * p.edge_eps;
-          L0 = v * rsq(l2);
-          sv0 = fabsf(dot(d, L0)) - radius_along(A, L0) - radius_along(B, L0);
-        }
-        // candidate gl + 8: edge crosses 8-14 (gl = 7 has none)
-        const int e1 = gl + 2;  // index of the edge pair (i, j) = (e1 / 3, e1 % 3)
-        const f3 v1 = cross(axis(A, e1 / 3), axis(B, e1 % 3));
-        const float l21 = dot(v1, v1);
-        const bool ok1 = has && gl < 7 && l21 >= p.edge_eps * p.edge_eps;
-        const f3 L1 = v1 * rsq(l21);
-        const float sv1 = fabsf(dot(d, L1)) - radius_along(A, L1) - radius_along(B, L1);
-        const bool out = (__ballot((ok0 && sv0 > p.margin) || (ok1 && sv1 > p.margin)) & gm) != 0ull;
-        // the contact axis: the group's candidates (separation value and unit
-        // axis) go to LDS at their candidate index (k < 8: lane k's first,
-        // k >= 8: lane k - 8's second; an invalid one holds -inf), and every lane of the
-        // group scans the fifteen in order: the kept axis starts at candidate
-        // 0 (a face of A, valid whenever the pair is) and is replaced only by
-        // a later one that exceeds it by tau_face (faces) or tau_edge (edges)
-        auto& cd = s.u.n.x.wave[wid].cand;
-        float* const cv = &cd.v[grp][0];
-        cv[gl] = ok0 ? sv0 : -INFINITY;
-        cv[gl + 8] = ok1 ? sv1 : -INFINITY;
-        cd.ax[0][grp][gl] = L0.x;
-        cd.ax[1][grp][gl] = L0.y;
-        cd.ax[2][grp][gl] = L0.z;
-        cd.ax[0][grp][gl + 8] = L1.x;
-        cd.ax[1][grp][gl + 8] = L1.y;
-        cd.ax[2][grp][gl + 8] = L1.z;
-        wave_sync();
-        const float4 c0 = reinterpret_cast<const float4*>(cv)[0], c1 = reinterpret_cast<const float4*>(cv)[1];
-        const float4 c2 = reinterpret_cast<const float4*>(cv)[2], c3 = reinterpret_cast<const float4*>(cv)[3];
-        bs = c0.x;
+      {
+        const Box A = load_box(s, ia), B = load_box(s, ib);
+        const f3 d = B.c - A.c;
+        // axes i of A and j of B by lane, two bits each: i 0 1 2 - - - 0 0 0 1
+        // 1 1 2 2 2 -, j - - - 0 1 2 0 1 2 0 1 2 0 1 2 -
+        const f3 ua = lds_axis(s, ia, (0x2a540024u >> (2 * gl)) & 3u);
+        const f3 ub = lds_axis(s, ib, (0x24924900u >> (2 * gl)) & 3u);
+        const f3 v = cross(ua, ub);
+        const float l2 = dot(v, v);
+        const bool edge = gl >= 6 && gl < 15 && l2 >= p.edge_eps * p.edge_eps;
+        const f3 L = sel(gl < 3, ua, sel(gl < 6, ub, v * rsq(l2)));
+        const float sv = fabsf(dot(d, L)) - radius_along(A, L) - radius_along(B, L);
+        const bool ok = gl < 6 || edge;
+        const bool out = (__ballot(ok && sv > p.margin) & gm) != 0ull;
+        // the contact axis: the candidates in order, the kept one replaced
+        // only by a later one that exceeds it by tau_face (faces) or tau_edge
+        // (edges); the edges are gone through only when one exceeds the
+        // faces' choice
+        bs = row_value<0>(sv);
         best = 0;
         auto scan = [&](float sk, int k, float tau) {
           if (sk > bs + tau) {
@@ -1137,26 +1167,33 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
             best = k;
           }
         };
-        scan(c0.y, 1, p.tau_face);
-        scan(c0.z, 2, p.tau_face);
-        scan(c0.w, 3, p.tau_face);
-        scan(c1.x, 4, p.tau_face);
-        scan(c1.y, 5, p.tau_face);
-        scan(c1.z, 6, p.tau_edge);
-        scan(c1.w, 7, p.tau_edge);
-        scan(c2.x, 8, p.tau_edge);
-        scan(c2.y, 9, p.tau_edge);
-        scan(c2.z, 10, p.tau_edge);
-        scan(c2.w, 11, p.tau_edge);
-        scan(c3.x, 12, p.tau_edge);
-        scan(c3.y, 13, p.tau_edge);
-        scan(c3.z, 14, p.tau_edge);
-        if (!has || out) best = -1;
-        // every lane of the group takes the kept axis from LDS, pointing from A to B
-        if (best >= 0) {
-          const f3 Lb = mk(cd.ax[0][grp][best], cd.ax[1][grp][best], cd.ax[2][grp][best]);
-          n = sel(dot(d, Lb) >= 0.0f, Lb, neg(Lb));
+        scan(row_value<1>(sv), 1, p.tau_face);
+        scan(row_value<2>(sv), 2, p.tau_face);
+        scan(row_value<3>(sv), 3, p.tau_face);
+        scan(row_value<4>(sv), 4, p.tau_face);
+        scan(row_value<5>(sv), 5, p.tau_face);
+        if (__ballot(has && edge && sv > bs + p.tau_edge) != 0ull) {
+          const float se = edge ? sv : -INFINITY;
+          scan(row_value<6>(se), 6, p.tau_edge);
+          scan(row_value<7>(se), 7, p.tau_edge);
+          scan(row_value<8>(se), 8, p.tau_edge);
+          scan(row_value<9>(se), 9, p.tau_edge);
+          scan(row_value<10>(se), 10, p.tau_edge);
+          scan(row_value<11>(se), 11, p.tau_edge);
+          scan(row_value<12>(se), 12, p.tau_edge);
+          scan(row_value<13>(se), 13, p.tau_edge);
+          scan(row_value<14>(se), 14, p.tau_edge);
         }
+        // every lane of the group takes the kept axis from its lane, pointing from A to B
+        const int from = ((ln & 48) + best) << 2;
+        auto take = [&](float x) {
+          return __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(x)));
+        };
+        const f3 Lb = mk(take(L.x), take(L.y), take(L.z));
+        if (!has || out) best = -1;
+        else n = sel(dot(d, Lb) >= 0.0f, Lb, neg(Lb));
+      }
+      if (__ballot(best >= 0) != 0ull) {
         // face axis: reference face of the axis owner, incident face of the
         // other box (most anti-parallel, ties to +x, -x, +y, -y, +z, -z), its
         // four corners one per lane, clipped by the reference face's side
@@ -1197,7 +1234,7 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
           const f3 fc = ic + am * (sg * hm);
           const f3 ep = ap * hp, eq = aq * hq;
           // corner gl of the incident face: signs (+,+), (-,+), (-,-), (+,-) of
-          // its two half edges (lanes 4-7 repeat corner 3); a product with +-1
+          // its two half edges (the lanes from 4 on repeat corner 3); a product with +-1
           // is exact, so each sum rounds once as a plain sum or difference
           const float spp = (gl == 1 || gl == 2) ? -1.0f : 1.0f, sqq = gl >= 2 ? -1.0f : 1.0f;
           P = fc + (ep * spp + eq * sqq);
@@ -1216,7 +1253,7 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
       int before = 0, round_total = __popcll(km);
       if constexpr (W > 1) {
         // kept contacts of every wave's pass: the earlier passes come first
-        const int par = (r0 / (8 * W)) & 1;
+        const int par = (r0 / (GROUPS * W)) & 1;
         if (lane == 0) s.rcount[par][wid] = round_total;
         __syncthreads();
         round_total = 0;
@@ -1801,7 +1838,7 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
     write_body_frames(b, first);
     sync_all<W>();
     const int tg = g.target[e];
-    const int lane = opaque(threadIdx.x & 63), b = lane / L, j = lane % L;
+    const int lane = opaque(threadIdx.x & 63), b = (unsigned)lane / L, j = (unsigned)lane % L;
     const bool active = lead && b < nb;
     float d2 = INFINITY;
     if (b < nb && b != tg && tg >= 0 && tg < nb) {
