@@ -205,30 +205,37 @@ __device__ __forceinline__ float radius_along(const Box& b, f3 L) {
   return b.h.x * fabsf(dot(b.a0, L)) + b.h.y * fabsf(dot(b.a1, L)) + b.h.z * fabsf(dot(b.a2, L));
 }
 
-// Whether the separating-axis test keeps boxes A and B apart: the maximum
-// over the candidate axes (faces of A, faces of B, edge crosses with
-// |a x b| >= eps) of s(L) = |d.L| - r_A(L) - r_B(L) is > 0.  The face axes
-// come first and the edge axes are skipped once a face axis has s > 0 (the
-// maximum is then > 0 whatever they give), so the decision is that of the
-// full maximum.  Every start-pose test goes through this one function.
-__device__ __forceinline__ bool sat_clear(const Box& A, const Box& B, float eps) {
+// s(L) = |d.L| - r_A(L) - r_B(L) for a candidate axis L, d = B.c - A.c: the
+// boxes' gap along L.
+__device__ __forceinline__ float gap_along(const Box& A, const Box& B, f3 d, f3 L) {
+  return fabsf(dot(d, L)) - radius_along(A, L) - radius_along(B, L);
+}
+
+// Whether an edge axis (a x b with |a x b| >= eps) has s > 0.
+__device__ __forceinline__ bool edges_clear(const Box& A, const Box& B, float eps) {
   const f3 d = B.c - A.c;
   float best = -INFINITY;
-#pragma unroll
-  for (int idx = 0; idx < 6; ++idx) {
-    const f3 L = idx < 3 ? axis(A, idx) : axis(B, idx - 3);
-    best = fmaxf(best, fabsf(dot(d, L)) - radius_along(A, L) - radius_along(B, L));
-  }
-  if (best > 0.0f) return true;
 #pragma unroll 1
   for (int idx = 0; idx < 9; ++idx) {
     const f3 v = cross(axis(A, idx / 3), axis(B, idx % 3));
     const float len = sqrtf(dot(v, v));
     if (len < eps) continue;
-    const f3 L = v * (1.0f / len);
-    best = fmaxf(best, fabsf(dot(d, L)) - radius_along(A, L) - radius_along(B, L));
+    best = fmaxf(best, gap_along(A, B, d, v * (1.0f / len)));
   }
   return best > 0.0f;
+}
+
+// Whether the separating-axis test keeps boxes A and B apart: the maximum
+// of s(L) over the candidate axes (faces of A, faces of B, edge crosses with
+// |a x b| >= eps) is > 0, that is, any of them is.  The face axes come first
+// and the edge axes are skipped once a face axis has s > 0.  Every start-pose
+// test makes this decision from gap_along and edges_clear.
+__device__ __forceinline__ bool sat_clear(const Box& A, const Box& B, float eps) {
+  const f3 d = B.c - A.c;
+  float best = -INFINITY;
+#pragma unroll
+  for (int idx = 0; idx < 6; ++idx) best = fmaxf(best, gap_along(A, B, d, idx < 3 ? axis(A, idx) : axis(B, idx - 3)));
+  return best > 0.0f || edges_clear(A, B, eps);
 }
 
 // The contour push a = obj * n_dirs + dir (Sec. IV-B): direction dir of
@@ -282,31 +289,6 @@ __device__ __forceinline__ Box pusher_box(const PusherPose& q, const Params& p) 
   b.h = mk(p.phx, p.phy, p.phz);
   return b;
 }
-
-// Start-pose validity of every contour push of the env whose body frames
-// are in LDS (Sec. IV-B: pushes that cannot start because of a collision
-// are discarded): lane l takes actions l, l + 64, ...; an action is valid
-// when its pusher start pose clears every box.  Lane w < PMBS_VALID_WORDS
-// returns word w (bit a mod 32 of word a / 32 set when action a is valid);
-// the other lanes return 0.
-// The validity bits of actions a0 .. a0 + 63 (lane k tests action a0 + k)
-// as a 64-bit ballot: bit set when the pusher at the action's start pose is
-// clear of every box.
-template <class S>
-__device__ __forceinline__ unsigned long long validity_bits(const S& s, int nb, const Params& p, int a0, int lane) {
-  const int n_act = nb * p.n_dirs;
-  const int a = a0 + lane;
-  bool ok = false;
-  if (a < n_act) {
-    const int obj = a / p.n_dirs, dir = a - obj * p.n_dirs;
-    const Box P = pusher_box(pusher_pose(contour_start(s, obj, dir, p), p), p);
-    ok = true;
-    for (int j = 0; j < nb; ++j)
-      if (ok && !sat_clear(load_box(s, j), P, p.edge_eps)) ok = false;
-  }
-  return __ballot(ok);
-}
-
 
 // A DPP quad permutation of a value: lane i of each four takes lane
 // (CTRL >> 2 i) & 3 of them.
@@ -2201,23 +2183,53 @@ struct Frames {
   float4 half[MAXB];
 };
 
+// Start-pose validity of every contour push (Sec. IV-B: pushes that cannot
+// start because of a collision are discarded): bit a mod 32 of word a / 32 is
+// set when the pusher at action a's start pose clears every box by sat_clear.
+//
 // Four waves per environment: the boxes' frames from the env state (or pool
-// slot src_slot[e]; < 0 skips the env) computed as the step kernel computes
-// them, then the validity words of every contour push by the step kernel's
-// own start-pose test, wave w taking actions 64 w .. 64 w + 63 (words 2 w
-// and 2 w + 1).  Workgroups loop over the envs (the count may come from
-// device memory).
-constexpr int VALID_WAVES = PMBS_VALID_WORDS / 2;
+// slot src_slot[e]; < 0 skips the env), computed as the step kernel computes
+// them, then a thread per action for its pusher, then every (action, box) pair,
+// box j by wave j mod 4.  The ALU bounds it: 15 axes for each of 8 nb * nb
+// pairs, of which few are near each other.  So the pairs go through three
+// sieves, a wave's own list of pairs packed after each: the pusher's two
+// horizontal axes, lane = action (the pusher's own radii formed once; most of
+// the pairs end here), then the other four face axes, then the nine edge axes,
+// lane = pair.  Workgroups loop over the envs (the count may come from device
+// memory).
+constexpr int VALID_WAVES = PMBS_VALID_WORDS / 2, VALID_ACTIONS = 32 * PMBS_VALID_WORDS;
+struct ValidShared {
+  Frames f;
+  float4 centre[VALID_ACTIONS];    // pusher centre (x, y), radii along its first two axes
+  float4 axes[VALID_ACTIONS];      // its first two axes (x, y each; z = 0)
+  unsigned short list[VALID_WAVES][VALID_ACTIONS * (MAXB / VALID_WAVES + 1)];   // action | box << 8
+  unsigned hit[PMBS_VALID_WORDS];  // actions that meet a box
+};
+
+__device__ __forceinline__ Box action_box(float4 centre, float4 axes, const Params& p) {
+  Box b;
+  b.c = mk(centre.x, centre.y, p.pusher_z);
+  b.a0 = mk(axes.x, axes.y, 0.0f);
+  b.a1 = mk(axes.z, axes.w, 0.0f);
+  b.a2 = mk(0, 0, 1);
+  b.h = mk(p.phx, p.phy, p.phz);
+  return b;
+}
+
 __global__ __launch_bounds__(64 * VALID_WAVES) void valid_kernel(ValidArgs g) {
-  __shared__ Frames s;
+  static_assert(MAXB <= 256 && VALID_ACTIONS <= 256, "a pair is 8 + 8 bits");
+  __shared__ ValidShared s;
+  const Params& p = g.p;
   const int n = g.count ? g.count[0] + g.count[1] : g.n_envs;
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
+  const unsigned long long below = (1ull << lane) - 1ull;
+  unsigned short* const list = s.list[wid];
   for (int e = blockIdx.x; e < n; e += gridDim.x) {
     const int src = g.src_slot ? g.src_slot[e] : -1;
     if (g.src_slot && src < 0) continue;
     const int base = g.env_offset[e];
     const int nb = g.env_offset[e + 1] - base;
-    if (wid == 0 && lane < nb) {
+    if (t < nb) {
       const float* st = src >= 0 ? g.pool + (size_t)src * 13 * g.pool_stride : g.state;
       const int SN = src >= 0 ? g.pool_stride : g.stride;
       const int si = src >= 0 ? lane : base + lane;
@@ -2225,17 +2237,66 @@ __global__ __launch_bounds__(64 * VALID_WAVES) void valid_kernel(ValidArgs g) {
       const int bi = g.bc_base ? g.bc_base[e] + lane : base + lane;
       f3 c0, c1, c2;
       quat_cols(st[3 * SN + si], st[4 * SN + si], st[5 * SN + si], st[6 * SN + si], &c0, &c1, &c2);
-      s.pos[lane] = make_float4(st[0 * SN + si], st[1 * SN + si], st[2 * SN + si], 0.0f);
-      s.col[0][lane] = f4(c0, 0.0f);
-      s.col[1][lane] = f4(c1, 0.0f);
-      s.col[2][lane] = f4(c2, 0.0f);
-      s.half[lane] = make_float4(g.bconst[0 * BN + bi], g.bconst[1 * BN + bi], g.bconst[2 * BN + bi], 0.0f);
+      s.f.pos[lane] = make_float4(st[0 * SN + si], st[1 * SN + si], st[2 * SN + si], 0.0f);
+      s.f.col[0][lane] = f4(c0, 0.0f);
+      s.f.col[1][lane] = f4(c1, 0.0f);
+      s.f.col[2][lane] = f4(c2, 0.0f);
+      s.f.half[lane] = make_float4(g.bconst[0 * BN + bi], g.bconst[1 * BN + bi], g.bconst[2 * BN + bi], 0.0f);
+    }
+    if (t < PMBS_VALID_WORDS) s.hit[t] = 0u;
+    __syncthreads();
+    const int n_act = min(nb * p.n_dirs, VALID_ACTIONS);
+    if (t < n_act) {
+      const int obj = t / p.n_dirs, dir = t - obj * p.n_dirs;
+      const Box P = pusher_box(pusher_pose(contour_start(s.f, obj, dir, p), p), p);
+      s.centre[t] = make_float4(P.c.x, P.c.y, radius_along(P, P.a0), radius_along(P, P.a1));
+      s.axes[t] = make_float4(P.a0.x, P.a0.y, P.a1.x, P.a1.y);
     }
     __syncthreads();
-    const int a0 = 64 * wid;
-    const unsigned long long m = a0 < nb * g.p.n_dirs ? validity_bits(s, nb, g.p, a0, lane) : 0ull;
-    if (lane < 2) g.out[(size_t)e * PMBS_VALID_WORDS + 2 * wid + lane] = lane ? (unsigned)(m >> 32) : (unsigned)m;
-    __syncthreads();   // the frames are read before the next env's overwrite them
+    int kept = 0;
+    for (int j = wid; j < nb; j += VALID_WAVES) {
+      const Box A = load_box(s.f, j);
+      for (int a0 = 0; a0 < n_act; a0 += 64) {
+        const int a = min(a0 + lane, n_act - 1);
+        const float4 pc = s.centre[a];
+        const Box P = action_box(pc, s.axes[a], p);
+        const f3 d = P.c - A.c;
+        const bool apart = fabsf(dot(d, P.a0)) - radius_along(A, P.a0) - pc.z > 0.0f ||
+                           fabsf(dot(d, P.a1)) - radius_along(A, P.a1) - pc.w > 0.0f;
+        const bool keep = a0 + lane < n_act && !apart;
+        const unsigned long long m = __ballot(keep);
+        if (keep) list[kept + __popcll(m & below)] = (unsigned short)(a | j << 8);
+        kept += __popcll(m);
+      }
+    }
+    // a list is packed in place: what is written lies at or before the 64
+    // entries that were just read
+    wave_sync();
+    int left = 0;
+    for (int i0 = 0; i0 < kept; i0 += 64) {
+      const int v = list[min(i0 + lane, kept - 1)];
+      const Box A = load_box(s.f, v >> 8), P = action_box(s.centre[v & 255], s.axes[v & 255], p);
+      const f3 d = P.c - A.c;
+      float best = gap_along(A, P, d, P.a2);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) best = fmaxf(best, gap_along(A, P, d, axis(A, k)));
+      const bool keep = i0 + lane < kept && !(best > 0.0f);
+      const unsigned long long m = __ballot(keep);
+      wave_sync();
+      if (keep) list[left + __popcll(m & below)] = (unsigned short)v;
+      left += __popcll(m);
+      wave_sync();
+    }
+    for (int i0 = 0; i0 < left; i0 += 64) {
+      const int v = list[min(i0 + lane, left - 1)], a = v & 255;
+      const Box A = load_box(s.f, v >> 8), P = action_box(s.centre[a], s.axes[a], p);
+      if (i0 + lane < left && !edges_clear(A, P, p.edge_eps)) atomicOr(&s.hit[a >> 5], 1u << (a & 31));
+    }
+    __syncthreads();
+    if (t < PMBS_VALID_WORDS) {
+      const int m = n_act - 32 * t;
+      g.out[(size_t)e * PMBS_VALID_WORDS + t] = ~s.hit[t] & (m >= 32 ? ~0u : m > 0 ? (1u << m) - 1u : 0u);
+    }
   }
 }
 

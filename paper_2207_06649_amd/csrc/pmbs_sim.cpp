@@ -613,6 +613,26 @@ pmbs_status pmbs_sim_get_launch_plan(const pmbs_sim_t* sim, pmbs_launch_plan* pl
   return PMBS_OK;
 }
 
+// The 13 rows of a state of n bodies between two row strides, queued on st.
+// Each copy is a launch of about 4.7 us whatever its size here, so rows that
+// lie end to end on both sides (a simulator filled to max_bodies, as a
+// planner's is) go as one, and rows of device memory otherwise as one
+// strided copy; rows to or from host memory then go one by one, since the
+// runtime stages pageable memory by whole copies.
+static hipError_t copy_rows(float* dst, int dst_stride, const float* src, int src_stride, int n, hipMemcpyKind kind,
+                            hipStream_t st) {
+  if (n <= 0) return hipSuccess;
+  const size_t w = (size_t)n * sizeof(float);
+  if (dst_stride == n && src_stride == n) return hipMemcpyAsync(dst, src, 13 * w, kind, st);
+  if (kind == hipMemcpyDeviceToDevice)
+    return hipMemcpy2DAsync(dst, (size_t)dst_stride * sizeof(float), src, (size_t)src_stride * sizeof(float), w, 13, kind,
+                            st);
+  hipError_t e = hipSuccess;
+  for (int r = 0; r < 13 && e == hipSuccess; ++r)
+    e = hipMemcpyAsync(dst + (size_t)r * dst_stride, src + (size_t)r * src_stride, w, kind, st);
+  return e;
+}
+
 pmbs_status pmbs_sim_set_state(pmbs_sim_t* sim, int32_t n_envs, const int32_t* env_offset, const float* state,
                                int32_t state_is_device, const float* body) {
   if (!sim || !env_offset || !state || !body) return fail(PMBS_ERR_INVALID_ARG, "null argument");
@@ -639,11 +659,9 @@ pmbs_status pmbs_sim_set_state(pmbs_sim_t* sim, int32_t n_envs, const int32_t* e
     if (cs != PMBS_OK) return cs;
   }
   // state rows are strided by max_bodies on the device
-  for (int r = 0; r < 13 && n > 0; ++r) {
-    e = hipMemcpyAsync(sim->d_state + (size_t)r * N, state + (size_t)r * n, (size_t)n * sizeof(float),
-                       state_is_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, sim->stream);
-    if (e != hipSuccess) return hip_fail(e, "state upload");
-  }
+  e = copy_rows(sim->d_state, N, state, n, n, state_is_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
+                sim->stream);
+  if (e != hipSuccess) return hip_fail(e, "state upload");
   e = hipMemcpyAsync(sim->d_bconst, bc.data(), bc.size() * sizeof(float), hipMemcpyHostToDevice, sim->stream);
   if (e != hipSuccess) return hip_fail(e, "body upload");
   e = hipMemcpyAsync(sim->d_env_offset, env_offset, (size_t)(n_envs + 1) * sizeof(int32_t), hipMemcpyHostToDevice,
@@ -665,13 +683,11 @@ pmbs_status pmbs_sim_get_state(pmbs_sim_t* sim, float* out, int32_t dst_is_devic
   if (!sim || !out) return fail(PMBS_ERR_INVALID_ARG, "null argument");
   if (sim->pool_layout) return fail(PMBS_ERR_INVALID_ARG, "the env layout holds pool-only rollouts: load a state first");
   const int n = sim->n_bodies, N = sim->cfg.max_bodies;
-  for (int r = 0; r < 13 && n > 0; ++r) {
-    hipError_t e = hipMemcpyAsync(out + (size_t)r * n, sim->d_state + (size_t)r * N, (size_t)n * sizeof(float),
-                                  dst_is_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, sim->stream);
-    if (e != hipSuccess) return hip_fail(e, "state download");
-  }
+  hipError_t e = copy_rows(out, n, sim->d_state, N, n, dst_is_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost,
+                           sim->stream);
+  if (e != hipSuccess) return hip_fail(e, "state download");
   if (!dst_is_device) {
-    hipError_t e = hipStreamSynchronize(sim->stream);
+    e = hipStreamSynchronize(sim->stream);
     if (e != hipSuccess) return hip_fail(e, "get_state sync");
   }
   return PMBS_OK;

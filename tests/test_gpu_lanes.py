@@ -151,3 +151,57 @@ def test_more_than_64_rows(pm, n, waves):
     assert np.abs(got[0][:, 7:] - o[:, 7:]).max() <= 1e-4
     other = stepped(pm, [0, n], st, bd, FAR, 1, waves, 512)
     assert all(np.array_equal(a, b) for a, b in zip(got, other))
+
+
+@pytest.mark.parametrize("n", [1, 2, 8, 9, 16, 31])
+def test_validity_words_at_the_edges_of_the_waves(pm, n):
+    """The pairs (push, box) of an environment go through packed lists, a list
+    per wave and box j in that of wave j mod 4: 8 boxes fill a wave of pushes,
+    9 take a second, 31 are the largest environment.  Tilted boxes crowded
+    together, so that many pairs reach the last list; every push that float64
+    decides by 10 um or more is decided alike."""
+    rng = np.random.default_rng(100 + n)
+    st, bd = np.zeros((n, 13)), np.zeros((n, 5))
+    for i in range(n):
+        q = rng.normal(size=4) * [1.0, 0.4, 0.4, 1.0]
+        st[i, :3] = [*rng.uniform(-0.1, 0.1, size=2), rng.uniform(0.01, 0.05)]
+        st[i, 3:7] = q / np.linalg.norm(q)
+        bd[i] = [*rng.uniform(0.01, 0.03, size=3), 0.1, 0.5]
+    st, bd = f32(st), f32(bd)
+    cfg = O.make_config()
+    sim = pm.Sim(max_envs=1, max_bodies=n)
+    sim.set_state([0, n], st, bd)
+    words = sim.valid_pushes()[0]
+    got = np.array([(int(words[a >> 5]) >> (a & 31)) & 1 for a in range(256)], bool)
+    assert not got[8 * n:].any()
+    want = O.valid_pushes(cfg, st, bd)
+    sure = 0
+    for a in range(8 * n):
+        push = O.contour_push(cfg, st[a // 8], bd[a // 8], a % 8, 8)
+        yaw = np.arctan2(push[3] - push[1], push[2] - push[0])
+        x, q = np.array([push[0], push[1], cfg.pusher_z]), np.array([np.cos(yaw / 2), 0, 0, np.sin(yaw / 2)])
+        sep = [O.sat_max_separation(cfg, st[j, :3], st[j, 3:7], bd[j, :3], x, q, np.array(cfg.pusher_half[:]))
+               for j in range(n)]
+        if min(abs(v) for v in sep) >= 1e-5:
+            sure += 1
+            assert got[a] == want[a], (a, min(sep))
+    assert sure >= 0.9 * 8 * n
+
+
+@pytest.mark.parametrize("spare", [0, 5])
+def test_state_rows_with_and_without_spare_capacity(pm, spare):
+    """Rows that lie end to end go as one copy, others by their strides; to and
+    from host and device memory, bit for bit."""
+    import torch
+    b = scenes.clutter_batch(3, 4, 7)
+    st = np.asarray(b.state, np.float32)
+    sim = pm.Sim(max_envs=4, max_bodies=b.n_bodies + spare)
+    sim.set_state(b.env_offset, st, b.body)
+    assert np.array_equal(sim.get_state(), st)
+    dev = sim.get_state_device()
+    torch.cuda.synchronize()
+    assert np.array_equal(dev.cpu().numpy().T, st)
+    flip = torch.tensor(np.ascontiguousarray(st[::-1].T), device="cuda")
+    torch.cuda.synchronize()
+    sim.set_state(b.env_offset, flip, b.body[::-1])
+    assert np.array_equal(sim.get_state(), st[::-1])
