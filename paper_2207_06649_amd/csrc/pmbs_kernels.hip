@@ -123,7 +123,7 @@ struct Smem {
   static constexpr int PLANE = MB;                // LDS index of the table
   static constexpr int NOBJ = MB + 1;
   static constexpr int MAX_PAIRS = MB * (MB - 1) / 2;
-  float4 pos[NOBJ];                  // centre
+  float4 pos[NOBJ];                  // centre, how far the body has moved in the push
   float4 col[3][NOBJ];               // rotation columns (body axes in world)
   float4 half[NOBJ];                 // hx, hy, hz, inverse mass
   float4 quat[MB];                   // orientation (the lanes' copy between the stages that use it)
@@ -137,6 +137,7 @@ struct Smem {
   unsigned short inc[2 * C];
   int lstart[MB];                    // incidence list starts
   unsigned short pairs[MAX_PAIRS];   // candidate pairs (one wave: then the live ones)
+  float apart[(MAX_PAIRS + 63) / 64 * 64];   // pair number p's boxes stay apart while they have moved less than this
   unsigned short list[W > 1 ? W : 1][W > 1 ? MAX_PAIRS : 1];   // two waves: each its copy of the live pairs
   // 31-box layout: the pairs whose AABBs, grown by SKIN, overlapped when they
   // were last listed, and those grown AABBs
@@ -151,7 +152,7 @@ struct Smem {
       float4 stage[C][2];            // narrowphase output: (p, sep), (n, -)
       union alignas(16) {
         struct {
-          float4 lo[MB], hi[MB];     // AABBs: min and max corner (x, y, z, -)
+          float4 lo[MB], hi[MB];     // AABBs: min corner and pos's fourth, max corner
         } box;
         struct {
           unsigned char live[MAX_PAIRS];     // candidate pairs that no face axis separates
@@ -585,6 +586,19 @@ __device__ __forceinline__ unsigned pair_of(int p, int n) {
   return (unsigned)(i | ((p - i * (2 * n - i - 1) / 2 + i + 1) << 5));
 }
 
+// The number of pair (i, j), i < j < n, in that order.
+__device__ __forceinline__ int number_of(int i, int j, int n) { return i * (2 * n - i - 1) / 2 + j - i - 1; }
+
+// |x| + |y| + |z|
+__device__ __forceinline__ float sum_abs(f3 a) { return fabsf(a.x) + fabsf(a.y) + fabsf(a.z); }
+
+// Maximum over each eight lanes: DPP quad permutations, then row_half_mirror.
+__device__ __forceinline__ float max_of_eight(float v) {
+  v = fmaxf(v, quad<Q_XOR1>(v));
+  v = fmaxf(v, quad<Q_XOR2>(v));
+  return fmaxf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x141, 0xf, 0xf, true)));
+}
+
 // ------------------------------------------------------------------ footprint distance (reward)
 // Footprint of a box = its projection on the table (a zonotope with
 // generators h_k a_k projected).  Overlap: a separating axis among the
@@ -801,10 +815,10 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
 
   // frames of the bodies (centre, rotation)
   f3 c0, c1, c2;
-  auto write_body_frames = [&](int b, bool first) {
+  auto write_body_frames = [&](int b, bool first, float moved) {
     quat_cols(q0, q1, q2, q3, &c0, &c1, &c2);
     if (first) {
-      st3(&s.pos[b], x);
+      s.pos[b] = f4(x, moved);
       st3(&s.col[0][b], c0);
       st3(&s.col[1][b], c1);
       st3(&s.col[2][b], c2);
@@ -835,8 +849,43 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
   for (int job = 0; job < 2; ++job) {
   for (int t = 0; t < n_push; ++t) {
   // ---- push begin (uniform across the workgroup)
-  write_body_frames(b, first);
+  write_body_frames(b, first, 0.0f);
+  if (lead) {
+    for (int i = lane; i < n_tri; i += 64) s.apart[i] = -INFINITY;
+  }
   sync_all<W>();
+  // Pairs that a face axis keeps apart are left out of the candidates while
+  // they provably stay so.  A body's `moved` grows each substep by a bound on
+  // how far any point within `reach` of its centre can have moved: speed and
+  // angular speed times reach, over dt, each 2-norm bounded by the sum of the
+  // components, and the position stage's roundings (4.8e-7 of centre and reach
+  // is 8 half ulps of each).  Along a face axis that turns with its box, a gap
+  // shrinks by no more than the two bodies' bounds when reach is at least the
+  // distance from either centre to any point of the other box: boxes whose
+  // AABBs overlap are within sqrt(3) (2 R + 2 margin) + R of each other in that
+  // sense, R the largest half diagonal.  With this a candidate list holds 2.5
+  // of the 9.3 overlapping pairs of 21 boxes, 1.0 of 7.1 of 15, and the sieve
+  // below, 1200 to 1500 cycles of a substep before, 65 to 180.
+  float reach = sqrtf(dot(ph, ph)), far = 0.0f;
+  if (lane < nb) {
+    const f3 hl = xyz(s.half[lane]);
+    reach = fmaxf(reach, sqrtf(dot(hl, hl)));
+    far = sum_abs(xyz(s.pos[lane]));
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    reach = fmaxf(reach, __shfl_xor(reach, o, 64));
+    far = fmaxf(far, __shfl_xor(far, o, 64));
+  }
+  reach = uniform(4.5f * reach + 4.0f * p.margin);
+  // sums are rounded up, and grow with the distance from where the push began
+  constexpr float MOVE_UP = 1.0f + 0x1p-20f;
+  float move_round = 4.8e-7f * (far + reach);
+  const float turn_reach = uniform(dt * reach);
+  // the least gap that counts: the margin, and 8e-6 of reach for the roundings of two evaluations
+  const float gap0 = uniform(p.margin + 8e-6f * reach);
+  // a pair's apart value from a gap along a face axis and the sum of its `moved`
+  auto apart_until = [&](float gap, float moved) { return gap - gap0 + moved * 0.999999f; };
+
   bool have_push;
   float4 push = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   if (rollout) {
@@ -908,6 +957,7 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
     st3(&s.col[1][nb], pc1);
     st3(&s.col[2][nb], mk(0, 0, 1));
   }
+  move_round = uniform(move_round + 4.8e-7f * sum_abs(xp));
   const f3 pext = uniform(aabb_ext(pc0, pc1, mk(0, 0, 1), ph, p.margin));
   pdir = uniform(pdir);
   n_move = __builtin_amdgcn_readfirstlane(n_move);
@@ -927,11 +977,12 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
   }
   int n_inc = 0, inc0 = 0;   // the lane's body's list of row contacts: length and start
   int n_near = 0;            // near pairs (the broadphase's wave), the lane's first of them
-  unsigned near0 = 0u;
+  unsigned near0 = 0u;   // (its number, i, j: 16 + 8 + 8 bits)
   for (int k = 0; k < n_sub; ++k) {
     const int lane = opaque(threadIdx.x & 63), b = (unsigned)lane / L, j = (unsigned)lane % L;
     const bool active = lead && b < nb, first = active && j == 0;
     // ---- 1. velocity stage
+    const float step_move = fmaf(turn_reach, sum_abs(w), fmaf(dt, sum_abs(v), move_round));
     v.z -= p.gravity * dt;
     const float vs = (valid && k < n_move) ? p.push_speed : 0.0f;
     const f3 vp = pdir * vs;
@@ -941,6 +992,7 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
     // registers over the substep they spill.
     const int bl = active ? b : 0;
     h = xyz(s.half[bl]);
+    const float moved = fmaf(s.pos[bl].w, MOVE_UP, step_move);
     f3 ga, gb, gpa, gpb;   // the grown AABBs of the lane's body and of the pusher
     if constexpr (S::KEEP) {
       ga = xyz(s.glo[bl]);
@@ -948,21 +1000,23 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
       gpa = xyz(s.glo[nb]);
       gpb = xyz(s.ghi[nb]);
     }
-    write_body_frames(b, first);
+    write_body_frames(b, first, moved);
     bool relist_near = false;
     {
       const f3 ext = aabb_ext(c0, c1, c2, h, p.margin);
       const f3 lo = x - ext, hi = x + ext;
       if (first) {
-        st3(&s.u.n.x.box.lo[b], lo);
+        s.u.n.x.box.lo[b] = f4(lo, moved);
         st3(&s.u.n.x.box.hi[b], hi);
       }
       const bool pusher = lead && lane == 0;
       const f3 plo = xp - pext, phi = xp + pext;
       if (pusher) {
-        st3(&s.pos[nb], xp);
+        // the pusher does not turn
+        const float m = 1.001f * fmaf((float)k, move_round, (float)min(k, n_move) * (fabsf(p.push_speed) * dt));
+        s.pos[nb] = f4(xp, m);
         st3(&s.vel[nb], vp);
-        st3(&s.u.n.x.box.lo[nb], plo);
+        s.u.n.x.box.lo[nb] = f4(plo, m);
         st3(&s.u.n.x.box.hi[nb], phi);
       }
       if constexpr (S::KEEP) {
@@ -997,29 +1051,37 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
     // passes); in the 31-box one (up to eight) those of the near list, which
     // is one pass, and every pair's grown AABBs when that has to be listed
     // again: at a push's start and after 6 mm of motion, fifteen substeps of
-    // the pusher's.  30 boxes: 2.2 us less per substep of a lone wave.
-    int n_pairs = 0;
+    // the pusher's (22 objects: 1535 -> 520 cycles of a lone wave's substep;
+    // 700 x 27: 1.52 -> 1.46 ms).
+    int n_pairs = 0, n_cand = 0;   // overlapping pairs; those of them that are candidates
     if (W == 1 || wid == 1) {
       struct Boxes {
         unsigned ii, jj;
-        f3 il, ih, jl, jh;
+        float4 il, jl;
+        f3 ih, jh;
+        float apart;
       };
-      auto load = [&](unsigned ii, unsigned jj) {
+      auto load = [&](unsigned ii, unsigned jj, int number) {
         const auto& b4 = s.u.n.x.box;
-        return Boxes{ii, jj, xyz(b4.lo[ii]), xyz(b4.hi[ii]), xyz(b4.lo[jj]), xyz(b4.hi[jj])};
+        return Boxes{ii, jj, b4.lo[ii], b4.lo[jj], xyz(b4.hi[ii]), xyz(b4.hi[jj]), s.apart[number]};
       };
       auto load_tri = [&](int k2) {
         const unsigned ij = (unsigned)opaque((int)tri[k2 / 3]) >> (10 * (k2 % 3));
         const unsigned ii = ij & 31u, jj = (ij >> 5) & 31u;
-        if constexpr (S::KEEP) return Boxes{ii, jj, xyz(s.glo[ii]), xyz(s.ghi[ii]), xyz(s.glo[jj]), xyz(s.ghi[jj])};
-        else return load(ii, jj);
+        if constexpr (S::KEEP) return Boxes{ii, jj, s.glo[ii], s.glo[jj], xyz(s.ghi[ii]), xyz(s.ghi[jj]), 0.0f};
+        else return load(ii, jj, 64 * k2 + lane);
       };
-      // the overlapping ones of a pass after the n before them in out
-      auto list = [&](const Boxes& t, auto& out, int& n) {
+      // the overlapping ones of a pass after the n before them in out, without
+      // those that are known to be apart (near pairs: all of them)
+      auto list = [&](const Boxes& t, auto& out, int& n, bool near) {
         // one compare per ballot, joined in scalar registers
-        const unsigned long long hm = __ballot(t.ii < t.jj) & __ballot(t.il.x <= t.jh.x) & __ballot(t.jl.x <= t.ih.x) &
-                                      __ballot(t.il.y <= t.jh.y) & __ballot(t.jl.y <= t.ih.y) &
-                                      __ballot(t.il.z <= t.jh.z) & __ballot(t.jl.z <= t.ih.z);
+        unsigned long long hm = __ballot(t.ii < t.jj) & __ballot(t.il.x <= t.jh.x) & __ballot(t.jl.x <= t.ih.x) &
+                                __ballot(t.il.y <= t.jh.y) & __ballot(t.jl.y <= t.ih.y) &
+                                __ballot(t.il.z <= t.jh.z) & __ballot(t.jl.z <= t.ih.z);
+        if (!near) {
+          n_pairs += __popcll(hm);
+          hm &= ~__ballot(t.il.w + t.jl.w < t.apart);
+        }
         // rank among the lower lanes' hits (mbcnt)
         const int rk = __builtin_amdgcn_mbcnt_hi((unsigned)(hm >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)hm, 0u));
         if (__builtin_amdgcn_inverse_ballot_w64(hm)) out[n + rk] = (unsigned short)((t.ii << 8) | t.jj);
@@ -1028,7 +1090,7 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
       // every pair (of grown AABBs in the 31-box layout), two passes' corners
       // in flight together (past the last pair a lane has the pair (0, 0),
       // which is none)
-      auto list_all = [&](auto& out, int& n) {
+      auto list_all = [&](auto& out, int& n, bool near) {
 #pragma unroll
         for (int k2 = 0; k2 < PASSES; k2 += 2) {
           if (64 * k2 < n_tri) {
@@ -1036,29 +1098,35 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
             if (k2 + 1 < PASSES && 64 * (k2 + 1) < n_tri) {
               const Boxes t1 = load_tri(k2 + 1 < PASSES ? k2 + 1 : k2);
               __builtin_amdgcn_sched_barrier(0);
-              list(t0, out, n);
-              list(t1, out, n);
+              list(t0, out, n, near);
+              list(t1, out, n, near);
             } else {
-              list(t0, out, n);
+              list(t0, out, n, near);
             }
           }
         }
       };
       if constexpr (S::KEEP) {
+        // near pair p0 + lane, its pair number in the upper half
+        auto numbered = [&](int p0) -> unsigned {
+          if (p0 + lane >= n_near) return 0u;
+          const unsigned pr = s.near[p0 + lane];
+          return pr | (unsigned)number_of(pr >> 8, pr & 255u, n_obj) << 16;
+        };
         if constexpr (W > 1) relist_near = __builtin_amdgcn_readfirstlane(s.sh_near) != 0;
         if (relist_near) {
           n_near = 0;
-          list_all(s.near, n_near);
+          list_all(s.near, n_near, true);
           wave_sync();
-          near0 = lane < n_near ? s.near[lane] : 0u;
+          near0 = numbered(0);
         }
-        list(load(near0 >> 8, near0 & 255u), s.pairs, n_pairs);
+        list(load((near0 >> 8) & 255u, near0 & 255u, near0 >> 16), s.pairs, n_cand, false);
         for (int p0 = 64; p0 < n_near; p0 += 64) {
-          const unsigned pr = p0 + lane < n_near ? s.near[p0 + lane] : 0u;
-          list(load(pr >> 8, pr & 255u), s.pairs, n_pairs);
+          const unsigned pr = numbered(p0);
+          list(load((pr >> 8) & 255u, pr & 255u, pr >> 16), s.pairs, n_cand, false);
         }
       } else {
-        list_all(s.pairs, n_pairs);
+        list_all(s.pairs, n_cand, false);
       }
     }
 
@@ -1115,14 +1183,16 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
     }
     if constexpr (W > 1) {
       // every wave needs the pair list and the table contacts
-      if (wid == 1 && lane == 0) s.sh_pairs = n_pairs;
+      if (wid == 1 && lane == 0) s.sh_pairs = n_pairs | n_cand << 16;
       if (lead && lane == 0) {
         s.sh_table = n_table;
         s.sh_held = n_held;
         s.sh_extra = n_extra;
       }
       __syncthreads();
-      n_pairs = __builtin_amdgcn_readfirstlane(s.sh_pairs);
+      n_cand = __builtin_amdgcn_readfirstlane(s.sh_pairs);
+      n_pairs = n_cand & 0xffff;
+      n_cand >>= 16;
       n_table = __builtin_amdgcn_readfirstlane(s.sh_table);
       n_held = __builtin_amdgcn_readfirstlane(s.sh_held);
       n_extra = __builtin_amdgcn_readfirstlane(s.sh_extra);
@@ -1133,37 +1203,44 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
     int n_rows = n_extra;
 
     // ---- 4b. box-box and pusher-box contacts, pairs in lexicographic order.
-    // More than four candidate pairs are sieved first, eight per pass on eight
-    // lanes each: a pair separated along a face axis by more than the margin
-    // has no contact whatever the other axes give (at the headline 92 % of
-    // them; face gl of A, gl - 3 of B).  The live ones are listed in order.
-    int n_live = n_pairs;
+    // More than four candidate pairs (a push's first substeps, mostly) are
+    // sieved first, eight per pass on eight lanes each: a pair separated along
+    // a face axis by more than the margin has no contact whatever the other
+    // axes give (face gl of A, gl - 3 of B).  Up to four go into one pass of
+    // the full test, which costs what it does for one.  The live ones are
+    // listed in order.
+    int n_live = n_cand;
     const unsigned short* live_list = s.pairs;
-    if (n_pairs > GROUPS) {
+    if (n_cand > GROUPS) {
       // opaque: the lane's addresses and selects are formed here, not kept in
       // registers over the whole push
       const int ln = opaque(lane), grp = ln >> 3, gl = ln & 7;
-      for (int r0 = 8 * wid; r0 < n_pairs; r0 += 8 * W) {
+      for (int r0 = 8 * wid; r0 < n_cand; r0 += 8 * W) {
         const int pi = r0 + grp;
-        const bool has = pi < n_pairs;
+        const bool has = pi < n_cand;
         const unsigned pr = has ? s.pairs[pi] : 0u;
         const int ia = pr >> 8, ib = pr & 255;
         const Box A = load_box(s, ia), B = load_box(s, ib);
+        const float moved = s.pos[ia].w + s.pos[ib].w;
         const f3 d = B.c - A.c;
         const f3 L = lds_axis(s, gl < 3 ? ia : ib, gl < 3 ? gl : (gl < 6 ? gl - 3 : gl - 6));
         const float sv = fabsf(dot(d, L)) - radius_along(A, L) - radius_along(B, L);
-        const unsigned long long apart = __ballot(sv > p.margin) & (0xffull << (8 * grp));
-        if (has && gl == 0) s.u.n.x.np.live[pi] = apart == 0ull ? 1 : 0;
+        const float gap = max_of_eight(sv);
+        if (has && gl == 0) {
+          s.u.n.x.np.live[pi] = gap > p.margin ? 0 : 1;
+          // (the first substep's orientations may not be unit quaternions yet)
+          if (gap > gap0 && k > 0) s.apart[number_of(ia, ib, n_obj)] = apart_until(gap, moved);
+        }
       }
       sync_all<W>();
       // one wave lists them in place (a place is read before it is written),
       // two each in a list of its own
       unsigned short* const out = W > 1 ? s.list[wid] : s.pairs;
       n_live = 0;
-      for (int p0 = 0; p0 < n_pairs; p0 += 64) {
+      for (int p0 = 0; p0 < n_cand; p0 += 64) {
         const int pi = p0 + ln;
-        const bool hit = pi < n_pairs && s.u.n.x.np.live[pi] != 0;
-        const unsigned short pr = pi < n_pairs ? s.pairs[pi] : 0;
+        const bool hit = pi < n_cand && s.u.n.x.np.live[pi] != 0;
+        const unsigned short pr = pi < n_cand ? s.pairs[pi] : 0;
         const unsigned long long hm = __ballot(hit);
         const int rk = __builtin_amdgcn_mbcnt_hi((unsigned)(hm >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)hm, 0u));
         if (hit) out[n_live + rk] = pr;
@@ -1220,6 +1297,8 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
         scan(row_value<3>(sv), 3, p.tau_face);
         scan(row_value<4>(sv), 4, p.tau_face);
         scan(row_value<5>(sv), 5, p.tau_face);
+        if (has && gl == 0 && bs > gap0 && k > 0)
+          s.apart[number_of(ia, ib, n_obj)] = apart_until(bs, s.pos[ia].w + s.pos[ib].w);
         if (__ballot(has && edge && sv > bs + p.tau_edge) != 0ull) {
           const float se = edge ? sv : -INFINITY;
           scan(row_value<6>(se), 6, p.tau_edge);
@@ -1883,7 +1962,7 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
     // ---- reward after the push: clearance of the target's footprint, by
     // every wave from the frames in LDS (the same stopping decision); the L
     // lanes of a body share its vertices
-    write_body_frames(b, first);
+    write_body_frames(b, first, 0.0f);
     sync_all<W>();
     const int tg = g.target[e];
     const int lane = opaque(threadIdx.x & 63), b = (unsigned)lane / L, j = (unsigned)lane % L;

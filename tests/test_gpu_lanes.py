@@ -205,3 +205,37 @@ def test_state_rows_with_and_without_spare_capacity(pm, spare):
     torch.cuda.synchronize()
     sim.set_state(b.env_offset, flip, b.body[::-1])
     assert np.array_equal(sim.get_state(), st[::-1])
+
+
+@pytest.mark.parametrize("n,waves", [(3, 1), (15, 1), (15, 2), (16, 1), (22, 2), (30, 1)])
+def test_pairs_kept_apart_come_back(pm, n, waves):
+    """A pair that a face axis keeps apart is left out until the bound on its
+    boxes' motion has used up the gap.  A large box a kilometre away makes that
+    bound so large that every pair is tested again at every substep, and
+    changes nothing else: the other boxes, spinning, thrown at each other and
+    pushed, end bit for bit alike with and without it."""
+    rng = np.random.default_rng(10 * n + waves)
+    off, st, bd, far_off, far_st, far_bd, push = [0], [], [], [0], [], [], []
+    for e in range(8):
+        s, b = np.zeros((n, 13)), np.zeros((n, 5))
+        side = int(np.ceil(np.sqrt(n)))
+        for i in range(n):
+            q = rng.normal(size=4) * [1.0, 0.3, 0.3, 1.0]
+            b[i] = [*rng.uniform(0.008, 0.025, size=3), rng.uniform(0.05, 0.2), 0.5]
+            s[i, :3] = [0.065 * (i % side - side / 2), 0.065 * (i // side - side / 2), rng.uniform(0.03, 0.06)]
+            s[i, 3:7] = q / np.linalg.norm(q)
+            s[i, 7:10] = rng.normal(scale=0.3, size=3)
+            s[i, 10:13] = rng.normal(scale=6.0 if e % 2 else 0.5, size=3)
+        s, b = f32(s), f32(b)
+        huge = np.zeros((1, 13))
+        huge[0, :4] = [1000.0, 0.0, 0.5, 1.0]
+        st.append(s), bd.append(b), off.append(off[-1] + n)
+        far_st.append(np.concatenate([s, huge])), far_bd.append(np.concatenate([b, [[40.0, 40.0, 0.5, 100.0, 0.5]]]))
+        far_off.append(far_off[-1] + n + 1)
+        x = 0.065 * side / 2 + 0.08
+        push.append([-x, rng.uniform(-0.05, 0.05), x, rng.uniform(-0.05, 0.05)])
+    args = dict(waves=waves, contacts=256 if n > 15 else 128)
+    near, status, _ = stepped(pm, off, np.concatenate(st), np.concatenate(bd), push, 150, **args)
+    far, far_status, _ = stepped(pm, far_off, np.concatenate(far_st), np.concatenate(far_bd), push, 150, **args)
+    assert np.isfinite(near).all() and np.array_equal(status, far_status)
+    assert np.array_equal(near, far.reshape(8, n + 1, 13)[:, :n].reshape(-1, 13))
