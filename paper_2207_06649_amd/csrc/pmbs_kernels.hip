@@ -93,6 +93,9 @@ __device__ __forceinline__ int opaque(int x) {
   return x;
 }
 
+// The compiler has a value here, before and after other side effects as written.
+__device__ __forceinline__ void hold(f3& v) { asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z)); }
+
 // A value that is the same in every lane, in scalar registers.
 __device__ __forceinline__ float uniform(float v) {
   return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
@@ -546,6 +549,64 @@ __device__ __forceinline__ void prep_quad(const S& s, int c, int q, const Params
   ct->at_b = 4 * b + qc;
 }
 
+// Row contact lane / 4 of n_rows in the lane's quad, with its impulse of the
+// previous substep; past the last an absent contact of the table with itself:
+// zero impulses.
+template <class S>
+__device__ __forceinline__ QuadContact begin_quad(const S& s, int lane, int n_rows, int nwarm, int n_extra, const Params& p) {
+  const int c = lane >> 2, q = lane & 3;
+  const f3 z = mk(0, 0, 0);
+  QuadContact qc;
+  if (c < n_rows) {
+    prep_quad(s, c, q, p, &qc);
+    qc.lam = turn(warm_impulse(s, c, nwarm, n_extra), q).x;
+  } else {
+    qc = QuadContact{4 * S::PLANE, 4 * S::PLANE, z, z, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+  }
+  return qc;
+}
+
+// The impulse rows (P, ra x P, rb x P) of a change dl of the quad's impulses.
+template <class S>
+__device__ __forceinline__ void put_quad(S& s, int lane, const QuadContact& qc, float dl) {
+  float* const rows = reinterpret_cast<float*>(&s.u.imp[0][0]) + lane;
+  const float R = fmaf(qc.comp.x, quad<0x00>(dl), fmaf(qc.comp.y, quad<0x55>(dl), qc.comp.z * quad<0xaa>(dl)));
+  const float R1 = quad<0xc9>(R), R2 = quad<0xd2>(R);   // components q + 1, q + 2
+  rows[0] = R;
+  rows[4 * S::C] = qc.ra1 * R2 - qc.ra2 * R1;
+  rows[8 * S::C] = qc.rb1 * R2 - qc.rb2 * R1;
+}
+
+// One iteration's update of the quad's impulses from the published velocities;
+// meanwhile() runs while these load.  Returns the change.
+template <class S, class F>
+__device__ __forceinline__ float update_quad(const S& s, QuadContact& qc, F meanwhile) {
+  const float* const vel = reinterpret_cast<const float*>(&s.vel[0]);
+  const float* const ang = reinterpret_cast<const float*>(&s.ang[0]);
+  const float va = vel[qc.at_a], wa1 = ang[qc.at_a], wa2 = ang[qc.at_a + 1];
+  const float vb = vel[qc.at_b], wb1 = ang[qc.at_b], wb2 = ang[qc.at_b + 1];
+  meanwhile();
+  const float u = fmaf(wb1, qc.rb2, fmaf(-wb2, qc.rb1, vb)) - fmaf(wa1, qc.ra2, fmaf(-wa2, qc.ra1, va));
+  const f3 U = mk(quad<0x00>(u), quad<0x55>(u), quad<0xaa>(u));
+  float l = __int_as_float(max(__float_as_int(qc.lam + qc.k * (qc.vs - dot(U, qc.dir))), qc.lo));
+  const float ln = quad<0x00>(l), lt1 = quad<0x55>(l), lt2 = quad<0xaa>(l);
+  const float lim = qc.mu * ln, mag2 = lt1 * lt1 + lt2 * lt2;
+  l *= fminf(lim * rsq(mag2), 1.0f);
+  const float dl = l - qc.lam;
+  qc.lam = l;
+  return dl;
+}
+
+// The substep's accumulated impulses by key, for the next one.
+template <class S>
+__device__ __forceinline__ void keep_quad(S& s, int lane, int n_rows, const QuadContact& qc) {
+  const int c = lane >> 2, q = lane & 3;
+  if (c < n_rows && q < 3) {
+    if (q == 0) s.wkey[c] = contact_key<S>(s.cab[c]);
+    s.wl[q][c] = qc.lam;
+  }
+}
+
 // A table contact: normal z, tangents -y and x, nothing on side a.  The
 // impulse of changes (dn, d1, d2) is (d2, -d1, dn) exactly.
 struct TableContact {
@@ -761,12 +822,16 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
   constexpr int C = S::C, PLANE = S::PLANE, MB = S::MB;
   constexpr int L = NB == 16 ? 4 : 2;   // lanes per body
   constexpr int TS = 4 / L;             // table contacts per lane
+  constexpr bool SPLIT = W > 1 && TS > 1;   // the second wave updates the row contacts
   const Params& p = g.p;
   // opaque: what follows from the lane number is formed anew for each env
   // and substep; kept over them it fills the registers with addresses
   const int lane = opaque(threadIdx.x & 63);
   const int wid = W > 1 ? (int)(threadIdx.x >> 6) : 0;
   const bool lead = wid == 0;
+  // scalar where there are barriers on either side of its branch, which whole
+  // waves then take
+  const bool row_wave = SPLIT ? __builtin_amdgcn_readfirstlane(wid) != 0 : !lead;
   const int b = (unsigned)lane / L, j = (unsigned)lane % L;
   const int base = g.env_offset[e];
   const int nb = g.env_offset[e + 1] - base;
@@ -1417,6 +1482,7 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
     }
     const int nc = nc_raw < C ? nc_raw : C;
     n_rows = n_rows < row_cap ? n_rows : row_cap;
+    if constexpr (SPLIT) n_rows = __builtin_amdgcn_readfirstlane(n_rows);
     if constexpr (COST) {
       // The work estimate of the env's push from its start pose; nothing else
       // is written.  A substep with row contacts costs about 2.6 times one
@@ -1490,8 +1556,31 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
       return;
     }
 
-    // the rest of the substep is the lead wave's
-    if (lead) {
+    // the rest of the substep is the lead wave's, but for up to 16 row
+    // contacts of the 31-box layout: there the second wave prepares and
+    // updates them in quads while the lead updates its lanes' table contacts,
+    // two each (22 objects: 1100 -> 1000 cycles an iteration; rollouts of 256
+    // x 21 6.10 -> 5.94 ms).  With one table contact per lane, as in the
+    // 16-box layout, two barriers an iteration cost what the split gives
+    // (1024 x 15, two waves a SIMD: 1.12 -> 1.14 ms): no split there.
+    const bool split = SPLIT && n_rows > 0 && n_rows <= 16;
+    if (row_wave) {
+      if constexpr (SPLIT) if (split) {
+        const int lane = opaque(threadIdx.x & 63);
+        __syncthreads();   // the bodies' data and the contact counts
+        QuadContact qc = begin_quad(s, lane, n_rows, nwarm, n_extra, p);
+        wave_sync();
+        put_quad(s, lane, qc, qc.lam);
+        __syncthreads();
+        for (int it = 0; it < p.iters; ++it) {
+          __syncthreads();   // the iteration-start velocities
+          put_quad(s, lane, qc, update_quad(s, qc, []() {}));
+          __syncthreads();   // the impulse rows
+        }
+        keep_quad(s, lane, n_rows, qc);
+      }
+      if constexpr (SPLIT) nwarm = n_rows;
+    } else {
     // world inverse inertia Iw^-1 = R diag(invI) R^T: diagonal, off-diagonal (xy, xz, yz)
     f3 md, mo;
     {
@@ -1617,6 +1706,9 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
       }
       corners = mask;
     }
+
+    if constexpr (SPLIT)
+      if (split) __syncthreads();   // to the row wave
 
     // ---- 6. prep of the lanes' table contacts (an absent one has zero
     // masses, so its impulses stay zero)
@@ -1811,56 +1903,41 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
       // instead of 61, and a third of the prep's masses).
       wave_sync();
       if (n_rows <= 16) {
-        QuadContact qc;
-        {
-          const int c = lane >> 2, q = lane & 3;
-          if (c < n_rows) {
-            prep_quad(s, c, q, p, &qc);
-            qc.lam = turn(warm_impulse(s, c, nwarm, n_extra), q).x;
-          } else {
-            // an absent contact of the table with itself: zero impulses
-            const f3 z = mk(0, 0, 0);
-            qc = QuadContact{4 * PLANE, 4 * PLANE, z, z, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-          }
-        }
-        wave_sync();
-        float* const rows = reinterpret_cast<float*>(&s.u.imp[0][0]) + lane;
-        auto put_rows = [&](float dl) {
-          const float R = fmaf(qc.comp.x, quad<0x00>(dl), fmaf(qc.comp.y, quad<0x55>(dl), qc.comp.z * quad<0xaa>(dl)));
-          const float R1 = quad<0xc9>(R), R2 = quad<0xd2>(R);   // components q + 1, q + 2
-          rows[0] = R;
-          rows[4 * C] = qc.ra1 * R2 - qc.ra2 * R1;
-          rows[8 * C] = qc.rb1 * R2 - qc.rb2 * R1;
-          wave_sync();   // the impulse rows
-        };
-        put_rows(qc.lam);
-        sums();
-        const float* const vel = reinterpret_cast<const float*>(&s.vel[0]);
-        const float* const ang = reinterpret_cast<const float*>(&s.ang[0]);
-        for (int it = 0; it < p.iters; ++it) {
-          publish();
-          const float va = vel[qc.at_a], wa1 = ang[qc.at_a], wa2 = ang[qc.at_a + 1];
-          const float vb = vel[qc.at_b], wb1 = ang[qc.at_b], wb2 = ang[qc.at_b + 1];
-          __builtin_amdgcn_sched_barrier(0);
-          table_begin();   // while the loads are in flight
-          __builtin_amdgcn_sched_barrier(0);
-          table_end();     // between the steps of the rows' chain
-          const float u = fmaf(wb1, qc.rb2, fmaf(-wb2, qc.rb1, vb)) - fmaf(wa1, qc.ra2, fmaf(-wa2, qc.ra1, va));
-          const f3 U = mk(quad<0x00>(u), quad<0x55>(u), quad<0xaa>(u));
-          float l = __int_as_float(max(__float_as_int(qc.lam + qc.k * (qc.vs - dot(U, qc.dir))), qc.lo));
-          const float ln = quad<0x00>(l), lt1 = quad<0x55>(l), lt2 = quad<0xaa>(l);
-          const float lim = qc.mu * ln, mag2 = lt1 * lt1 + lt2 * lt2;
-          l *= fminf(lim * rsq(mag2), 1.0f);
-          const float dl = l - qc.lam;
-          qc.lam = l;
-          put_rows(dl);
+        if constexpr (SPLIT) {
+          __syncthreads();   // the rows of the impulses carried over
           sums();
-        }
-        // remember this substep's accumulated impulses by key
-        const int c = lane >> 2, q = lane & 3;
-        if (c < n_rows && q < 3) {
-          if (q == 0) s.wkey[c] = contact_key<S>(s.cab[c]);
-          s.wl[q][c] = qc.lam;
+          for (int it = 0; it < p.iters; ++it) {
+            publish();
+            __syncthreads();
+            // between the barriers, while the row wave is busy: the compiler
+            // would move register work to either side of them
+            hold(v);
+            hold(w);
+            table_update();
+#pragma unroll
+            for (int ts = 0; ts < TS; ++ts) hold(P[ts]);
+            __syncthreads();
+            sums();
+          }
+        } else {
+          QuadContact qc = begin_quad(s, lane, n_rows, nwarm, n_extra, p);
+          wave_sync();
+          put_quad(s, lane, qc, qc.lam);
+          wave_sync();
+          sums();
+          for (int it = 0; it < p.iters; ++it) {
+            publish();
+            const float dl = update_quad(s, qc, [&]() {
+              __builtin_amdgcn_sched_barrier(0);
+              table_begin();   // while the loads are in flight
+              __builtin_amdgcn_sched_barrier(0);
+              table_end();     // between the steps of the rows' chain
+            });
+            put_quad(s, lane, qc, dl);
+            wave_sync();   // the impulse rows
+            sums();
+          }
+          keep_quad(s, lane, n_rows, qc);
         }
       } else {
         // the first RS slots' contacts in registers; the others, which only
