@@ -31,7 +31,10 @@ namespace pmbs {
 constexpr int MAXB = 32;             // boxes (<= 31) + the pusher
 constexpr int GROUPS = 4;            // pairs per narrowphase pass (16-lane groups)
 constexpr int POLY = 8;              // clip polygon capacity
-constexpr float SKIN = 0.006f;       // growth of the AABBs of the broadphase's near list (m)
+// Growth of the AABBs of the broadphase's near list (m).  More lengthens the
+// list, less has it listed anew more often: 700 x 27 1.39 to 1.40 ms with 3 mm,
+// 1.38 with 6 and with 12, where more environments have more than one pass.
+constexpr float SKIN = 0.006f;
 
 // ------------------------------------------------------------------ vectors
 struct f3 { float x, y, z; };
@@ -139,9 +142,8 @@ struct Smem {
   // (1 = b), in contact-index order.
   unsigned short inc[2 * C];
   int lstart[MB];                    // incidence list starts
-  unsigned short pairs[MAX_PAIRS];   // candidate pairs (one wave: then the live ones)
+  unsigned short pairs[MAX_PAIRS];   // candidate pairs
   float apart[(MAX_PAIRS + 63) / 64 * 64];   // pair number p's boxes stay apart while they have moved less than this
-  unsigned short list[W > 1 ? W : 1][W > 1 ? MAX_PAIRS : 1];   // two waves: each its copy of the live pairs
   // 31-box layout: the pairs whose AABBs, grown by SKIN, overlapped when they
   // were last listed, and those grown AABBs
   static constexpr bool KEEP = NB != 16;
@@ -157,10 +159,7 @@ struct Smem {
         struct {
           float4 lo[MB], hi[MB];     // AABBs: min corner and pos's fourth, max corner
         } box;
-        struct {
-          unsigned char live[MAX_PAIRS];     // candidate pairs that no face axis separates
-          float clip[W][2][POLY][3][GROUPS]; // each wave's clip polygons
-        } np;
+        float clip[W][2][POLY][3][GROUPS];   // each wave's clip polygons
         unsigned incm[NOBJ][2 * K];  // incidence build: contact bit masks per body
         float4 lam[MB * 4];          // table impulses (n, t1, t2) and corner mask of a changed corner set
       } x;
@@ -311,12 +310,12 @@ constexpr int Q_LOW = 0x44, Q_HIGH = 0xee;    // lanes 0, 1, 0, 1 and 2, 3, 2, 3
 // the clip buffers of wave wid
 template <class S>
 __device__ __forceinline__ f3 cl_get(const S& s, int wid, int buf, int i, int grp) {
-  const auto& c = s.u.n.x.np.clip[wid][buf][i];
+  const auto& c = s.u.n.x.clip[wid][buf][i];
   return mk(c[0][grp], c[1][grp], c[2][grp]);
 }
 template <class S>
 __device__ __forceinline__ void cl_put(S& s, int wid, int buf, int i, int grp, f3 v) {
-  auto& c = s.u.n.x.np.clip[wid][buf][i];
+  auto& c = s.u.n.x.clip[wid][buf][i];
   c[0][grp] = v.x;
   c[1][grp] = v.y;
   c[2][grp] = v.z;
@@ -653,13 +652,6 @@ __device__ __forceinline__ int number_of(int i, int j, int n) { return i * (2 * 
 // |x| + |y| + |z|
 __device__ __forceinline__ float sum_abs(f3 a) { return fabsf(a.x) + fabsf(a.y) + fabsf(a.z); }
 
-// Maximum over each eight lanes: DPP quad permutations, then row_half_mirror.
-__device__ __forceinline__ float max_of_eight(float v) {
-  v = fmaxf(v, quad<Q_XOR1>(v));
-  v = fmaxf(v, quad<Q_XOR2>(v));
-  return fmaxf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x141, 0xf, 0xf, true)));
-}
-
 // ------------------------------------------------------------------ footprint distance (reward)
 // Footprint of a box = its projection on the table (a zonotope with
 // generators h_k a_k projected).  Overlap: a separating axis among the
@@ -808,7 +800,9 @@ __device__ __forceinline__ void sync_all() {
 // touches another iterates without LDS at all.  4096 x 15: 3.15 -> 2.19 ms;
 // 700 x 27: 2.66 -> 1.85; 1024 x 15 on two waves: 1.50 -> 1.32; 64 x 9, one
 // wave per SIMD: 1.19 -> 1.10.  With row contacts in quads of lanes (below):
-// 2.09, 1.73, 1.18 and 0.97 ms.
+// 2.09, 1.73, 1.18 and 0.97 ms; with what followed, 1.76, 1.35, 1.12 and 0.88.
+// Now it is the vector ALU where a SIMD has three environments, and the chain
+// of dependent instructions, a substep after the other, where it has one.
 //
 // With W > 1 waves per environment the second wave tests the broadphase pairs
 // while the lead finds the table contacts, and takes every second narrowphase
@@ -929,8 +923,9 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
   // distance from either centre to any point of the other box: boxes whose
   // AABBs overlap are within sqrt(3) (2 R + 2 margin) + R of each other in that
   // sense, R the largest half diagonal.  With this a candidate list holds 2.5
-  // of the 9.3 overlapping pairs of 21 boxes, 1.0 of 7.1 of 15, and the sieve
-  // below, 1200 to 1500 cycles of a substep before, 65 to 180.
+  // of the 9.3 overlapping pairs of 21 boxes and 1.0 of 7.1 of 15; a sieve that
+  // found the others anew took 1200 to 1500 cycles of a substep (1024 x 15: 1.17
+  // -> 1.13 ms; 700 x 27: 1.44 -> 1.39).
   float reach = sqrtf(dot(ph, ph)), far = 0.0f;
   if (lane < nb) {
     const f3 hl = xyz(s.half[lane]);
@@ -1267,64 +1262,25 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
     const int row_cap = C - n_held;   // row contacts that fit the capacity
     int n_rows = n_extra;
 
-    // ---- 4b. box-box and pusher-box contacts, pairs in lexicographic order.
-    // More than four candidate pairs (a push's first substeps, mostly) are
-    // sieved first, eight per pass on eight lanes each: a pair separated along
-    // a face axis by more than the margin has no contact whatever the other
-    // axes give (face gl of A, gl - 3 of B).  Up to four go into one pass of
-    // the full test, which costs what it does for one.  The live ones are
-    // listed in order.
-    int n_live = n_cand;
-    const unsigned short* live_list = s.pairs;
-    if (n_cand > GROUPS) {
-      // opaque: the lane's addresses and selects are formed here, not kept in
-      // registers over the whole push
-      const int ln = opaque(lane), grp = ln >> 3, gl = ln & 7;
-      for (int r0 = 8 * wid; r0 < n_cand; r0 += 8 * W) {
-        const int pi = r0 + grp;
-        const bool has = pi < n_cand;
-        const unsigned pr = has ? s.pairs[pi] : 0u;
-        const int ia = pr >> 8, ib = pr & 255;
-        const Box A = load_box(s, ia), B = load_box(s, ib);
-        const float moved = s.pos[ia].w + s.pos[ib].w;
-        const f3 d = B.c - A.c;
-        const f3 L = lds_axis(s, gl < 3 ? ia : ib, gl < 3 ? gl : (gl < 6 ? gl - 3 : gl - 6));
-        const float sv = fabsf(dot(d, L)) - radius_along(A, L) - radius_along(B, L);
-        const float gap = max_of_eight(sv);
-        if (has && gl == 0) {
-          s.u.n.x.np.live[pi] = gap > p.margin ? 0 : 1;
-          // (the first substep's orientations may not be unit quaternions yet)
-          if (gap > gap0 && k > 0) s.apart[number_of(ia, ib, n_obj)] = apart_until(gap, moved);
-        }
-      }
-      sync_all<W>();
-      // one wave lists them in place (a place is read before it is written),
-      // two each in a list of its own
-      unsigned short* const out = W > 1 ? s.list[wid] : s.pairs;
-      n_live = 0;
-      for (int p0 = 0; p0 < n_cand; p0 += 64) {
-        const int pi = p0 + ln;
-        const bool hit = pi < n_cand && s.u.n.x.np.live[pi] != 0;
-        const unsigned short pr = pi < n_cand ? s.pairs[pi] : 0;
-        const unsigned long long hm = __ballot(hit);
-        const int rk = __builtin_amdgcn_mbcnt_hi((unsigned)(hm >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)hm, 0u));
-        if (hit) out[n_live + rk] = pr;
-        n_live += __popcll(hm);
-      }
-      live_list = out;
-      wave_sync();
-    }
-    // Four pairs per pass, 16 lanes each: lane k evaluates candidate axis k
-    // (0-2 faces of A, 3-5 faces of B, 6-14 edge crosses A_i x B_j), one
-    // evaluation for all fifteen.  Bound by the pass's chain of LDS round
-    // trips and dependent instructions.  With W waves a round is W passes,
-    // wave w taking pairs r0 + 4 w ..; the round's contacts keep the order.
-    for (int r0 = 0; r0 < n_live; r0 += GROUPS * W) {
+    // ---- 4b. box-box and pusher-box contacts, candidate pairs in
+    // lexicographic order.  Four pairs per pass, 16 lanes each: lane k
+    // evaluates candidate axis k (0-2 faces of A, 3-5 faces of B, 6-14 edge
+    // crosses A_i x B_j), one evaluation for all fifteen; clipping follows only
+    // when some pair of the pass has no axis that keeps it apart.  Bound by the
+    // pass's chain of LDS round trips and dependent instructions: about 1000
+    // cycles of a lone wave, and 2000 more with a contact to clip, so that
+    // listing the pairs that a face axis separates beforehand, eight lanes a
+    // pair, takes longer than it saves once those that stay apart are no
+    // candidates (700 x 27: 1.38 ms with such a sieve, 1.35 without; against
+    // eight lanes a pair for the fifteen axes, before: 1.67 -> 1.52 ms).  With W
+    // waves a round is W passes, wave w taking pairs r0 + 4 w ..; the round's
+    // contacts keep the order.
+    for (int r0 = 0; r0 < n_cand; r0 += GROUPS * W) {
       const int ln = opaque(lane);
       const int grp = ln >> 4, gl = ln & 15;
       const int pi = r0 + GROUPS * wid + grp;
-      const bool has = pi < n_live;
-      const unsigned pr = has ? live_list[pi] : 0u;
+      const bool has = pi < n_cand;
+      const unsigned pr = has ? s.pairs[pi] : 0u;
       const int ia = pr >> 8, ib = pr & 255;
       const unsigned long long gm = 0xffffull << (16 * grp);
       bool keep = false, face = false;
@@ -1362,6 +1318,8 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
         scan(row_value<3>(sv), 3, p.tau_face);
         scan(row_value<4>(sv), 4, p.tau_face);
         scan(row_value<5>(sv), 5, p.tau_face);
+        // a face axis keeps the boxes apart for a while (but the first
+        // substep's orientations may not be unit quaternions yet)
         if (has && gl == 0 && bs > gap0 && k > 0)
           s.apart[number_of(ia, ib, n_obj)] = apart_until(bs, s.pos[ia].w + s.pos[ib].w);
         if (__ballot(has && edge && sv > bs + p.tau_edge) != 0ull) {
@@ -2178,6 +2136,9 @@ __device__ __forceinline__ void init_plane(S& s, const Params& p) {
   }
 }
 
+// Three waves per SIMD for the kernel of the many small environments, at 168
+// registers: 4096 x 15 takes 1.76 ms so, 1.98 with two (no spills), and took
+// 2.61 with four where three took 2.19.
 template <int K, int W, int NB>
 __global__ __launch_bounds__(64 * W, NB == 16 && W == 1 ? 3 : 2) void step_kernel(StepArgs g) {
   __shared__ Smem<K, W, NB> s;
@@ -2467,7 +2428,9 @@ hipError_t launch_valid(const ValidArgs& a, hipStream_t stream, int grid) {
 // Calls f(kernel tag) for the kernel of a contact class (128, 256 or 512
 // contacts: 2, 4 or 8 slots of row contacts per lane), a workgroup shape (1
 // or 2 waves per environment; the 512-contact class has one) and the largest
-// body count: 128 contacts and at most 16 boxes take the 16-box layout.
+// body count: 128 contacts and at most 16 boxes, which is what four lanes a
+// body leave room for, take the 16-box layout (4096 x 15 1.76 ms, 2.25 in the
+// 31-box layout; 1024 x 15 1.12 and 1.24; 64 x 9 0.88 and 0.98).
 template <int K_, int W_, int NB_>
 struct Shape {
   static constexpr int K = K_, W = W_, NB = NB_;
