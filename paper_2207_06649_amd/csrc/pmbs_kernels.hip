@@ -2308,8 +2308,9 @@ struct Frames {
 // sieves, a wave's own list of pairs packed after each: the pusher's two
 // horizontal axes, lane = action (the pusher's own radii formed once; most of
 // the pairs end here), then the other four face axes, then the nine edge axes,
-// lane = pair.  Workgroups loop over the envs (the count may come from device
-// memory).
+// lane = pair.  1024 x 21: 45 to 64 -> 19 us; 64 x 11: 32 -> 10.6, with a lane
+// per push walking all the boxes before.  Workgroups loop over the envs (the
+// count may come from device memory).
 constexpr int VALID_WAVES = PMBS_VALID_WORDS / 2, VALID_ACTIONS = 32 * PMBS_VALID_WORDS;
 struct ValidShared {
   Frames f;
