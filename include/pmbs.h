@@ -25,6 +25,9 @@
  *  - Input arrays in host memory are copied before the call returns; input
  *    arrays in device memory are read in place when the stream reaches the
  *    call, so they must stay valid until then.
+ *  - A pmbs_sim_step, pmbs_sim_collide or plain device-input rollout that the
+ *    caller captures in a graph of its own may be replayed on environments
+ *    loaded later, as many of them as at the capture and of any body counts.
  *  - One handle is used by one host thread at a time.
  */
 #ifndef PMBS_H

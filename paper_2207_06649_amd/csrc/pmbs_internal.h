@@ -133,7 +133,9 @@ int64_t work_weight(const pmbs_sim_t* sim, const int32_t* act_offset, int e);
 void share_pool(pmbs_sim_t* sim, const pmbs_sim_t* from);
 // waves per environment of a contact class under the launch plan
 int plan_waves(const pmbs_sim_t* sim, int max_contacts);
-// most bodies of the envs that a queued rollout gives the 128-contact kernel
+// most bodies that any env of a launch on the simulator's stream can have
+int launch_nb(const pmbs_sim_t* sim);
+// and of the envs that a queued rollout gives the 128-contact kernel
 int small_nb(const pmbs_sim_t* sim);
 int shape_index(int max_contacts, int max_nb);
 // workgroups of a persistent launch of the given contact class and shape

@@ -290,10 +290,12 @@ int class_grid(pmbs_sim_t* sim, int max_contacts, int blocks_per_cu, int waves, 
       sim->cus = prop.multiProcessorCount;
   }
   const int k = shape_index(max_contacts, max_nb), w = waves == 2 ? 1 : 0;
-  if (sim->occ[k][w] <= 0) {
-    const int o = step_blocks_per_cu(max_contacts, waves == 2 ? 2 : 1, max_nb);
-    sim->occ[k][w] = o > 0 ? o : 1;
-  }
+  // both layouts of a class at once: a call under capture may need the other one
+  if (sim->occ[k][w] <= 0)
+    for (int nb : {16, PMBS_MAX_BODIES_PER_ENV}) {
+      const int o = step_blocks_per_cu(max_contacts, waves == 2 ? 2 : 1, nb);
+      sim->occ[shape_index(max_contacts, nb)][w] = o > 0 ? o : 1;
+    }
   const int per_cu = blocks_per_cu > 0 && blocks_per_cu < sim->occ[k][w] ? blocks_per_cu : sim->occ[k][w];
   return sim->cus * per_cu;
 }
@@ -411,7 +413,18 @@ int class_split(const pmbs_sim_t* sim) {
   return sim->cfg.max_contacts == 128 ? PMBS_MAX_BODIES_PER_ENV : sim->plan.small_max_bodies;
 }
 
-int small_nb(const pmbs_sim_t* sim) { return std::min(class_split(sim), (int)sim->max_nb); }
+// The layout of a launch follows the environments that are loaded, but a
+// caller's graph may replay it after others were, which the kernels find in
+// device memory: under capture it follows what the simulator can hold.
+int launch_nb(const pmbs_sim_t* sim) {
+  if (sim->max_nb > 16 || !sim->stream) return sim->max_nb;   // the default stream is never captured
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(sim->stream, &cs) != hipSuccess) (void)hipGetLastError();
+  else if (cs == hipStreamCaptureStatusNone) return sim->max_nb;
+  return std::min((int)PMBS_MAX_BODIES_PER_ENV, sim->cfg.max_bodies);
+}
+
+int small_nb(const pmbs_sim_t* sim) { return std::min(class_split(sim), launch_nb(sim)); }
 
 int64_t work_weight(const pmbs_sim_t* sim, const int32_t* act_offset, int e) {
   const int h = act_offset[e + 1] - act_offset[e], nb = sim->host_offset[e + 1] - sim->host_offset[e];
@@ -705,7 +718,7 @@ pmbs_status pmbs_sim_step(pmbs_sim_t* sim, const float* push, int32_t push_is_de
   a.n_substeps = n_substeps;
   const int mc = sim->cfg.max_contacts, waves = plan_waves(sim, mc);
   hipError_t e = hipSuccess;
-  const int grid = class_grid(sim, mc, 0, waves, sim->max_nb);
+  const int nb = launch_nb(sim), grid = class_grid(sim, mc, 0, waves, nb);
   if (sim->plan.order != 0 && n_substeps > 0 && sim->n_envs > grid && grid >= 8) {
     // more envs than resident workgroups: a cost pass estimates each env's
     // work at its start pose, and persistent workgroups take the envs from
@@ -715,14 +728,14 @@ pmbs_status pmbs_sim_step(pmbs_sim_t* sim, const float* push, int32_t push_is_de
     // are d_ctl[16..23], which rollouts leave alone)
     StepArgs c = a;
     c.cost_key = sim->d_order + sim->cfg.max_envs;
-    e = launch_cost(c, mc, sim->stream, waves, sim->max_nb);
+    e = launch_cost(c, mc, sim->stream, waves, nb);
     if (e == hipSuccess) e = launch_order(c.cost_key, sim->n_envs, sim->d_order, sim->d_ctl + 16, sim->stream);
     a.order = sim->d_order;
     a.queue = sim->d_ctl + 16;
     a.xcd_queues = 1;
-    if (e == hipSuccess) e = launch_step_class(a, mc, sim->stream, grid, waves, sim->max_nb);
+    if (e == hipSuccess) e = launch_step_class(a, mc, sim->stream, grid, waves, nb);
   } else {
-    e = launch_step(a, mc, sim->stream, waves, sim->max_nb);
+    e = launch_step(a, mc, sim->stream, waves, nb);
   }
   if (e != hipSuccess) return hip_fail(e, "step launch");
   return PMBS_OK;
@@ -931,7 +944,7 @@ pmbs_status pmbs_sim_rollout_ex(pmbs_sim_t* sim, const int32_t* actions, const i
   ValidArgs va = valid_args(sim, a.child_slot);
   const ValidArgs* vap = (flags & PMBS_ROLLOUT_CHILD_VALID) && a.child_slot ? &va : nullptr;
   if (!use_queue) {
-    hipError_t e = launch_step(a, sim->cfg.max_contacts, sim->stream, plan_waves(sim, sim->cfg.max_contacts), sim->max_nb);
+    hipError_t e = launch_step(a, sim->cfg.max_contacts, sim->stream, plan_waves(sim, sim->cfg.max_contacts), launch_nb(sim));
     if (e == hipSuccess && vap) e = launch_valid(va, sim->stream);
     if (e != hipSuccess) return hip_fail(e, "rollout launch");
     return PMBS_OK;
@@ -941,8 +954,7 @@ pmbs_status pmbs_sim_rollout_ex(pmbs_sim_t* sim, const int32_t* actions, const i
   if (e != hipSuccess) return hip_fail(e, "stream creation");
   for (int mc : {128, 256, 512})
     if (mc <= sim->cfg.max_contacts)
-      for (int w : {1, 2})   // occupancy queries outside any capture
-        for (int nb : {small_nb(sim), (int)sim->max_nb}) (void)class_grid(sim, mc, 0, w, nb);
+      for (int w : {1, 2}) (void)class_grid(sim, mc, 0, w, sim->max_nb);  // occupancy queries outside any capture
   if (!(flags & PMBS_ROLLOUT_GRAPH)) {
     e = enqueue_queued(sim, a, sim->stream, true, counts[0], counts[1], vap);
     if (e != hipSuccess) return hip_fail(e, "rollout launch");
@@ -1042,7 +1054,7 @@ pmbs_status pmbs_sim_collide(pmbs_sim_t* sim, const float* push, int32_t push_is
   a.collide_only = 1;
   a.dbg_count = d_counts;
   a.dbg_contacts = d_contacts;
-  hipError_t e = launch_step(a, sim->cfg.max_contacts, sim->stream, 1, sim->max_nb);
+  hipError_t e = launch_step(a, sim->cfg.max_contacts, sim->stream, 1, launch_nb(sim));
   if (e != hipSuccess) return hip_fail(e, "collide launch");
   return PMBS_OK;
 }
