@@ -138,6 +138,9 @@ int launch_nb(const pmbs_sim_t* sim);
 // and of the envs that a queued rollout gives the 128-contact kernel
 int small_nb(const pmbs_sim_t* sim);
 int shape_index(int max_contacts, int max_nb);
+// resident workgroups per CU, as last looked up, of the kernel that a queued
+// rollout under this plan (not the one in force) runs a contact class with
+int resident_blocks(const pmbs_sim_t* sim, const pmbs_launch_plan& plan, int max_contacts);
 // workgroups of a persistent launch of the given contact class and shape
 int class_grid(pmbs_sim_t* sim, int max_contacts, int blocks_per_cu, int waves, int max_nb);
 // the queued rollout launches (all contact classes and fallbacks) on

@@ -426,6 +426,12 @@ int launch_nb(const pmbs_sim_t* sim) {
 
 int small_nb(const pmbs_sim_t* sim) { return std::min(class_split(sim), launch_nb(sim)); }
 
+int resident_blocks(const pmbs_sim_t* sim, const pmbs_launch_plan& plan, int max_contacts) {
+  const int split = sim->cfg.max_contacts == 128 ? PMBS_MAX_BODIES_PER_ENV : plan.small_max_bodies;
+  const int waves = max_contacts <= 128 ? plan.small_waves : max_contacts <= 256 ? plan.large_waves : 1;
+  return sim->occ[shape_index(max_contacts, std::min(split, launch_nb(sim)))][waves == 2 ? 1 : 0];
+}
+
 int64_t work_weight(const pmbs_sim_t* sim, const int32_t* act_offset, int e) {
   const int h = act_offset[e + 1] - act_offset[e], nb = sim->host_offset[e + 1] - sim->host_offset[e];
   return sim->plan.order == 0 ? h : (int64_t)h * (nb + 4);

@@ -222,8 +222,8 @@ pmbs_status pmbs_sim_autotune(pmbs_sim_t* sim, const int32_t* actions, const int
   shapes();
   thresholds();
   shapes();
-  // workgroups per CU of the chosen shapes (occupancy known from the runs above)
-  const int occ_s = sim->occ[shape_index(128, small_nb(sim))][win.small_waves == 2 ? 1 : 0], occ_l = sim->occ[1][win.large_waves == 2 ? 1 : 0];
+  // workgroups per CU of the chosen plan's kernels (known from the runs above)
+  const int occ_s = resident_blocks(sim, win, 128), occ_l = resident_blocks(sim, win, 256);
   for (int b = 1; b < occ_s; ++b) {
     pmbs_launch_plan p = win;
     p.small_blocks_per_cu = b;
