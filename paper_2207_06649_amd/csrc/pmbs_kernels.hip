@@ -495,6 +495,124 @@ __device__ __forceinline__ f3 warm_impulse(const S& s, int c, int nwarm, int n_e
   return l;
 }
 
+// Row contact c in registers, with its impulse of the previous substep; past
+// the last an absent contact of the table with itself: zero impulses.
+template <class S>
+__device__ __forceinline__ Contact begin_row(const S& s, int c, int n_rows, int nwarm, int n_extra, const Params& p) {
+  Contact q;
+  if (c < n_rows) {
+    prep_contact(s, c, p, &q);
+    const f3 l = warm_impulse(s, c, nwarm, n_extra);
+    q.ln = l.x;
+    q.lt1 = l.y;
+    q.lt2 = l.z;
+  } else {
+    const f3 z = mk(0, 0, 0);
+    q = Contact{S::PLANE | (S::PLANE << 8), z, z, z, z, z, 0, 0, 0, 0, 0, 0, 0, 0};
+  }
+  return q;
+}
+
+// The impulse rows (P, ra x P, rb x P) of the impulse R.
+template <class S>
+__device__ __forceinline__ void put_row(S& s, int c, const Contact& q, f3 R) {
+  st3(&s.u.imp[0][c], R);
+  st3(&s.u.imp[1][c], cross(q.ra, R));
+  st3(&s.u.imp[2][c], cross(q.rb, R));
+}
+
+// One iteration's update from the published velocities.
+template <class S>
+__device__ __forceinline__ void update_row(S& s, int c, Contact& q) {
+  const int a = q.ab & 255, bb = (q.ab >> 8) & 255;
+  const f3 va = xyz(s.vel[a]), ta = xyz(s.ang[a]), vb = xyz(s.vel[bb]), tb = xyz(s.ang[bb]);
+  const f3 wa = mk(ta.z, ta.x, ta.y), wb = mk(tb.z, tb.x, tb.y);
+  const f3 u = cross_add(wb, q.rb, vb) - cross_add(wa, q.ra, va);
+  const float ln = fmaxf(q.ln + q.kn * (q.vstar - dot(u, q.n)), 0.0f);
+  const float dln = ln - q.ln;
+  q.ln = ln;
+  float lt1 = q.lt1 - q.kt1 * dot(u, q.t1);
+  float lt2 = q.lt2 - q.kt2 * dot(u, q.t2);
+  const float lim = q.mu * ln, mag2 = lt1 * lt1 + lt2 * lt2;
+  const float sc = fminf(lim * rsq(mag2), 1.0f);
+  lt1 *= sc;
+  lt2 *= sc;
+  const float dl1 = lt1 - q.lt1, dl2 = lt2 - q.lt2;
+  q.lt1 = lt1;
+  q.lt2 = lt2;
+  put_row(s, c, q, fma3(q.n, dln, fma3(q.t1, dl1, q.t2 * dl2)));
+}
+
+// The substep's accumulated impulses by key, for the next one.
+template <class S>
+__device__ __forceinline__ void keep_row(S& s, int c, int n_rows, const Contact& q) {
+  if (c < n_rows) {
+    s.wkey[c] = contact_key<S>(q.ab);
+    s.wl[0][c] = q.ln;
+    s.wl[1][c] = q.lt1;
+    s.wl[2][c] = q.lt2;
+  }
+}
+
+// A wave's row contacts, a lane each: slots FIRST, FIRST + STEP, ... of 64
+// contacts.  RS of its slots are held in registers; the others, in the classes
+// of many contacts on one wave, in a lane's private memory, the next one's on
+// its way while one is updated.  exchange() orders the rows and velocities
+// against the other lanes' (of every wave that has part in them); sums(),
+// publish() and table() are the body lanes' part of an iteration.  Bound by the
+// chain of an iteration: velocities gathered, about 90 instructions a slot, rows
+// left in LDS and added by the bodies' lanes.  60 substeps of 1024 x 10 cubes in
+// two touching towers (73 rows), 128-contact class: two waves 1.69 -> 1.16 ms
+// against all rows on the lead wave, one wave 1.78 -> 1.49 with the sums below;
+// 1024 x 30 touching cubes (244 rows, 512-contact class) 10.3 -> 8.6 ms.
+template <int FIRST, int STEP, int RS, class S, class X, class Q, class V, class T>
+__device__ __forceinline__ void solve_rows(S& s, int lane, int n_rows, int nwarm, int n_extra, const Params& p, X exchange,
+                                           Q sums, V publish, T table) {
+  constexpr int N = S::C / 64 / STEP;   // the wave's slots
+  Contact ct[RS], more[N > RS ? N - RS : 1];
+  auto has = [&](int i) { return 64 * (FIRST + STEP * i) < n_rows; };
+  auto at = [&](int i) { return 64 * (FIRST + STEP * i) + lane; };
+  auto each_slot = [&](auto f) {
+#pragma unroll
+    for (int i = 0; i < RS; ++i)
+      if ((FIRST == 0 && i == 0) || has(i)) f(at(i), ct[i]);
+    if constexpr (N > RS) {
+#pragma unroll 1
+      for (int i = RS; i < N && has(i); ++i) f(at(i), more[i - RS]);
+    }
+  };
+  each_slot([&](int c, Contact& q) { q = begin_row(s, c, n_rows, nwarm, n_extra, p); });
+  exchange();   // the rows take the staging array's place
+  each_slot([&](int c, Contact& q) { put_row(s, c, q, fma3(q.n, q.ln, fma3(q.t1, q.lt1, q.t2 * q.lt2))); });
+  exchange();
+  sums();
+  for (int it = 0; it < p.iters; ++it) {
+    publish();
+    Contact next;
+    if constexpr (N > RS) {
+      if (has(RS)) next = more[0];
+    }
+    table();
+#pragma unroll
+    for (int i = 0; i < RS; ++i)
+      if ((FIRST == 0 && i == 0) || has(i)) update_row(s, at(i), ct[i]);
+    if constexpr (N > RS) {
+#pragma unroll 1
+      for (int i = RS; i < N && has(i); ++i) {
+        Contact q = next;
+        if (i + 1 < N && has(i + 1)) next = more[i + 1 - RS];
+        update_row(s, at(i), q);
+        more[i - RS].ln = q.ln;
+        more[i - RS].lt1 = q.lt1;
+        more[i - RS].lt2 = q.lt2;
+      }
+    }
+    exchange();   // the impulse rows
+    sums();
+  }
+  each_slot([&](int c, Contact& q) { keep_row(s, c, n_rows, q); });
+}
+
 // A row contact spread over four lanes: lane q of the quad has row q of its
 // frame (q = 0 normal, 1 and 2 tangents; impulse lam, effective mass k) and
 // component q of its vectors (lane 3 repeats lane 0 and is not read).
@@ -812,7 +930,7 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
   constexpr int C = S::C, PLANE = S::PLANE, MB = S::MB;
   constexpr int L = NB == 16 ? 4 : 2;   // lanes per body
   constexpr int TS = 4 / L;             // table contacts per lane
-  constexpr bool SPLIT = W > 1 && TS > 1;   // the second wave updates the row contacts
+  constexpr bool SPLIT = W > 1 && TS > 1;   // the second wave updates the quads of row contacts
   const Params& p = g.p;
   // opaque: what follows from the lane number is formed anew for each env
   // and substep; kept over them it fills the registers with addresses
@@ -821,7 +939,7 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
   const bool lead = wid == 0;
   // scalar where there are barriers on either side of its branch, which whole
   // waves then take
-  const bool row_wave = SPLIT ? __builtin_amdgcn_readfirstlane(wid) != 0 : !lead;
+  const bool row_wave = W > 1 && __builtin_amdgcn_readfirstlane(wid) != 0;
   const int b = (unsigned)lane / L, j = (unsigned)lane % L;
   const int base = g.env_offset[e];
   const int nb = g.env_offset[e + 1] - base;
@@ -1436,7 +1554,7 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
     }
     const int nc = nc_raw < C ? nc_raw : C;
     n_rows = n_rows < row_cap ? n_rows : row_cap;
-    if constexpr (SPLIT) n_rows = __builtin_amdgcn_readfirstlane(n_rows);
+    if constexpr (W > 1) n_rows = __builtin_amdgcn_readfirstlane(n_rows);
     if constexpr (COST) {
       // The work estimate of the env's push from its start pose; nothing else
       // is written.  A substep with row contacts costs about 2.6 times one
@@ -1510,30 +1628,36 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
       return;
     }
 
-    // the rest of the substep is the lead wave's, but for up to 16 row
-    // contacts of the 31-box layout: there the second wave prepares and
-    // updates them in quads while the lead updates its lanes' table contacts,
-    // two each (22 objects: 1100 -> 1000 cycles an iteration; rollouts of 256
-    // x 21 6.10 -> 5.94 ms).  With one table contact per lane, as in the
-    // 16-box layout, two barriers an iteration cost what the split gives
-    // (1024 x 15, two waves a SIMD: 1.12 -> 1.14 ms): no split there.
-    const bool split = SPLIT && n_rows > 0 && n_rows <= 16;
+    // The rest of the substep is the lead wave's, but for the row contacts that
+    // the second wave prepares and updates while the lead updates its lanes'
+    // table contacts.  Up to 16 of them it takes in quads, in the 31-box layout
+    // (22 objects: 1100 -> 1000 cycles an iteration; rollouts of 256 x 21 6.10 ->
+    // 5.94 ms); with one table contact per lane, as in the 16-box layout, two
+    // barriers an iteration cost what the split gives (1024 x 15, two waves a
+    // SIMD: 1.12 -> 1.14 ms): no split there.  Of more than 16 it takes every
+    // second slot of 64, the first among them.
+    const bool split = W > 1 && (n_rows > 16 || (SPLIT && n_rows > 0));
     if (row_wave) {
-      if constexpr (SPLIT) if (split) {
+      if constexpr (W > 1) if (split) {
         const int lane = opaque(threadIdx.x & 63);
         __syncthreads();   // the bodies' data and the contact counts
-        QuadContact qc = begin_quad(s, lane, n_rows, nwarm, n_extra, p);
-        wave_sync();
-        put_quad(s, lane, qc, qc.lam);
-        __syncthreads();
-        for (int it = 0; it < p.iters; ++it) {
-          __syncthreads();   // the iteration-start velocities
-          put_quad(s, lane, qc, update_quad(s, qc, []() {}));
-          __syncthreads();   // the impulse rows
+        if (n_rows > 16) {
+          solve_rows<0, 2, K / 2>(s, lane, n_rows, nwarm, n_extra, p, []() { __syncthreads(); }, []() {},
+                                  []() { __syncthreads(); }, []() {});
+        } else if constexpr (SPLIT) {
+          QuadContact qc = begin_quad(s, lane, n_rows, nwarm, n_extra, p);
+          wave_sync();
+          put_quad(s, lane, qc, qc.lam);
+          __syncthreads();
+          for (int it = 0; it < p.iters; ++it) {
+            __syncthreads();   // the iteration-start velocities
+            put_quad(s, lane, qc, update_quad(s, qc, []() {}));
+            __syncthreads();   // the impulse rows
+          }
+          keep_quad(s, lane, n_rows, qc);
         }
-        keep_quad(s, lane, n_rows, qc);
       }
-      if constexpr (SPLIT) nwarm = n_rows;
+      if constexpr (W > 1) nwarm = n_rows;
     } else {
     // world inverse inertia Iw^-1 = R diag(invI) R^T: diagonal, off-diagonal (xy, xz, yz)
     f3 md, mo;
@@ -1661,7 +1785,7 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
       corners = mask;
     }
 
-    if constexpr (SPLIT)
+    if constexpr (W > 1)
       if (split) __syncthreads();   // to the row wave
 
     // ---- 6. prep of the lanes' table contacts (an absent one has zero
@@ -1894,74 +2018,94 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
           keep_quad(s, lane, n_rows, qc);
         }
       } else {
-        // the first RS slots' contacts in registers; the others, which only
-        // towers and piles reach, in a lane's private memory, so that they
-        // cost no environment registers
-        constexpr int RS = NB == 16 ? 1 : 2;
-        Contact ct[RS], more[K > RS ? K - RS : 1];
-        auto each_slot = [&](auto f) {
+        // the same sums where a body has many rows: its lane's first 12
+        // entries stay in registers, a row's offset and bit 0 for a term to
+        // subtract, and are loaded in groups, all of a group in flight together
+        // (18 rows a body: 2000 -> 1000 cycles against one entry after the other)
+        constexpr int E = 12, G = 4;
+        unsigned entry[E];
+        bool group[E / G];   // some lane has an entry in the group
 #pragma unroll
-          for (int sl = 0; sl < RS; ++sl)
-            if (sl == 0 || 64 * sl < n_rows) f(64 * sl + lane, ct[sl]);
-          if constexpr (K > RS) {
-#pragma unroll 1
-            for (int sl = RS; 64 * sl < n_rows; ++sl) f(64 * sl + lane, more[sl - RS]);
+        for (int u = 0; u < E; ++u) {
+          if (u % G == 0) group[u / G] = __ballot(n_inc > k0 + 2 * u) != 0ull;
+          entry[u] = zrow | 1u;
+          if (group[u / G]) {
+            const int i = k0 + 2 * u;
+            const unsigned code = s.inc[inc0 + min(i, max(n_inc - 1, 0))];
+            if (i < n_inc) entry[u] = (ang_lane ? row_ang(code) : row_lin(code)) | (~code & 1u);
           }
-        };
-        each_slot([&](int c, Contact& q) {
-          if (c < n_rows) {
-            prep_contact(s, c, p, &q);
-            const f3 l = warm_impulse(s, c, nwarm, n_extra);
-            q.ln = l.x;
-            q.lt1 = l.y;
-            q.lt2 = l.z;
-          } else {
-            const f3 z = mk(0, 0, 0);
-            q = Contact{PLANE | (PLANE << 8), z, z, z, z, z, 0, 0, 0, 0, 0, 0, 0, 0};
-          }
-        });
-        wave_sync();
-        auto put_rows = [&](int c, const Contact& q, f3 R) {
-          st3(&s.u.imp[0][c], R);
-          st3(&s.u.imp[1][c], cross(q.ra, R));
-          st3(&s.u.imp[2][c], cross(q.rb, R));
-        };
-        each_slot([&](int c, Contact& q) { put_rows(c, q, fma3(q.n, q.ln, fma3(q.t1, q.lt1, q.t2 * q.lt2))); });
-        wave_sync();
-        sums();
-        for (int it = 0; it < p.iters; ++it) {
-          publish();
-          table_update();
-          each_slot([&](int c, Contact& q) {
-            const int a = q.ab & 255, bb = (q.ab >> 8) & 255;
-            const f3 va = xyz(s.vel[a]), ta = xyz(s.ang[a]), vb = xyz(s.vel[bb]), tb = xyz(s.ang[bb]);
-            const f3 wa = mk(ta.z, ta.x, ta.y), wb = mk(tb.z, tb.x, tb.y);
-            const f3 u = cross_add(wb, q.rb, vb) - cross_add(wa, q.ra, va);
-            const float ln = fmaxf(q.ln + q.kn * (q.vstar - dot(u, q.n)), 0.0f);
-            const float dln = ln - q.ln;
-            q.ln = ln;
-            float lt1 = q.lt1 - q.kt1 * dot(u, q.t1);
-            float lt2 = q.lt2 - q.kt2 * dot(u, q.t2);
-            const float lim = q.mu * ln, mag2 = lt1 * lt1 + lt2 * lt2;
-            const float sc = fminf(lim * rsq(mag2), 1.0f);
-            lt1 *= sc;
-            lt2 *= sc;
-            const float dl1 = lt1 - q.lt1, dl2 = lt2 - q.lt2;
-            q.lt1 = lt1;
-            q.lt2 = lt2;
-            put_rows(c, q, fma3(q.n, dln, fma3(q.t1, dl1, q.t2 * dl2)));
-          });
-          wave_sync();   // the impulse rows
-          sums();
         }
-        each_slot([&](int c, Contact& q) {
-          if (c < n_rows) {
-            s.wkey[c] = contact_key<S>(q.ab);
-            s.wl[0][c] = q.ln;
-            s.wl[1][c] = q.lt1;
-            s.wl[2][c] = q.lt2;
+        const bool longer = __ballot(n_inc > k0 + 2 * E) != 0ull;
+        auto sums_many = [&]() {
+          f3 lin, ang, a;
+          f3 r[G], t[L == 2 ? G : 1];
+          auto load = [&](int u0) {
+#pragma unroll
+            for (int u = 0; u < G; ++u) {
+              const unsigned off = entry[u0 + u] & ~1u;
+              r[u] = row_at(off);
+              if constexpr (L == 2)
+                t[u] = row_at(off == zrow ? zrow : off + (2u - (entry[u0 + u] & 1u)) * (unsigned)(C * 16));
+            }
+          };
+          auto add = [&](int u0) {
+#pragma unroll
+            for (int u = 0; u < G; ++u) {
+              const float sg = __uint_as_float(0x3f800000u | entry[u0 + u] << 31);
+              if constexpr (L == 4) {
+                a = add_signed(a, sg, r[u]);
+              } else {
+                lin = add_signed(lin, sg, r[u]);
+                ang = add_signed(ang, sg, t[u]);
+              }
+            }
+          };
+          load(0);
+          __builtin_amdgcn_sched_barrier(0);
+          table_sums(&lin, &ang);   // while the loads are in flight
+          a = sel(ang_lane, ang, lin);
+          add(0);
+#pragma unroll
+          for (int u0 = G; u0 < E; u0 += G)
+            if (group[u0 / G]) {
+              load(u0);
+              add(u0);
+            }
+          if (longer)
+            for (int i = k0 + 2 * E; i < n_inc; i += 2) {
+              const unsigned code = s.inc[inc0 + i];
+              const float sg = (code & 1u) ? 1.0f : -1.0f;
+              if constexpr (L == 4) {
+                a = add_signed(a, sg, row_at(ang_lane ? row_ang(code) : row_lin(code)));
+              } else {
+                lin = add_signed(lin, sg, row_at(row_lin(code)));
+                ang = add_signed(ang, sg, row_at(row_ang(code)));
+              }
+            }
+          if constexpr (L == 4) {
+            a = a + quad<Q_XOR1>(a);
+            apply(quad<Q_LOW>(a), quad<Q_HIGH>(a));
+          } else {
+            apply(lin + quad<Q_XOR1>(lin), ang + quad<Q_XOR1>(ang));
           }
-        });
+        };
+        if constexpr (W == 1) {
+          // the first slots in registers (the 512-contact class, which LDS
+          // holds to a wave per SIMD, has them for all its slots)
+          constexpr int RS = NB == 16 ? 1 : K == 8 ? 8 : 2;
+          solve_rows<0, 1, RS>(s, lane, n_rows, nwarm, n_extra, p, []() { wave_sync(); }, sums_many, publish, table_update);
+        } else {
+          solve_rows<1, 2, K / 2>(s, lane, n_rows, nwarm, n_extra, p, []() { __syncthreads(); }, sums_many, [&]() {
+            publish();
+            __syncthreads();
+            hold(v);   // as above
+            hold(w);
+          }, [&]() {
+            table_update();
+#pragma unroll
+            for (int ts = 0; ts < TS; ++ts) hold(P[ts]);
+          });
+        }
       }
     }
     nwarm = n_rows;
