@@ -24,12 +24,13 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "pmbs_kernels.h"
 
 namespace pmbs {
 
 constexpr int MAXB = 32;             // boxes (<= 31) + the pusher
-constexpr int GROUPS = 4;            // pairs per narrowphase pass (16-lane groups)
 constexpr int POLY = 8;              // clip polygon capacity
 // Growth of the AABBs of the broadphase's near list (m).  More lengthens the
 // list, less has it listed anew more often: 700 x 27 1.39 to 1.40 ms with 3 mm,
@@ -159,7 +160,7 @@ struct Smem {
         struct {
           float4 lo[MB], hi[MB];     // AABBs: min corner and pos's fourth, max corner
         } box;
-        float clip[W][2][POLY][3][GROUPS];   // each wave's clip polygons
+        float clip[W][2][POLY][3][8];   // each wave's clip polygons, of up to eight pairs
         unsigned incm[NOBJ][2 * K];  // incidence build: contact bit masks per body
         float4 lam[MB * 4];          // table impulses (n, t1, t2) and corner mask of a changed corner set
       } x;
@@ -321,19 +322,29 @@ __device__ __forceinline__ void cl_put(S& s, int wid, int buf, int i, int grp, f
   c[2][grp] = v.z;
 }
 
-// Value of lane K of each 16-lane row (DPP row broadcast).
-template <int K>
-__device__ __forceinline__ float row_value(float v) {
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x150 + K, 0xf, 0xf, true));
+// Value of lane K of each group of LP = 16 or 8 lanes (DPP row broadcast; of
+// eight lanes, each half of a row takes its own lane K).
+template <int LP, int K>
+__device__ __forceinline__ float group_value(float v) {
+  const int i = __float_as_int(v);
+  if constexpr (LP == 16) return __int_as_float(__builtin_amdgcn_mov_dpp(i, 0x150 + K, 0xf, 0xf, true));
+  const int lower = __builtin_amdgcn_update_dpp(i, i, 0x150 + K, 0xf, 0x3, true);
+  return __int_as_float(__builtin_amdgcn_update_dpp(lower, i, 0x150 + (K + 8) % 16, 0xf, 0xc, true));
 }
 
-// The lane before in each 16-lane row, lane 0 taking lane 15: DPP row_ror:1.
-__device__ __forceinline__ float row_prev(float v) {
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x121, 0xf, 0xf, true));
+// The lane before in each group, lane 0 taking the last: DPP row_ror:1, and
+// row_ror:9 for the first lanes of eight.
+template <int LP>
+__device__ __forceinline__ float group_prev(float v, bool first) {
+  const int i = __float_as_int(v);
+  const int prev = __builtin_amdgcn_mov_dpp(i, 0x121, 0xf, 0xf, true);
+  if constexpr (LP == 16) return __int_as_float(prev);
+  const int wrap = __builtin_amdgcn_mov_dpp(i, 0x129, 0xf, 0xf, true);
+  return __int_as_float(first ? wrap : prev);
 }
 
 // One Sutherland-Hodgman stage against sign * ((x - f).dir) - h <= 0 for
-// the polygons of all four groups at once, point i of a group's polygon
+// the polygons of all groups of LP lanes at once, point i of a group's polygon
 // in lane i of the group (lanes past the last point, lanes 8-15 too, hold copies
 // of it).
 // Lane i handles the edge from point i-1 (the last point for i = 0) to
@@ -341,8 +352,8 @@ __device__ __forceinline__ float row_prev(float v) {
 // point i if inside, at its rank among the group's emissions; at most POLY
 // points are kept.  Called by the whole wave.  Copies in all sixteen lanes make
 // the point before one DPP move, also for lane 0 (1024 x 15: 1.12 -> 1.11 ms
-// against two moves and a select within eight lanes).
-template <class S>
+// against the two moves and the select of eight lanes).
+template <int LP, class S>
 __device__ __forceinline__ int clip_group(S& s, f3* P, int n, f3 f, f3 dir, float sign, float h, int buf,
                                           int grp, int gl, int lane, int wid) {
   const float dc = sign * dot(*P - f, dir) - h;
@@ -350,13 +361,14 @@ __device__ __forceinline__ int clip_group(S& s, f3* P, int n, f3 f, f3 dir, floa
   // point is kept in place, so the stage changes nothing
   if (__ballot(gl < n && !(dc <= 0.0f)) == 0ull) return n;
   // the previous point, for lane 0 the last lane's copy of the last
-  const f3 Pp = mk(row_prev(P->x), row_prev(P->y), row_prev(P->z));
-  const float dp = row_prev(dc);
+  const bool first = gl == 0;
+  const f3 Pp = mk(group_prev<LP>(P->x, first), group_prev<LP>(P->y, first), group_prev<LP>(P->z, first));
+  const float dp = group_prev<LP>(dc, first);
   const bool live = gl < n;
   const bool in_c = dc <= 0.0f, in_p = dp <= 0.0f;
   const bool emit_x = live && (in_c != in_p), emit_c = live && in_c;
   const unsigned long long mx = __ballot(emit_x), mc = __ballot(emit_c);
-  const unsigned long long gm = 0xffffull << (16 * grp), below = ((1ull << lane) - 1ull) & gm;
+  const unsigned long long gm = ((1ull << LP) - 1ull) << (LP * grp), below = ((1ull << lane) - 1ull) & gm;
   const int q = __popcll(mx & below) + __popcll(mc & below);
   const int m = __popcll(mx & gm) + __popcll(mc & gm);
   if (emit_x && q < POLY) cl_put(s, wid, buf, q, grp, fma3(*P - Pp, dp * rcp(dp - dc), Pp));
@@ -1377,26 +1389,26 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
     int n_rows = n_extra;
 
     // ---- 4b. box-box and pusher-box contacts, candidate pairs in
-    // lexicographic order.  Four pairs per pass, 16 lanes each: lane k
-    // evaluates candidate axis k (0-2 faces of A, 3-5 faces of B, 6-14 edge
-    // crosses A_i x B_j), one evaluation for all fifteen; clipping follows only
-    // when some pair of the pass has no axis that keeps it apart.  Bound by the
-    // pass's chain of LDS round trips and dependent instructions: about 1000
-    // cycles of a lone wave, and 2000 more with a contact to clip, so that
-    // listing the pairs that a face axis separates beforehand, eight lanes a
-    // pair, takes longer than it saves once those that stay apart are no
-    // candidates (700 x 27: 1.38 ms with such a sieve, 1.35 without; against
-    // eight lanes a pair for the fifteen axes, before: 1.67 -> 1.52 ms).  With W
-    // waves a round is W passes, wave w taking pairs r0 + 4 w ..; the round's
-    // contacts keep the order.
-    for (int r0 = 0; r0 < n_cand; r0 += GROUPS * W) {
+    // lexicographic order, a pass of four pairs (LP = 16 lanes each) or of eight
+    // (LP = 8): lane k evaluates candidate axis k (0-2 faces of A, 3-5 faces of
+    // B, 6-14 edge crosses A_i x B_j) and, of eight lanes, axis k + 8; clipping
+    // follows only when some pair of the pass has no axis that keeps it apart.
+    // With W waves a round is W passes, wave w taking the w-th; the round's
+    // contacts keep the order.  Bound by the pass's chain of LDS round trips and
+    // dependent instructions: about 1000 cycles of a lone wave for the axes, and
+    // 2000 more with a contact to clip, so that listing the pairs that a face
+    // axis separates beforehand, eight lanes a pair, takes longer than it saves
+    // once those that stay apart are no candidates (700 x 27: 1.38 ms with such a
+    // sieve, 1.35 without).
+    auto narrow_pass = [&](auto lanes_per_pair, int r0) {
+      constexpr int LP = decltype(lanes_per_pair)::value, GROUPS = 64 / LP;
       const int ln = opaque(lane);
-      const int grp = ln >> 4, gl = ln & 15;
+      const int grp = ln / LP, gl = ln % LP;
       const int pi = r0 + GROUPS * wid + grp;
       const bool has = pi < n_cand;
       const unsigned pr = has ? s.pairs[pi] : 0u;
       const int ia = pr >> 8, ib = pr & 255;
-      const unsigned long long gm = 0xffffull << (16 * grp);
+      const unsigned long long gm = ((1ull << LP) - 1ull) << (LP * grp);
       bool keep = false, face = false;
       f3 P = mk(0, 0, 0), nref = mk(0, 0, 1), n = mk(0, 0, 0);
       float psep = 0.0f, bs = 0.0f;
@@ -1404,22 +1416,30 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
       {
         const Box A = load_box(s, ia), B = load_box(s, ib);
         const f3 d = B.c - A.c;
-        // axes i of A and j of B by lane, two bits each: i 0 1 2 - - - 0 0 0 1
-        // 1 1 2 2 2 -, j - - - 0 1 2 0 1 2 0 1 2 0 1 2 -
-        const f3 ua = lds_axis(s, ia, (0x2a540024u >> (2 * gl)) & 3u);
-        const f3 ub = lds_axis(s, ib, (0x24924900u >> (2 * gl)) & 3u);
-        const f3 v = cross(ua, ub);
-        const float l2 = dot(v, v);
-        const bool edge = gl >= 6 && gl < 15 && l2 >= p.edge_eps * p.edge_eps;
-        const f3 L = sel(gl < 3, ua, sel(gl < 6, ub, v * rsq(l2)));
-        const float sv = fabsf(dot(d, L)) - radius_along(A, L) - radius_along(B, L);
-        const bool ok = gl < 6 || edge;
-        const bool out = (__ballot(ok && sv > p.margin) & gm) != 0ull;
+        struct Candidate {
+          f3 L;
+          float sv;
+          bool edge;   // a usable edge axis
+        };
+        auto candidate = [&](int k) {
+          // axes i of A and j of B by k, two bits each: i 0 1 2 - - - 0 0 0 1
+          // 1 1 2 2 2 -, j - - - 0 1 2 0 1 2 0 1 2 0 1 2 -
+          const f3 ua = lds_axis(s, ia, (0x2a540024u >> (2 * k)) & 3u);
+          const f3 ub = lds_axis(s, ib, (0x24924900u >> (2 * k)) & 3u);
+          const f3 v = cross(ua, ub);
+          const float l2 = dot(v, v);
+          const f3 L = sel(k < 3, ua, sel(k < 6, ub, v * rsq(l2)));
+          return Candidate{L, fabsf(dot(d, L)) - radius_along(A, L) - radius_along(B, L),
+                           k >= 6 && k < 15 && l2 >= p.edge_eps * p.edge_eps};
+        };
+        const Candidate q0 = candidate(gl), q1 = LP == 8 ? candidate(gl + 8) : q0;
+        const bool over = ((gl < 6 || q0.edge) && q0.sv > p.margin) || (LP == 8 && q1.edge && q1.sv > p.margin);
+        const bool out = (__ballot(over) & gm) != 0ull;
         // the contact axis: the candidates in order, the kept one replaced
         // only by a later one that exceeds it by tau_face (faces) or tau_edge
         // (edges); the edges are gone through only when one exceeds the
         // faces' choice
-        bs = row_value<0>(sv);
+        bs = group_value<LP, 0>(q0.sv);
         best = 0;
         auto scan = [&](float sk, int k, float tau) {
           if (sk > bs + tau) {
@@ -1427,33 +1447,35 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
             best = k;
           }
         };
-        scan(row_value<1>(sv), 1, p.tau_face);
-        scan(row_value<2>(sv), 2, p.tau_face);
-        scan(row_value<3>(sv), 3, p.tau_face);
-        scan(row_value<4>(sv), 4, p.tau_face);
-        scan(row_value<5>(sv), 5, p.tau_face);
+        scan(group_value<LP, 1>(q0.sv), 1, p.tau_face);
+        scan(group_value<LP, 2>(q0.sv), 2, p.tau_face);
+        scan(group_value<LP, 3>(q0.sv), 3, p.tau_face);
+        scan(group_value<LP, 4>(q0.sv), 4, p.tau_face);
+        scan(group_value<LP, 5>(q0.sv), 5, p.tau_face);
         // a face axis keeps the boxes apart for a while (but the first
         // substep's orientations may not be unit quaternions yet)
         if (has && gl == 0 && bs > gap0 && k > 0)
           s.apart[number_of(ia, ib, n_obj)] = apart_until(bs, s.pos[ia].w + s.pos[ib].w);
-        if (__ballot(has && edge && sv > bs + p.tau_edge) != 0ull) {
-          const float se = edge ? sv : -INFINITY;
-          scan(row_value<6>(se), 6, p.tau_edge);
-          scan(row_value<7>(se), 7, p.tau_edge);
-          scan(row_value<8>(se), 8, p.tau_edge);
-          scan(row_value<9>(se), 9, p.tau_edge);
-          scan(row_value<10>(se), 10, p.tau_edge);
-          scan(row_value<11>(se), 11, p.tau_edge);
-          scan(row_value<12>(se), 12, p.tau_edge);
-          scan(row_value<13>(se), 13, p.tau_edge);
-          scan(row_value<14>(se), 14, p.tau_edge);
+        const float least = bs + p.tau_edge;
+        if (__ballot(has && ((q0.edge && q0.sv > least) || (LP == 8 && q1.edge && q1.sv > least))) != 0ull) {
+          const float e0 = q0.edge ? q0.sv : -INFINITY, e1 = LP == 8 ? (q1.edge ? q1.sv : -INFINITY) : e0;
+          scan(group_value<LP, 6>(e0), 6, p.tau_edge);
+          scan(group_value<LP, 7>(e0), 7, p.tau_edge);
+          scan(group_value<LP, 8 % LP>(e1), 8, p.tau_edge);
+          scan(group_value<LP, 9 % LP>(e1), 9, p.tau_edge);
+          scan(group_value<LP, 10 % LP>(e1), 10, p.tau_edge);
+          scan(group_value<LP, 11 % LP>(e1), 11, p.tau_edge);
+          scan(group_value<LP, 12 % LP>(e1), 12, p.tau_edge);
+          scan(group_value<LP, 13 % LP>(e1), 13, p.tau_edge);
+          scan(group_value<LP, 14 % LP>(e1), 14, p.tau_edge);
         }
         // every lane of the group takes the kept axis from its lane, pointing from A to B
-        const int from = ((ln & 48) + best) << 2;
+        const int from = ((ln & (64 - LP)) + best % LP) << 2;
         auto take = [&](float x) {
           return __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(x)));
         };
-        const f3 Lb = mk(take(L.x), take(L.y), take(L.z));
+        const f3 Lo = LP == 8 ? sel(best < 8, q0.L, q1.L) : q0.L;
+        const f3 Lb = mk(take(Lo.x), take(Lo.y), take(Lo.z));
         if (!has || out) best = -1;
         else n = sel(dot(d, Lb) >= 0.0f, Lb, neg(Lb));
       }
@@ -1504,10 +1526,10 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
           P = fc + (ep * spp + eq * sqq);
           np = 4;
         }
-        np = clip_group(s, &P, np, fref, u, 1.0f, hu, 0, grp, gl, lane, wid);
-        np = clip_group(s, &P, np, fref, u, -1.0f, hu, 1, grp, gl, lane, wid);
-        np = clip_group(s, &P, np, fref, w, 1.0f, hw, 0, grp, gl, lane, wid);
-        np = clip_group(s, &P, np, fref, w, -1.0f, hw, 1, grp, gl, lane, wid);
+        np = clip_group<LP>(s, &P, np, fref, u, 1.0f, hu, 0, grp, gl, lane, wid);
+        np = clip_group<LP>(s, &P, np, fref, u, -1.0f, hu, 1, grp, gl, lane, wid);
+        np = clip_group<LP>(s, &P, np, fref, w, 1.0f, hw, 0, grp, gl, lane, wid);
+        np = clip_group<LP>(s, &P, np, fref, w, -1.0f, hw, 1, grp, gl, lane, wid);
         // contacts: kept polygon points (face) or one edge-edge point
         psep = dot(nref, P - fref);
         keep = face ? (gl < np && psep <= p.margin) : (best >= 6 && gl == 0);
@@ -1542,7 +1564,16 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
         }
       }
       n_rows += round_total;
-    }
+    };
+    // Up to one pass of sixteen lanes a pair per wave takes that, the shorter
+    // chain (4096 x 15 1.66 ms, 1.70 with eight lanes always); more go eight to
+    // a pass, which takes hardly longer (60 substeps of 1024 x 8 touching cubes,
+    // 16 pairs: 1.12 -> 0.95 ms; 1024 x 30 in a pile, 138: 14.8 -> 11.6; 700 x 27
+    // 1.33 -> 1.24).
+    if (n_cand > 4 * W)
+      for (int r0 = 0; r0 < n_cand; r0 += 8 * W) narrow_pass(std::integral_constant<int, 8>{}, r0);
+    else if (n_cand > 0)
+      narrow_pass(std::integral_constant<int, 16>{}, 0);
     const int nc_raw = n_table + n_rows - n_extra;
     if (nc_raw > C) {
       status |= PMBS_ENV_CONTACT_OVERFLOW;
