@@ -46,11 +46,16 @@ struct pmbs_sim {
   // internal streams and events for the concurrent class launches and graph capture
   hipStream_t side = nullptr, cap = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t graph_exec = nullptr;
-  pmbs::StepArgs graph_args;
-  pmbs_launch_plan graph_plan;
-  int graph_valid = 0;   // the captured sequence ends with the children's validity launch
+  // captured rollouts, by graph_index: one per set of kernels, so that batches
+  // that need one set and the other in turn are not captured each time (32 x 12
+  // and 32 x 18 boxes, 10 substeps, 256 contacts: 303 us a rollout so, 210 kept)
+  struct Captured {
+    hipGraph_t graph = nullptr;
+    hipGraphExec_t exec = nullptr;
+    pmbs::StepArgs args;
+    pmbs_launch_plan plan;
+    int valid = 0;   // the sequence ends with the children's validity launch
+  } captured[2];
   // pinned staging of host rollout inputs: two buffers used in turn, each
   // reusable once the event behind its last uploads has passed
   char* h_stage[2] = {nullptr, nullptr};
@@ -61,7 +66,6 @@ struct pmbs_sim {
   int32_t n_envs, n_bodies;
   std::vector<int32_t> host_offset;
   int32_t max_nb = 0;         // most bodies of any env of host_offset
-  int graph_small_nb = 0;     // most bodies of the captured 128-contact kernel's envs
   bool pool_layout = false;   // envs live only in pool slots, body constants at d_bc_base rows
   ~pmbs_sim();
 };
@@ -138,6 +142,9 @@ int launch_nb(const pmbs_sim_t* sim);
 // and of the envs that a queued rollout gives the 128-contact kernel
 int small_nb(const pmbs_sim_t* sim);
 int shape_index(int max_contacts, int max_nb);
+// which kernels' layouts a queued rollout takes: 1 when the 128-contact one is
+// that for more than 16 bodies
+int graph_index(const pmbs_sim_t* sim);
 // resident workgroups per CU, as last looked up, of the kernel that a queued
 // rollout under this plan (not the one in force) runs a contact class with
 int resident_blocks(const pmbs_sim_t* sim, const pmbs_launch_plan& plan, int max_contacts);

@@ -426,6 +426,8 @@ int launch_nb(const pmbs_sim_t* sim) {
 
 int small_nb(const pmbs_sim_t* sim) { return std::min(class_split(sim), launch_nb(sim)); }
 
+int graph_index(const pmbs_sim_t* sim) { return small_nb(sim) > 16 ? 1 : 0; }
+
 int resident_blocks(const pmbs_sim_t* sim, const pmbs_launch_plan& plan, int max_contacts) {
   const int split = sim->cfg.max_contacts == 128 ? PMBS_MAX_BODIES_PER_ENV : plan.small_max_bodies;
   const int waves = max_contacts <= 128 ? plan.small_waves : max_contacts <= 256 ? plan.large_waves : 1;
@@ -487,8 +489,10 @@ pmbs_sim::~pmbs_sim() {
     if (h_stage[k]) (void)hipHostFree(h_stage[k]);
     if (ev_stage[k]) (void)hipEventDestroy(ev_stage[k]);
   }
-  if (graph_exec) (void)hipGraphExecDestroy(graph_exec);
-  if (graph) (void)hipGraphDestroy(graph);
+  for (Captured& c : captured) {
+    if (c.exec) (void)hipGraphExecDestroy(c.exec);
+    if (c.graph) (void)hipGraphDestroy(c.graph);
+  }
   if (ev_fork) (void)hipEventDestroy(ev_fork);
   if (ev_join) (void)hipEventDestroy(ev_join);
   if (side) (void)hipStreamDestroy(side);
@@ -967,13 +971,13 @@ pmbs_status pmbs_sim_rollout_ex(pmbs_sim_t* sim, const int32_t* actions, const i
     return PMBS_OK;
   }
   const int with_valid = vap ? 1 : 0;
-  if (!sim->graph_exec || std::memcmp(&sim->graph_args, &a, sizeof a) != 0 ||
-      std::memcmp(&sim->graph_plan, &sim->plan, sizeof sim->plan) != 0 || sim->graph_valid != with_valid ||
-      (sim->graph_small_nb > 16) != (small_nb(sim) > 16)) {
-    if (sim->graph_exec) (void)hipGraphExecDestroy(sim->graph_exec);
-    if (sim->graph) (void)hipGraphDestroy(sim->graph);
-    sim->graph_exec = nullptr;
-    sim->graph = nullptr;
+  auto& cap = sim->captured[graph_index(sim)];
+  if (!cap.exec || std::memcmp(&cap.args, &a, sizeof a) != 0 ||
+      std::memcmp(&cap.plan, &sim->plan, sizeof sim->plan) != 0 || cap.valid != with_valid) {
+    if (cap.exec) (void)hipGraphExecDestroy(cap.exec);
+    if (cap.graph) (void)hipGraphDestroy(cap.graph);
+    cap.exec = nullptr;
+    cap.graph = nullptr;
     e = hipStreamBeginCapture(sim->cap, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return hip_fail(e, "graph capture begin");
     const hipError_t ce = enqueue_queued(sim, a, sim->cap, false, 0, 0, vap);
@@ -983,18 +987,17 @@ pmbs_status pmbs_sim_rollout_ex(pmbs_sim_t* sim, const int32_t* actions, const i
       if (graph) (void)hipGraphDestroy(graph);
       return hip_fail(ce != hipSuccess ? ce : e, "graph capture");
     }
-    sim->graph = graph;
-    e = hipGraphInstantiate(&sim->graph_exec, graph, nullptr, nullptr, 0);
+    cap.graph = graph;
+    e = hipGraphInstantiate(&cap.exec, graph, nullptr, nullptr, 0);
     if (e != hipSuccess) {
-      sim->graph_exec = nullptr;
+      cap.exec = nullptr;
       return hip_fail(e, "graph instantiate");
     }
-    sim->graph_args = a;
-    sim->graph_plan = sim->plan;
-    sim->graph_valid = with_valid;
-    sim->graph_small_nb = small_nb(sim);
+    cap.args = a;
+    cap.plan = sim->plan;
+    cap.valid = with_valid;
   }
-  e = hipGraphLaunch(sim->graph_exec, sim->stream);
+  e = hipGraphLaunch(cap.exec, sim->stream);
   if (e != hipSuccess) return hip_fail(e, "graph launch");
   return PMBS_OK;
 }

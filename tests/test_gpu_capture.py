@@ -69,3 +69,37 @@ def test_callers_graph_of_a_step_serves_other_body_counts(pm, waves, spare):
             load(k)
             graph.replay()
             assert same(result(), want[k]), loads[k]
+
+
+@pytest.mark.parametrize("contacts,waves", [(128, 1), (128, 2), (256, 1), (512, 2)])
+def test_captured_rollouts_serve_other_body_counts(pm, contacts, waves):
+    """Rollouts of the same launch arguments on one simulator, the largest
+    environment at most 16 boxes, then more, then fewer again: the kernels
+    captured for one load are not replayed on the other, and both sets of
+    kernels are kept.  Every replay is bit for bit the eager rollout of a fresh
+    simulator."""
+    import torch
+    loads = [(12, 16, 3), (17, 20, 3), (15, 16, 8), (18, 5, 30), (31, 2, 16), (16, 16, 16)]
+    E, H = 3, 2
+    off = np.array([0, 2, 4, 6], np.int32)
+    sim = pm.Sim(max_envs=E, max_bodies=64, max_contacts=contacts, max_horizon=H)
+    rew = torch.zeros((E, H), dtype=torch.float32, device="cuda:0")
+    cnt = torch.zeros(E, dtype=torch.int32, device="cuda:0")
+
+    def roll(s, k, flags, rewards=None, counts=None):
+        b = batch(10 * k, loads[k])
+        s.set_launch_plan(small_max_bodies=31, small_waves=waves, large_waves=waves)
+        s.load(b)
+        acts = np.array([8 * (i % n) + 3 * i % 8 for n in loads[k] for i in range(2)], np.int32)
+        got = s.rollout(acts, off, np.zeros(E, np.int32), n_substeps=20, max_h=H,
+                        flags=flags | pm.ROLLOUT_WRITE_STATE, rewards=rewards, counts=counts)
+        return got[0].copy(), got[1].copy(), s.get_state(), s.env_status()
+
+    want = [roll(pm.Sim(max_envs=E, max_bodies=64, max_contacts=contacts, max_horizon=H), k, pm.ROLLOUT_QUEUE)
+            for k in range(len(loads))]
+    for turn in range(3):
+        for k in range(len(loads)):
+            rew.fill_(-1.0)
+            cnt.zero_()
+            got = roll(sim, k, pm.ROLLOUT_QUEUE | pm.ROLLOUT_GRAPH, rew, cnt)
+            assert same(got, want[k]), (turn, loads[k])
