@@ -150,8 +150,8 @@ pmbs_status pmbs_sim_step(pmbs_sim_t* sim, const float* push, int32_t push_is_de
                                       (order and contact classes per the launch plan) */
 #define PMBS_ROLLOUT_GRAPH 4       /* with PMBS_ROLLOUT_QUEUE: replay the launches as one captured
                                       hipGraph (captured on first use and again whenever the
-                                      launch arguments or the plan change; one is kept for
-                                      environments of at most 16 bodies and one for larger) */
+                                      launch arguments or the plan change; kept apart by
+                                      whether an environment has more than 16 bodies) */
 #define PMBS_ROLLOUT_CHILD_VALID 8 /* an env with a child slot whose first push was valid writes
                                       the start-pose validity words of the child's state to the
                                       simulator's validity buffer (pmbs_sim_push_valid) */

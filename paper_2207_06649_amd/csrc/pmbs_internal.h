@@ -39,9 +39,9 @@ struct pmbs_sim {
   float* d_x_rewards;      // [max_envs][max_horizon] extra simulations' rewards (planner, server)
   int32_t* d_x_counts;     // [max_envs]
   uint32_t* d_valid;       // [max_envs][PMBS_VALID_WORDS] start-pose validity words
-  // CUs; resident blocks per CU of the kernels by shape_index (128 contacts
-  // with the 16-box layout, 256, 512, 128 with the 31-box layout) and waves per env
-  int cus = 0, occ[4][2] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};
+  // CUs; resident blocks per CU of the kernels by shape_index (128, 256 and 512
+  // contacts with the 16-box layout, then with the 31-box layout) and waves per env
+  int cus = 0, occ[6][2] = {};
   pmbs_launch_plan plan;
   // internal streams and events for the concurrent class launches and graph capture
   hipStream_t side = nullptr, cap = nullptr;
@@ -55,7 +55,7 @@ struct pmbs_sim {
     pmbs::StepArgs args;
     pmbs_launch_plan plan;
     int valid = 0;   // the sequence ends with the children's validity launch
-  } captured[2];
+  } captured[3];
   // pinned staging of host rollout inputs: two buffers used in turn, each
   // reusable once the event behind its last uploads has passed
   char* h_stage[2] = {nullptr, nullptr};
@@ -142,8 +142,8 @@ int launch_nb(const pmbs_sim_t* sim);
 // and of the envs that a queued rollout gives the 128-contact kernel
 int small_nb(const pmbs_sim_t* sim);
 int shape_index(int max_contacts, int max_nb);
-// which kernels' layouts a queued rollout takes: 1 when the 128-contact one is
-// that for more than 16 bodies
+// which kernels' layouts a queued rollout takes: 0 all for at most 16 bodies, 1
+// the 128-contact one, 2 none
 int graph_index(const pmbs_sim_t* sim);
 // resident workgroups per CU, as last looked up, of the kernel that a queued
 // rollout under this plan (not the one in force) runs a contact class with

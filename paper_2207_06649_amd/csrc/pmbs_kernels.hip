@@ -2123,7 +2123,7 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
         if constexpr (W == 1) {
           // the first slots in registers (the 512-contact class, which LDS
           // holds to a wave per SIMD, has them for all its slots)
-          constexpr int RS = NB == 16 ? 1 : K == 8 ? 8 : 2;
+          constexpr int RS = K == 2 && NB == 16 ? 1 : K == 8 ? 8 : 2;
           solve_rows<0, 1, RS>(s, lane, n_rows, nwarm, n_extra, p, []() { wave_sync(); }, sums_many, publish, table_update);
         } else {
           solve_rows<1, 2, K / 2>(s, lane, n_rows, nwarm, n_extra, p, []() { __syncthreads(); }, sums_many, [&]() {
@@ -2311,7 +2311,7 @@ __device__ __forceinline__ void init_plane(S& s, const Params& p) {
 // registers: 4096 x 15 takes 1.76 ms so, 1.98 with two (no spills), and took
 // 2.61 with four where three took 2.19.
 template <int K, int W, int NB>
-__global__ __launch_bounds__(64 * W, NB == 16 && W == 1 ? 3 : 2) void step_kernel(StepArgs g) {
+__global__ __launch_bounds__(64 * W, K == 2 && NB == 16 && W == 1 ? 3 : 2) void step_kernel(StepArgs g) {
   __shared__ Smem<K, W, NB> s;
   __shared__ int next;
   init_plane(s, g.p);
@@ -2600,18 +2600,24 @@ hipError_t launch_valid(const ValidArgs& a, hipStream_t stream, int grid) {
 // Calls f(kernel tag) for the kernel of a contact class (128, 256 or 512
 // contacts: 2, 4 or 8 slots of row contacts per lane), a workgroup shape (1
 // or 2 waves per environment; the 512-contact class has one) and the largest
-// body count: 128 contacts and at most 16 boxes, which is what four lanes a
-// body leave room for, take the 16-box layout (4096 x 15 1.76 ms, 2.25 in the
-// 31-box layout; 1024 x 15 1.12 and 1.24; 64 x 9 0.88 and 0.98).
+// body count: at most 16 boxes, which is what four lanes a body leave room for,
+// take the 16-box layout (128 contacts: 4096 x 15 1.76 ms, 2.25 in the 31-box
+// layout; 1024 x 15 1.12 and 1.24; 64 x 9 0.88 and 0.98.  256 contacts, 60
+// substeps of 1024 x 10 cubes in two touching towers: 1.34 and 1.51; 4096 x 8
+// touching cubes, eight workgroups a CU and five: 3.13 and 4.48).
 template <int K_, int W_, int NB_>
 struct Shape {
   static constexpr int K = K_, W = W_, NB = NB_;
 };
 template <class F>
 static auto with_shape(int max_contacts, int waves, int max_nb, F f) {
-  if (max_contacts > 256) return f(Shape<8, 1, 32>{});
-  if (max_contacts > 128) return waves == 2 ? f(Shape<4, 2, 32>{}) : f(Shape<4, 1, 32>{});
-  if (max_nb > 16) return waves == 2 ? f(Shape<2, 2, 32>{}) : f(Shape<2, 1, 32>{});
+  if (max_nb > 16) {
+    if (max_contacts > 256) return f(Shape<8, 1, 32>{});
+    if (max_contacts > 128) return waves == 2 ? f(Shape<4, 2, 32>{}) : f(Shape<4, 1, 32>{});
+    return waves == 2 ? f(Shape<2, 2, 32>{}) : f(Shape<2, 1, 32>{});
+  }
+  if (max_contacts > 256) return f(Shape<8, 1, 16>{});
+  if (max_contacts > 128) return waves == 2 ? f(Shape<4, 2, 16>{}) : f(Shape<4, 1, 16>{});
   return waves == 2 ? f(Shape<2, 2, 16>{}) : f(Shape<2, 1, 16>{});
 }
 

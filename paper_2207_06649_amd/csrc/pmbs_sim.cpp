@@ -273,7 +273,7 @@ pmbs_status rewards_from_pool(pmbs_sim_t* sim, const int32_t* slots, const int32
 }
 
 int shape_index(int max_contacts, int max_nb) {
-  return max_contacts <= 128 ? (max_nb <= 16 ? 0 : 3) : max_contacts <= 256 ? 1 : 2;
+  return (max_contacts <= 128 ? 0 : max_contacts <= 256 ? 1 : 2) + (max_nb <= 16 ? 0 : 3);
 }
 
 int plan_waves(const pmbs_sim_t* sim, int max_contacts) {
@@ -334,7 +334,7 @@ hipError_t enqueue_queued(pmbs_sim_t* sim, const StepArgs& a, hipStream_t stream
   // persistent workgroups of the two classes; with the counts known (no
   // capture) never more than the class has envs, so a batch of at most one
   // env per CU gets one workgroup per CU (none sharing a CU with another)
-  const int nb_s = small_nb(sim), nb_l = sim->max_nb;
+  const int nb_s = small_nb(sim), nb_l = launch_nb(sim);
   int grid_s = class_grid(sim, 128, pl.small_blocks_per_cu, ws, nb_s);
   int grid_l = class_grid(sim, 256, pl.large_blocks_per_cu, wl, nb_l);
   if (skip_empty) {
@@ -426,12 +426,13 @@ int launch_nb(const pmbs_sim_t* sim) {
 
 int small_nb(const pmbs_sim_t* sim) { return std::min(class_split(sim), launch_nb(sim)); }
 
-int graph_index(const pmbs_sim_t* sim) { return small_nb(sim) > 16 ? 1 : 0; }
+int graph_index(const pmbs_sim_t* sim) { return (small_nb(sim) > 16) + (launch_nb(sim) > 16); }
 
 int resident_blocks(const pmbs_sim_t* sim, const pmbs_launch_plan& plan, int max_contacts) {
   const int split = sim->cfg.max_contacts == 128 ? PMBS_MAX_BODIES_PER_ENV : plan.small_max_bodies;
   const int waves = max_contacts <= 128 ? plan.small_waves : max_contacts <= 256 ? plan.large_waves : 1;
-  return sim->occ[shape_index(max_contacts, std::min(split, launch_nb(sim)))][waves == 2 ? 1 : 0];
+  const int nb = max_contacts <= 128 ? std::min(split, launch_nb(sim)) : launch_nb(sim);
+  return sim->occ[shape_index(max_contacts, nb)][waves == 2 ? 1 : 0];
 }
 
 int64_t work_weight(const pmbs_sim_t* sim, const int32_t* act_offset, int e) {

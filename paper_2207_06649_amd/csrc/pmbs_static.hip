@@ -147,7 +147,7 @@ pmbs_status pmbs_sim_rollout_static(pmbs_sim_t* sim, const int32_t* actions, con
   // stream): 128-contact list, 256-contact list, then the fallbacks
   const int mc = sim->cfg.max_contacts;
   const pmbs_launch_plan& pl = sim->plan;
-  const int ws = plan_waves(sim, 128), wl = plan_waves(sim, 256), nb_s = small_nb(sim), nb_l = sim->max_nb;
+  const int ws = plan_waves(sim, 128), wl = plan_waves(sim, 256), nb_s = small_nb(sim), nb_l = launch_nb(sim);
   int32_t* ctl = sc + O_CTL;
   // the children's validity words, after every class
   const bool child_valid = (flags & PMBS_ROLLOUT_CHILD_VALID) && child_slot;
