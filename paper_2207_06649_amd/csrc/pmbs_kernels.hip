@@ -567,30 +567,26 @@ __device__ __forceinline__ void keep_row(S& s, int c, int n_rows, const Contact&
 }
 
 // A wave's row contacts, a lane each: slots FIRST, FIRST + STEP, ... of 64
-// contacts.  RS of its slots are held in registers; the others, in the classes
-// of many contacts on one wave, in a lane's private memory, the next one's on
-// its way while one is updated.  exchange() orders the rows and velocities
+// contacts, all in registers.  exchange() orders the rows and velocities
 // against the other lanes' (of every wave that has part in them); sums(),
 // publish() and table() are the body lanes' part of an iteration.  Bound by the
 // chain of an iteration: velocities gathered, about 90 instructions a slot, rows
 // left in LDS and added by the bodies' lanes.  60 substeps of 1024 x 10 cubes in
 // two touching towers (73 rows), 128-contact class: two waves 1.69 -> 1.16 ms
 // against all rows on the lead wave, one wave 1.78 -> 1.49 with the sums below;
-// 1024 x 30 touching cubes (244 rows, 512-contact class) 10.3 -> 8.6 ms.
-template <int FIRST, int STEP, int RS, class S, class X, class Q, class V, class T>
+// 1024 x 30 touching cubes (244 rows, 512-contact class) 10.3 -> 8.6 ms.  Slots
+// past the second in a lane's private memory instead, the next one's read ahead:
+// 1024 x 15 touching cubes (134 rows, 256-contact class) 1.96 -> 2.13 ms.
+template <int FIRST, int STEP, class S, class X, class Q, class V, class T>
 __device__ __forceinline__ void solve_rows(S& s, int lane, int n_rows, int nwarm, int n_extra, const Params& p, X exchange,
                                            Q sums, V publish, T table) {
   constexpr int N = S::C / 64 / STEP;   // the wave's slots
-  Contact ct[RS], more[N > RS ? N - RS : 1];
-  auto has = [&](int i) { return 64 * (FIRST + STEP * i) < n_rows; };
-  auto at = [&](int i) { return 64 * (FIRST + STEP * i) + lane; };
+  Contact ct[N];
   auto each_slot = [&](auto f) {
 #pragma unroll
-    for (int i = 0; i < RS; ++i)
-      if ((FIRST == 0 && i == 0) || has(i)) f(at(i), ct[i]);
-    if constexpr (N > RS) {
-#pragma unroll 1
-      for (int i = RS; i < N && has(i); ++i) f(at(i), more[i - RS]);
+    for (int i = 0; i < N; ++i) {
+      const int c = 64 * (FIRST + STEP * i);
+      if (c == 0 || c < n_rows) f(c + lane, ct[i]);
     }
   };
   each_slot([&](int c, Contact& q) { q = begin_row(s, c, n_rows, nwarm, n_extra, p); });
@@ -600,25 +596,8 @@ __device__ __forceinline__ void solve_rows(S& s, int lane, int n_rows, int nwarm
   sums();
   for (int it = 0; it < p.iters; ++it) {
     publish();
-    Contact next;
-    if constexpr (N > RS) {
-      if (has(RS)) next = more[0];
-    }
     table();
-#pragma unroll
-    for (int i = 0; i < RS; ++i)
-      if ((FIRST == 0 && i == 0) || has(i)) update_row(s, at(i), ct[i]);
-    if constexpr (N > RS) {
-#pragma unroll 1
-      for (int i = RS; i < N && has(i); ++i) {
-        Contact q = next;
-        if (i + 1 < N && has(i + 1)) next = more[i + 1 - RS];
-        update_row(s, at(i), q);
-        more[i - RS].ln = q.ln;
-        more[i - RS].lt1 = q.lt1;
-        more[i - RS].lt2 = q.lt2;
-      }
-    }
+    each_slot([&](int c, Contact& q) { update_row(s, c, q); });
     exchange();   // the impulse rows
     sums();
   }
@@ -1673,7 +1652,7 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
         const int lane = opaque(threadIdx.x & 63);
         __syncthreads();   // the bodies' data and the contact counts
         if (n_rows > 16) {
-          solve_rows<0, 2, K / 2>(s, lane, n_rows, nwarm, n_extra, p, []() { __syncthreads(); }, []() {},
+          solve_rows<0, 2>(s, lane, n_rows, nwarm, n_extra, p, []() { __syncthreads(); }, []() {},
                                   []() { __syncthreads(); }, []() {});
         } else if constexpr (SPLIT) {
           QuadContact qc = begin_quad(s, lane, n_rows, nwarm, n_extra, p);
@@ -2121,12 +2100,9 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
           }
         };
         if constexpr (W == 1) {
-          // the first slots in registers (the 512-contact class, which LDS
-          // holds to a wave per SIMD, has them for all its slots)
-          constexpr int RS = K == 2 && NB == 16 ? 1 : K == 8 ? 8 : 2;
-          solve_rows<0, 1, RS>(s, lane, n_rows, nwarm, n_extra, p, []() { wave_sync(); }, sums_many, publish, table_update);
+          solve_rows<0, 1>(s, lane, n_rows, nwarm, n_extra, p, []() { wave_sync(); }, sums_many, publish, table_update);
         } else {
-          solve_rows<1, 2, K / 2>(s, lane, n_rows, nwarm, n_extra, p, []() { __syncthreads(); }, sums_many, [&]() {
+          solve_rows<1, 2>(s, lane, n_rows, nwarm, n_extra, p, []() { __syncthreads(); }, sums_many, [&]() {
             publish();
             __syncthreads();
             hold(v);   // as above
