@@ -135,9 +135,9 @@ pmbs_status pmbs_sim_get_state(pmbs_sim_t* sim, float* state_out, int32_t dst_is
  * moves at push_speed for round(|e - s| / (push_speed dt)) substeps and then
  * stays.  A push whose start pose overlaps a box is discarded (Sec. IV-B):
  * the pusher is parked away, the substeps still run and the env status gets
- * PMBS_ENV_PUSH_INVALID.  With more envs than resident workgroups and launch
- * plan order 1 (the default) the step is three launches on the stream: a
- * cost pass (from each env's start pose, for how many substeps boxes or the
+ * PMBS_ENV_PUSH_INVALID.  With more envs than resident workgroups, at least
+ * 16 substeps and launch plan order 1 (the default) the step is three launches
+ * on the stream: a cost pass (from each env's start pose, for how many substeps boxes or the
  * pusher will touch), a sort of each XCD's envs by that estimate, and
  * persistent workgroups taking the envs largest first; every env's result
  * is bitwise that of one workgroup per env (order 0).  Asynchronous. */

@@ -730,7 +730,12 @@ pmbs_status pmbs_sim_step(pmbs_sim_t* sim, const float* push, int32_t push_is_de
   const int mc = sim->cfg.max_contacts, waves = plan_waves(sim, mc);
   hipError_t e = hipSuccess;
   const int nb = launch_nb(sim), grid = class_grid(sim, mc, 0, waves, nb);
-  if (sim->plan.order != 0 && n_substeps > 0 && sim->n_envs > grid && grid >= 8) {
+  // The cost pass, the sort and the queues take 40 to 80 us whatever the substeps
+  // (4096 x 15, one wave, us, plain and ordered: 1 substep 52 and 134, 8 161 and
+  // 191, 16 285 and 269, 32 541 and 435; 4096 x 30, two waves: 16 608 and 627, 32
+  // 1145 and 1075).
+  constexpr int ORDER_SUBSTEPS = 16;
+  if (sim->plan.order != 0 && n_substeps >= ORDER_SUBSTEPS && sim->n_envs > grid && grid >= 8) {
     // more envs than resident workgroups: a cost pass estimates each env's
     // work at its start pose, and persistent workgroups take the envs from
     // queues, largest estimate first, so the short ones fill the end of the

@@ -100,3 +100,20 @@ def test_heap_is_the_same_in_every_kernel(pm, n):
             assert all(np.array_equal(a, b) for a, b in zip(one, two)), (seed, contacts)
             if not one[1][0] & 1:
                 assert all(np.array_equal(a, b) for a, b in zip(one, want)), (seed, contacts)
+
+
+@pytest.mark.parametrize("n_sub", [0, 1, 15, 16, 17])
+def test_step_is_ordered_from_16_substeps(pm, n_sub):
+    """More environments than resident workgroups: a step of few substeps runs
+    one workgroup per environment, one of 16 or more the work-ordered queues;
+    states, status and statistics are those of the plain order."""
+    from paper_2207_06649_amd import scenes
+    b = scenes.concat([scenes.clutter_batch(3, 64, (1, 4))] * 56)   # 3584: past 12 a compute unit
+    sim = pm.Sim(max_envs=b.n_envs, max_bodies=b.n_bodies)
+    out = []
+    for order in (0, 1):
+        sim.set_launch_plan(order=order)
+        sim.set_state(b.env_offset, f32(b.state), f32(b.body))
+        sim.step(b.push.astype(np.float32), n_sub)
+        out.append((sim.get_state(), sim.env_status(), sim.stats()))
+    assert all(np.array_equal(x, y) for x, y in zip(*out))
