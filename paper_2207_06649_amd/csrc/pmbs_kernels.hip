@@ -294,7 +294,7 @@ __device__ __forceinline__ Box pusher_box(const PusherPose& q, const Params& p) 
   return b;
 }
 
-// A DPP quad permutation of a value: lane i of each four takes lane
+// A DPP move of a value; of a quad permutation, lane i of each four takes lane
 // (CTRL >> 2 i) & 3 of them.
 template <int CTRL>
 __device__ __forceinline__ float quad(float v) {
@@ -305,7 +305,17 @@ __device__ __forceinline__ f3 quad(f3 v) {
   return mk(quad<CTRL>(v.x), quad<CTRL>(v.y), quad<CTRL>(v.z));
 }
 constexpr int Q_XOR1 = 0xb1, Q_XOR2 = 0x4e;   // lane ^ 1, lane ^ 2
+constexpr int ROW_HALF_MIRROR = 0x141, ROW_MIRROR = 0x140;   // lane 7 - i of each 8, 15 - i of each 16
 constexpr int Q_LOW = 0x44, Q_HIGH = 0xee;    // lanes 0, 1, 0, 1 and 2, 3, 2, 3
+// The greatest value of lanes 0 to 31, in every lane.
+__device__ __forceinline__ float most32(float v) {
+  v = fmaxf(v, quad<Q_XOR1>(v));
+  v = fmaxf(v, quad<Q_XOR2>(v));
+  v = fmaxf(v, quad<ROW_HALF_MIRROR>(v));
+  v = fmaxf(v, quad<ROW_MIRROR>(v));
+  const int i = __float_as_int(v);
+  return fmaxf(__int_as_float(__builtin_amdgcn_readlane(i, 0)), __int_as_float(__builtin_amdgcn_readlane(i, 16)));
+}
 
 // ------------------------------------------------------------------ clipping
 // the clip buffers of wave wid
@@ -739,16 +749,17 @@ __device__ __forceinline__ f3 aabb_ext(f3 a0, f3 a1, f3 a2, f3 hh, float margin)
             fabsf(a0.z) * hh.x + fabsf(a1.z) * hh.y + fabsf(a2.z) * hh.z + margin);
 }
 
-// Pair number p of the pairs (i, j), i < j < n, in lexicographic order, as
-// i | j << 5; (0, 0) past the last pair.
+// Pair number p of the pairs (i, j), i < j < n <= 32, in lexicographic order, as
+// i | j << 5; (0, 0) past the last pair.  Row i begins at pair i (2 n - 1 - i) / 2;
+// the root's inverse of that is off by less than one row, since the roots of a
+// row's last pair and the next row's first are 0.03 apart or more.  (Eight a
+// lane at an env's start in the 31-box layout: one substep of 30 boxes on two
+// waves 25.8 -> 23.0 us against a rounded root and loops.)
 __device__ __forceinline__ unsigned pair_of(int p, int n) {
-  if (p >= n * (n - 1) / 2) return 0u;
-  const float m = (float)(2 * n - 1);
-  int i = (int)(0.5f * (m - sqrtf(fmaxf(m * m - 8.0f * (float)p, 0.0f))));
-  i = min(max(i, 0), n - 2);
-  while (i > 0 && i * (2 * n - i - 1) / 2 > p) --i;
-  while ((i + 1) * (2 * n - i - 2) / 2 <= p) ++i;
-  return (unsigned)(i | ((p - i * (2 * n - i - 1) / 2 + i + 1) << 5));
+  const int m = 2 * n - 1;
+  int i = (int)(0.5f * ((float)m - __builtin_amdgcn_sqrtf((float)max(m * m - 8 * p, 0))));
+  i += i * (m - i) / 2 > p ? -1 : (i + 1) * (m - i - 1) / 2 <= p ? 1 : 0;
+  return p < n * (n - 1) / 2 ? (unsigned)(i | (p - i * (m - i) / 2 + i + 1) << 5) : 0u;
 }
 
 // The number of pair (i, j), i < j < n, in that order.
@@ -1037,11 +1048,8 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
     reach = fmaxf(reach, sqrtf(dot(hl, hl)));
     far = sum_abs(xyz(s.pos[lane]));
   }
-  for (int o = 32; o > 0; o >>= 1) {
-    reach = fmaxf(reach, __shfl_xor(reach, o, 64));
-    far = fmaxf(far, __shfl_xor(far, o, 64));
-  }
-  reach = uniform(4.5f * reach + 4.0f * p.margin);
+  reach = uniform(4.5f * most32(reach) + 4.0f * p.margin);
+  far = most32(far);
   // sums are rounded up, and grow with the distance from where the push began
   constexpr float MOVE_UP = 1.0f + 0x1p-20f;
   float move_round = 4.8e-7f * (far + reach);
@@ -1615,9 +1623,11 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
       if (lead) {
         int tot;
         const int off = wave_excl_scan(j == 0 ? nt : 0, &tot);
-        if (first) {
-          int c = off;
+        const int off_b = off - (j == 0 ? 0 : nt);
+        if (active) {   // lane j the body's contacts j, j + L, ...
+          int c = off_b;
           for (unsigned m = mask; m; m &= m - 1, ++c) {
+            if ((c - off_b) % L != j) continue;
             const int kc = __builtin_ctz(m);
             const float sx = (kc & 1) ? h.x : -h.x, sy = (kc & 2) ? h.y : -h.y, sz = (kc & 4) ? h.z : -h.z;
             const f3 vtx = x + mk(c0.x * sx + c1.x * sy + c2.x * sz, c0.y * sx + c1.y * sy + c2.y * sz,
