@@ -194,8 +194,9 @@ typedef struct pmbs_launch_plan {
                                   pmbs_sim_step: 1 largest work estimate first (see there), 0 index order */
   int32_t small_waves;         /* workgroup shape of the 128-contact class: waves per environment (1 or
                                   2: a second wave takes the broadphase, every second narrowphase
-                                  pass and, with more than 16 bodies, up to 16 contacts between
-                                  boxes; bitwise the same result) */
+                                  pass, of more than 16 contacts between boxes every second 64, and
+                                  all of fewer when an environment of the launch has more than 16
+                                  bodies; bitwise the same result) */
   int32_t large_waves;         /* the same for the 256-contact class (and its overflow re-runs) */
 } pmbs_launch_plan;
 

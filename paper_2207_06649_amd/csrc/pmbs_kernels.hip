@@ -8,13 +8,14 @@
 // Lane roles inside the lead wave: four lanes per body in the 16-box layout,
 // two in the 31-box layout, all holding the body's whole state and together
 // its first four table contacts; every other contact is a row contact, one
-// per lane and slot.  Shared state goes through LDS: body frames, AABBs, the
-// pair list, the row contacts' staging array (reused for the impulse exchange
-// of the solver), per-body incidence lists, warm-start keys and impulses, and
-// the clip polygons of face clipping.
+// per four lanes or, of more than 16, one per lane and slot.  Shared state goes
+// through LDS: body frames, AABBs, the pair list, the row contacts' staging
+// array (reused for the impulse exchange of the solver), per-body incidence
+// lists, warm-start keys and impulses, and the clip polygons of face clipping.
 //
-// Per substep (all in one launch, state stays in registers/LDS; HBM is
-// touched once in and once out per call):
+// Per substep (all in one launch, the state in registers and LDS, read from HBM
+// once and written once per call; the kernel at three waves per SIMD spills
+// registers, which leave the L2: see step_kernel):
 //   velocity stage -> frames -> AABB broadphase -> box-plane and
 //   box-box/pusher-box contacts (15-axis SAT, Sutherland-Hodgman face
 //   clipping or edge-edge closest points) -> contact prep (mass splitting,
@@ -106,10 +107,10 @@ __device__ __forceinline__ float uniform(float v) {
 }
 __device__ __forceinline__ f3 uniform(f3 v) { return mk(uniform(v.x), uniform(v.y), uniform(v.z)); }
 
-// Orders the LDS accesses of the wave's lanes around this point.  A
-// workgroup is one wave and a wave's LDS operations are performed in issue
-// order, so a wavefront-scope fence (no wait instruction) plus a
-// code-motion barrier suffices; no wait for outstanding LDS operations.
+// Orders the LDS accesses of one wave's lanes around this point (of two waves:
+// sync_all).  A wave's LDS operations are performed in issue order, so a
+// wavefront-scope fence (no wait instruction) plus a code-motion barrier
+// suffices; no wait for outstanding LDS operations.
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -900,7 +901,7 @@ __device__ __forceinline__ void sync_all() {
 // ts): a table contact's only body is the lanes' own, so its update needs no
 // memory, and the body's sum over these contacts is a DPP exchange among
 // the L lanes.  The other contacts (pairs, the pusher, a box's fifth and
-// later table corner) are row contacts: one per lane of the lead wave and
+// later table corner) are row contacts: four lanes each, or one per lane and
 // slot, their velocities gathered from and their impulse rows left in LDS,
 // where the body lanes add them after the table contacts, the even and the
 // odd entries of the body's contact list separately, as ever.
@@ -921,8 +922,11 @@ __device__ __forceinline__ void sync_all() {
 // of dependent instructions, a substep after the other, where it has one.
 //
 // With W > 1 waves per environment the second wave tests the broadphase pairs
-// while the lead finds the table contacts, and takes every second narrowphase
-// pass of eight pairs; the results are bitwise those of W = 1.  Uniform
+// while the lead finds the table contacts, takes every second narrowphase pass
+// (of four or eight pairs), and updates row contacts while the lead updates its
+// lanes' table contacts: of more than 16 every second slot of 64, and up to 16
+// in quads, all of them, in the 31-box layout.  The results are bitwise those of
+// W = 1.  Uniform
 // decisions (push validity, rewards, overflow) are taken by every wave from
 // the same LDS data, so all waves run the same loops and meet at the same
 // barriers.
@@ -2295,7 +2299,8 @@ __device__ __forceinline__ void init_plane(S& s, const Params& p) {
 
 // Three waves per SIMD for the kernel of the many small environments, at 168
 // registers: 4096 x 15 takes 1.76 ms so, 1.98 with two (no spills), and took
-// 2.61 with four where three took 2.19.
+// 2.61 with four where three took 2.19.  Its 43 spilled registers a lane are
+// most of what the launch moves through HBM, 1 % of a copy's rate.
 template <int K, int W, int NB>
 __global__ __launch_bounds__(64 * W, K == 2 && NB == 16 && W == 1 ? 3 : 2) void step_kernel(StepArgs g) {
   __shared__ Smem<K, W, NB> s;

@@ -641,8 +641,9 @@ pmbs_status pmbs_sim_get_launch_plan(const pmbs_sim_t* sim, pmbs_launch_plan* pl
 // Each copy is a launch of about 4.7 us whatever its size here, so rows that
 // lie end to end on both sides (a simulator filled to max_bodies, as a
 // planner's is) go as one (a step of 64 x 9 with its state read back 929 ->
-// 907 us), and rows of device memory otherwise as one strided copy; rows to or from host memory then go one by one, since the
-// runtime stages pageable memory by whole copies.
+// 907 us), and rows of device memory otherwise as one strided copy; rows to or
+// from host memory then go one by one, since the runtime stages pageable memory
+// by whole copies.
 static hipError_t copy_rows(float* dst, int dst_stride, const float* src, int src_stride, int n, hipMemcpyKind kind,
                             hipStream_t st) {
   if (n <= 0) return hipSuccess;
