@@ -23,10 +23,10 @@ struct StepArgs {
   const int* env_offset;    // [n_envs+1]
   const float4* push;       // [n_envs] (x_s, y_s, x_e, y_e) or null
   uint32_t* env_status;     // [n_envs]
-  int* dbg_count;           // collide-only outputs
+  int* dbg_count;           // collide kernel's outputs
   float* dbg_contacts;
   long long* stats;         // optional [n_envs][3]: sums over substeps of contacts, candidate pairs; substeps
-  int n_envs, env_base, n_substeps, stride, collide_only;
+  int n_envs, env_base, n_substeps, stride;
   // rollout mode: contour pushes per env (actions[act_offset[e]..act_offset[e+1]),
   // packed obj * n_dirs + dir), reward after each push, child snapshot
   const int* actions;
@@ -124,6 +124,8 @@ hipError_t launch_step_class(const StepArgs& a, int max_contacts, hipStream_t st
 // estimate from its start pose; order: each XCD's contiguous run of envs by descending estimate
 // into order[0, n), and the eight queue counters queue[0..7] cleared
 hipError_t launch_cost(const StepArgs& a, int max_contacts, hipStream_t stream, int waves, int max_nb);
+// one block per env writes its contact list at the start pose
+hipError_t launch_collide(const StepArgs& a, int max_contacts, hipStream_t stream, int max_nb);
 hipError_t launch_order(const int* key, int n, int* order, int* queue, hipStream_t stream);
 hipError_t launch_zero(int* p, int n, hipStream_t stream);
 hipError_t launch_reward(const RewardArgs& a, hipStream_t stream);

@@ -930,7 +930,11 @@ __device__ __forceinline__ void sync_all() {
 // decisions (push validity, rewards, overflow) are taken by every wave from
 // the same LDS data, so all waves run the same loops and meet at the same
 // barriers.
-template <int K, int W, int NB, bool COST>
+//
+// The cost pass and pmbs_sim_collide end in the first substep, after its
+// contacts: their kernels hold no more than that.
+enum class Run { STEP, COST, COLLIDE };
+template <int K, int W, int NB, Run RUN>
 __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, const int e) {
   using S = Smem<K, W, NB>;
   constexpr int C = S::C, PLANE = S::PLANE, MB = S::MB;
@@ -1139,7 +1143,7 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
   pdir = uniform(pdir);
   n_move = __builtin_amdgcn_readfirstlane(n_move);
 
-  const int n_sub = g.collide_only ? 1 : g.n_substeps;
+  const int n_sub = g.n_substeps;
   // impulses are carried within one push only: the row contacts' (nwarm of
   // them, in LDS) and the table contacts', in the lanes, whose corners are
   // the bits of corners
@@ -1577,7 +1581,7 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
     const int nc = nc_raw < C ? nc_raw : C;
     n_rows = n_rows < row_cap ? n_rows : row_cap;
     if constexpr (W > 1) n_rows = __builtin_amdgcn_readfirstlane(n_rows);
-    if constexpr (COST) {
+    if constexpr (RUN == Run::COST) {
       // The work estimate of the env's push from its start pose; nothing else
       // is written.  A substep with row contacts costs about 2.6 times one
       // without (the solver's ten iterations through LDS and a live
@@ -1614,7 +1618,7 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
     c1 = xyz(s.col[1][bl]);
     c2 = xyz(s.col[2][bl]);
 
-    if (g.collide_only) {
+    if constexpr (RUN == Run::COLLIDE) {
       // the whole list: table contacts at their rank, then the staged pairs
       float* out = g.dbg_contacts + (size_t)e * C * 9;
       auto put = [&](int c, int a, int bb, f3 pt, f3 n, float sep) {
@@ -2299,7 +2303,7 @@ __device__ __forceinline__ void init_plane(S& s, const Params& p) {
 
 // Three waves per SIMD for the kernel of the many small environments, at 168
 // registers: 4096 x 15 takes 1.76 ms so, 1.98 with two (no spills), and took
-// 2.61 with four where three took 2.19.  Its 43 spilled registers a lane are
+// 2.61 with four where three took 2.19.  Its 53 spilled registers a lane are
 // most of what the launch moves through HBM, 1 % of a copy's rate.
 template <int K, int W, int NB>
 __global__ __launch_bounds__(64 * W, K == 2 && NB == 16 && W == 1 ? 3 : 2) void step_kernel(StepArgs g) {
@@ -2324,7 +2328,7 @@ __global__ __launch_bounds__(64 * W, K == 2 && NB == 16 && W == 1 ? 3 : 2) void 
       __syncthreads();
     }
     if (wi >= n_work) break;
-    run_env<K, W, NB, false>(s, g, __builtin_amdgcn_readfirstlane(g.order ? g.order[seg + wi] : wi));
+    run_env<K, W, NB, Run::STEP>(s, g, __builtin_amdgcn_readfirstlane(g.order ? g.order[seg + wi] : wi));
     if (!g.queue) break;
     __syncthreads();
   }
@@ -2338,7 +2342,18 @@ __global__ __launch_bounds__(64 * W, 2) void cost_kernel(StepArgs g) {
   __shared__ Smem<K, W, NB> s;
   init_plane(s, g.p);
   const int e = g.env_base + xcd_item(blockIdx.x, gridDim.x);
-  if (e < g.n_envs) run_env<K, W, NB, true>(s, g, e);
+  if (e < g.n_envs) run_env<K, W, NB, Run::COST>(s, g, e);
+}
+
+// pmbs_sim_collide: one block per env writes its contact list at the current
+// poses (4096 x 5, 128 contacts: 27.5 us by the step kernel at three waves per
+// SIMD, 23.0 so; 4096 x 21, 512 contacts 77.5 and 69.3).
+template <int K, int NB>
+__global__ __launch_bounds__(64, 2) void collide_kernel(StepArgs g) {
+  __shared__ Smem<K, 1, NB> s;
+  init_plane(s, g.p);
+  const int e = xcd_item(blockIdx.x, gridDim.x);
+  if (e < g.n_envs) run_env<K, 1, NB, Run::COLLIDE>(s, g, e);
 }
 
 // Schedule of a queued step: each XCD's contiguous run of envs (xcd_start)
@@ -2638,6 +2653,17 @@ hipError_t launch_cost(const StepArgs& a, int max_contacts, hipStream_t stream, 
   return with_shape(max_contacts, waves, max_nb, [&](auto t) {
     using T = decltype(t);
     hipLaunchKernelGGL((cost_kernel<T::K, T::W, T::NB>), dim3(n), dim3(64 * T::W), 0, stream, c);
+    return hipGetLastError();
+  });
+}
+
+hipError_t launch_collide(const StepArgs& a, int max_contacts, hipStream_t stream, int max_nb) {
+  if (a.n_envs <= 0 || !a.dbg_count || !a.dbg_contacts) return a.n_envs <= 0 ? hipSuccess : hipErrorInvalidValue;
+  StepArgs c = a;
+  c.n_substeps = 1;
+  return with_shape(max_contacts, 1, max_nb, [&](auto t) {
+    using T = decltype(t);
+    hipLaunchKernelGGL((collide_kernel<T::K, T::NB>), dim3(c.n_envs), dim3(64), 0, stream, c);
     return hipGetLastError();
   });
 }

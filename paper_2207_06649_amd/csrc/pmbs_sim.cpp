@@ -1066,11 +1066,9 @@ pmbs_status pmbs_sim_collide(pmbs_sim_t* sim, const float* push, int32_t push_is
   if (st != PMBS_OK) return st;
   StepArgs a = step_args(sim);
   a.push = d_push;
-  a.n_substeps = 1;
-  a.collide_only = 1;
   a.dbg_count = d_counts;
   a.dbg_contacts = d_contacts;
-  hipError_t e = launch_step(a, sim->cfg.max_contacts, sim->stream, 1, launch_nb(sim));
+  hipError_t e = launch_collide(a, sim->cfg.max_contacts, sim->stream, launch_nb(sim));
   if (e != hipSuccess) return hip_fail(e, "collide launch");
   return PMBS_OK;
 }
