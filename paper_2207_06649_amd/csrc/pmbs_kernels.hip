@@ -2046,11 +2046,13 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
           keep_quad(s, lane, n_rows, qc);
         }
       } else {
-        // the same sums where a body has many rows: its lane's first 12
-        // entries stay in registers, a row's offset and bit 0 for a term to
-        // subtract, and are loaded in groups, all of a group in flight together
-        // (18 rows a body: 2000 -> 1000 cycles against one entry after the other)
-        constexpr int E = 12, G = 4;
+        // the same sums where a body has many rows: its lane's first 12 entries
+        // stay in registers, a row's offset and bit 0 for a term to subtract, and
+        // are loaded in groups, all of a group in flight together (18 rows a body:
+        // 2000 -> 1000 cycles against one entry after the other).  In the
+        // 512-contact class, that of piles, 16 (1024 x 16 in a pile, 20 rows a
+        // body: 5.80 -> 5.65 ms; towers with 8 a body 1 to 2 % slower).
+        constexpr int E = K == 8 ? 16 : 12, G = 4;
         unsigned entry[E];
         bool group[E / G];   // some lane has an entry in the group
 #pragma unroll
