@@ -2061,7 +2061,7 @@ __device__ __forceinline__ void run_env(Smem<K, W, NB>& s, const StepArgs& g, co
           entry[u] = zrow | 1u;
           if (group[u / G]) {
             const int i = k0 + 2 * u;
-            const unsigned code = s.inc[inc0 + min(i, max(n_inc - 1, 0))];
+            const unsigned code = s.inc[i < n_inc ? inc0 + i : 0];
             if (i < n_inc) entry[u] = (ang_lane ? row_ang(code) : row_lin(code)) | (~code & 1u);
           }
         }
